@@ -1164,6 +1164,11 @@ struct PairStage {
   T xs[2][kPair][2][kWave + 1];   // x faces
   T ys[2][kPair + 1][2][kWave];   // y faces
   T gs[2][kPair][2][2][kWave];    // g^n (0) and g^{n+1} (1) of each cell
+  // the Gauss recurrences' second factors, exp(-2 lam h^2) - 1: the same in both halves of v
+  // and at every u node, so formed once per workgroup and not by every wavefront
+  T qx[kPair][kWave + 1];
+  T qy[kPair + 1][kWave];
+  T qg[kPair][2][kWave];
 };
 
 // A Gaussian factor exp(-lam (x - c)^2) along the uniform nodes x0, x0 + h, x0 + 2h, ...:
@@ -1339,17 +1344,10 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
   const T Af1 = st.cell[r1][C_AF][lane], AdF1 = st.cell[r1][C_ADF][lane];
   const Half hu = axis_half(P.K, SU, false), hv = axis_half(P.M, sv, false);
   const int hf = sv > 0 ? 0 : 1;
-  const T hstep = T(sv * P.dv);
-  const T h2 = T(-2) * hstep * hstep;
-  const T qx0 = expm1_of(h2 * st.sx[r0][sf(R_LAM)][xo]);
-  const T qx1 = expm1_of(h2 * st.sx[r1][sf(R_LAM)][xo]);
-  const T qyi = expm1_of(h2 * st.sy[fin_r][sf(R_LAM)][lane]);
-  const T qym = expm1_of(h2 * st.sy[fmid_r][sf(R_LAM)][lane]);
-  const T qyo = expm1_of(h2 * st.sy[fout_r][sf(R_LAM)][lane]);
-  const T qn0 = expm1_of(h2 * st.cell[r0][C_LAMN][lane]);
-  const T q10 = expm1_of(h2 * st.cell[r0][C_LAM1][lane]);
-  const T qn1 = expm1_of(h2 * st.cell[r1][C_LAMN][lane]);
-  const T q11 = expm1_of(h2 * st.cell[r1][C_LAM1][lane]);
+  const T qx0 = st.qx[r0][xo], qx1 = st.qx[r1][xo];
+  const T qyi = st.qy[fin_r][lane], qym = st.qy[fmid_r][lane], qyo = st.qy[fout_r][lane];
+  const T qn0 = st.qg[r0][0][lane], q10 = st.qg[r0][1][lane];
+  const T qn1 = st.qg[r1][0][lane], q11 = st.qg[r1][1][lane];
   const T two_idx = T(2.0 * P.inv_dx), two_idy = T(2.0 * P.inv_dy);
   int a0, a1;
   chunk_range(hu.count, g, G, a0, a1);
@@ -1560,12 +1558,8 @@ __device__ __forceinline__ void ghost_fill_quadrant(const KParams& P, const Pair
   const unsigned w0 = st0 ? oC : kDropOffset, w1 = st1 ? oD : kDropOffset;
   const Half hu = axis_half(P.K, SU, false), hv = axis_half(P.M, sv, false);
   const int hf = sv > 0 ? 0 : 1;
-  const T hstep = T(sv * P.dv);
-  const T h2 = T(-2) * hstep * hstep;
-  const T qn0 = expm1_of(h2 * st.cell[r0][C_LAMN][lane]);
-  const T q10 = expm1_of(h2 * st.cell[r0][C_LAM1][lane]);
-  const T qn1 = expm1_of(h2 * st.cell[r1][C_LAMN][lane]);
-  const T q11 = expm1_of(h2 * st.cell[r1][C_LAM1][lane]);
+  const T qn0 = st.qg[r0][0][lane], q10 = st.qg[r0][1][lane];
+  const T qn1 = st.qg[r1][0][lane], q11 = st.qg[r1][1][lane];
   const long long pstep = (long long)hv.step * P.PS;
   int a0, a1;
   chunk_range(hu.count, g, G, a0, a1);
@@ -1654,19 +1648,35 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
   // the ghost lane whose neighbouring cell is this segment's writes the ghost column (the
   // outlet column can also be the right halo of the segment before the last)
   const bool ghost_w = ghost_lane && (i < 0 || lane <= kHalo + kTileU);
-  // the Eq. (4) inputs of wavefronts 0 and 1 (row jb + w), requested before the stage so that
-  // their latency overlaps the stage's
-  double eWn[4] = {1.0, 0.0, 0.0, 1.0}, eF[4][4] = {};
-  if (w < kPair) {
-    const int jr = clampi(jb + w, 0, P.ny - 1);
+  // The prologue fills the stage with one barrier at its end.  Its parts do not read one another's
+  // LDS, so each wavefront first requests the inputs of its own part, then its share of the
+  // face records, works while those are in flight, and writes them to LDS last.  Parts:
+  //   wavefronts 0, 1   Eq. (4) and the cells' data of row jb + w, the Gauss starts of g^{n+1}
+  //   face units        the Gauss starts of 64 faces: x faces of row jb + r (unit r) and y face
+  //                     row jb + r (unit 2 + r); with eight wavefronts one unit to each of 2..6,
+  //                     with four 2 1/2 units (a half: one half of v) to each of 2, 3
+  //   g^n starts        wavefront 7, or with four wavefronts with the cells of each row
+  // What bounds it is the longest chain of dependent FP64 work (Eq. (4), two states, eight
+  // exponentials) on otherwise idle SIMDs; with the g^n starts and the recurrence factors (nine
+  // expm1 that every wavefront formed for itself) shared out, the update of 40 x 20 cells at
+  // 29^2 went from 22.3 to 20.3 us, of 400 x 100 at 40^2 from 332 to 327 us (FP64).
+  double eWn[kPair][4] = {{1.0, 0.0, 0.0, 1.0}, {1.0, 0.0, 0.0, 1.0}}, eF[4][4] = {};
+  const int row0 = w < kPair ? w : 0;  // first row of the wavefront's cells
+  const bool gn_wave = kCh == 2 && w == 7;
+  if (w < kPair || gn_wave) {
     const int ci = valid ? i : 0;
-    const size_t cc = (size_t)jr * P.nx + ci;
-    if (valid) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) eWn[k] = W[4 * cc + k];
+    for (int r = 0; r < (kCh == 2 ? kPair : 1); ++r) {
+      if (r > 0 && !gn_wave) continue;
+      const size_t cc = (size_t)clampi(jb + row0 + r, 0, P.ny - 1) * P.nx + ci;
+      if (valid) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) eWn[r][k] = W[4 * cc + k];
+      }
     }
-    if constexpr (!kFill) {
+    if (!kFill && w < kPair) {
       // the fluxes through the cell's left and right x faces and its lower and upper y faces
+      const int jr = clampi(jb + w, 0, P.ny - 1);
       const UGKS_GLOBAL double* fl = recx + (size_t)R_FX * nfx + (size_t)jr * (P.nx + 1) + ci;
       const UGKS_GLOBAL double* fb = recy + (size_t)R_FX * nfy + (size_t)jr * P.nx + ci;
 #pragma unroll
@@ -1678,17 +1688,43 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
       }
     }
   }
-  // stage the records of the pair's faces: x faces i0-2 .. i0+62 of both rows, y face rows
+  // face units of this wavefront: [fu0, fu1), all of both halves but the first half of the last
+  // (wavefront 2 of four) or the second half of the first (wavefront 3 of four)
+  constexpr int kUnits = kCh == 2 ? 1 : 3;
+  const int fu0 = kCh == 2 ? w - kPair : (w == 2 ? 0 : 2);
+  const bool face_wave = !kFill && w >= kPair && (kCh == 1 || w < 7);
+  double flam[kUnits], fvel[kUnits];
+  auto load_face_inputs = [&]() {
+    if (!face_wave) return;
+#pragma unroll
+    for (int n = 0; n < kUnits; ++n) {
+      const int u = fu0 + n;
+      if (u < kPair) {
+        const UGKS_GLOBAL double* rec = recx +
+                                        (size_t)clampi(jb + u, 0, P.ny - 1) * (P.nx + 1) +
+                                        clampi(i0 - kHalo + lane, 0, P.nx);
+        flam[n] = rec[(size_t)R_LAM * nfx];
+        fvel[n] = rec[(size_t)R_VY * nfx];
+      } else {
+        const UGKS_GLOBAL double* rec = recy + (size_t)clampi(jb + u - kPair, 0, P.ny) * P.nx +
+                                        clampi(i0 - kHalo + lane, 0, P.nx - 1);
+        flam[n] = rec[(size_t)R_LAM * nfy];
+        fvel[n] = rec[(size_t)R_VY * nfy];
+      }
+    }
+  };
+  if constexpr (sizeof(T) == 8) load_face_inputs();
+  // the records of the pair's faces: x faces i0-2 .. i0+62 of both rows, y face rows
   // jb .. jb+2 below / above lanes 0..63; indices clamped into the mesh for lanes and rows
-  // outside it.  Every thread issues all its record loads before it writes any to LDS: one
-  // trip of a load-then-store loop per value would wait out one memory latency per trip.
+  // outside it.  Every thread issues all its record loads before it uses any: one trip of a
+  // load-then-store loop per value would wait out one memory latency per trip.
+  constexpr int kThreads = kWave * kQuads * kCh;  // the launch's workgroup size
+  constexpr int kNX = kPair * (kWave + 1) * kSF, kNY = (kPair + 1) * kWave * kSF;
+  constexpr int kItX = kFill ? 1 : (kNX + kThreads - 1) / kThreads;
+  constexpr int kItY = kFill ? 1 : (kNY + kThreads - 1) / kThreads;
+  T vx[kItX], vy[kItY];
   if constexpr (!kFill) {
-    constexpr int kThreads = kWave * kQuads * kCh;  // the launch's workgroup size
-    constexpr int kNX = kPair * (kWave + 1) * kSF, kNY = (kPair + 1) * kWave * kSF;
-    constexpr int kItX = (kNX + kThreads - 1) / kThreads;
-    constexpr int kItY = (kNY + kThreads - 1) / kThreads;
     auto fld_of = [](int s) { return s <= sf(R_UX) ? R_GC + s : R_GC + s + 1; };  // skip R_VY
-    double vx[kItX], vy[kItY];
 #pragma unroll
     for (int it = 0; it < kItX; ++it) {
       const int e = threadIdx.x + it * kThreads;
@@ -1697,7 +1733,7 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
         const int s = rem / (kWave + 1), fc = rem - s * (kWave + 1);  // faces fastest
         const int fi = clampi(i0 - kHalo + fc, 0, P.nx);
         const int row = clampi(jb + r, 0, P.ny - 1);
-        vx[it] = recx[(size_t)fld_of(s) * nfx + (size_t)row * (P.nx + 1) + fi];
+        vx[it] = T(recx[(size_t)fld_of(s) * nfx + (size_t)row * (P.nx + 1) + fi]);
       }
     }
 #pragma unroll
@@ -1708,16 +1744,18 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
         const int s = rem / kWave, fc = rem - s * kWave;  // faces fastest
         const int fi = clampi(i0 - kHalo + fc, 0, P.nx - 1);
         const int row = clampi(jb + r, 0, P.ny);
-        vy[it] = recy[(size_t)fld_of(s) * nfy + (size_t)row * P.nx + fi];
+        vy[it] = T(recy[(size_t)fld_of(s) * nfy + (size_t)row * P.nx + fi]);
       }
     }
+  }
+  auto store_records = [&]() {
 #pragma unroll
     for (int it = 0; it < kItX; ++it) {
       const int e = threadIdx.x + it * kThreads;
       if (e < kNX) {
         const int r = e / ((kWave + 1) * kSF), rem = e - r * ((kWave + 1) * kSF);
         const int s = rem / (kWave + 1), fc = rem - s * (kWave + 1);
-        st.sx[r][s][fc] = T(vx[it]);
+        st.sx[r][s][fc] = vx[it];
       }
     }
 #pragma unroll
@@ -1726,11 +1764,15 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
       if (e < kNY) {
         const int r = e / (kWave * kSF), rem = e - r * (kWave * kSF);
         const int s = rem / kWave, fc = rem - s * kWave;
-        st.sy[r][s][fc] = T(vy[it]);
+        st.sy[r][s][fc] = vy[it];
       }
     }
+  };
+  // FP32 storage has no registers to hold its share of the records through its part
+  if constexpr (!kFill && sizeof(T) == 4) {
+    store_records();
+    load_face_inputs();
   }
-  __syncthreads();
   const double hstep = P.dv;
   // A start value below the normal range cannot be carried up to a peak that lies beyond the
   // chunk's first node: such a state (speed ratio |V| lambda^(1/2) above about 26 across v)
@@ -1756,6 +1798,16 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
     r[col] = T(exp(-lam * hs * (2.0 * d + hs)));
     lost = lost || (x > 700.0 && (h == 0 ? c > v0 : c < v0));
   };
+  // exp(-2 lam h^2) - 1, in the arithmetic type
+  auto second_factor = [&](double lam) {
+    const T h = T(hstep);
+    return expm1_of(T(-2) * h * h * T(lam));
+  };
+  // Gauss starts of g^n of the cells of row jb + r from their primitive state p
+  auto start_gn = [&](const Prim& p, int r) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) start(p.lam, p.V, h, st.gs[h][r][0][0], st.gs[h][r][0][1], lane);
+  };
   if (w < kPair) {
     // Eq. (4) for row jb + w, and the cell's Maxwellians of W^n and W^{n+1} with the
     // weights of Eq. (3) solved for f^{n+1}: f1 = Af f + AdF dF + (A1 g^{n+1} + An g^n)
@@ -1766,7 +1818,7 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
     const size_t cc = (size_t)jr * P.nx + ci;
     double Wn[4], W1[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) Wn[k] = eWn[k];
+    for (int k = 0; k < 4; ++k) Wn[k] = eWn[0][k];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if constexpr (kFill) {  // the ghost states of the current W
@@ -1857,39 +1909,38 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
     const double cell[C_COUNT] = {pn.lam, pn.U, pn.V, p1.lam, p1.U, p1.V, An, A1, Af, AdF};
 #pragma unroll
     for (int n = 0; n < C_COUNT; ++n) st.cell[r][n][lane] = T(cell[n]);
-    // Gauss starts of g^n and g^{n+1} of this cell in both halves of v
+    st.qg[r][0][lane] = second_factor(pn.lam);
+    st.qg[r][1][lane] = second_factor(p1.lam);
+    // Gauss starts of this cell in both halves of v
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      start(pn.lam, pn.V, h, st.gs[h][r][0][0], st.gs[h][r][0][1], lane);
+    for (int h = 0; h < 2; ++h)
       start(p1.lam, p1.V, h, st.gs[h][r][1][0], st.gs[h][r][1][1], lane);
-    }
-  } else if (!kFill) {
-    // Gauss starts of the faces (FP64 records): wavefront 2 + r takes the x faces of row
-    // jb + r; the y face rows jb .. jb + 2 go one to a wavefront 4..6 with eight wavefronts,
-    // else row jb to wavefront 2 and rows jb + 1, jb + 2 to wavefront 3
-    const int r = w - kPair;
-    if (r < kPair) {
-      const int jr = clampi(jb + r, 0, P.ny - 1);
-      for (int fc = lane; fc < kWave + 1; fc += kWave) {
-        const int fi = clampi(i0 - kHalo + fc, 0, P.nx);
-        const UGKS_GLOBAL double* rec = recx + (size_t)jr * (P.nx + 1) + fi;
-        const double lam = rec[(size_t)R_LAM * nfx], vy = rec[(size_t)R_VY * nfx];
+    if constexpr (kCh == 1) start_gn(pn, r);
+  } else if (gn_wave) {
+    // g^n of both rows' cells; a ghost column's g^n has weight zero, so any finite state serves
 #pragma unroll
-        for (int h = 0; h < 2; ++h) start(lam, vy, h, st.xs[h][r][0], st.xs[h][r][1], fc);
+    for (int r = 0; r < kPair; ++r) {
+      Prim pn{};
+      if (!P.collisionless) (void)prim_of(eWn[r], pn, P.lam_c);
+      start_gn(pn, r);
+    }
+  } else if (face_wave) {
+    // Gauss starts of the face units (FP64 records).  The last face of an x row (the right
+    // face of lane 63) starts nothing: no written cell takes a flux from it.
+#pragma unroll
+    for (int n = 0; n < kUnits; ++n) {
+      const int u = fu0 + n;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (kCh == 1 && ((w == 2 && n == 2 && h == 1) || (w == 3 && n == 0 && h == 0))) continue;
+        T* e = u < kPair ? st.xs[h][u][0] : st.ys[h][u - kPair][0];
+        T* r = u < kPair ? st.xs[h][u][1] : st.ys[h][u - kPair][1];
+        start(flam[n], fvel[n], h, e, r, lane);
+        if (h == 0) (u < kPair ? st.qx[u] : st.qy[u - kPair])[lane] = second_factor(flam[n]);
       }
     }
-    const int fr0 = kCh == 2 ? r - kPair : (r == 0 ? 0 : 1);
-    const int fr1 = kCh == 2 ? min(r - kPair + 1, kPair + 1) : (r == 0 ? 1 : kPair + 1);
-    for (int fr = max(fr0, 0); fr < fr1; ++fr) {
-      const int fi = clampi(i0 - kHalo + lane, 0, P.nx - 1);
-      const int row = clampi(jb + fr, 0, P.ny);
-      const UGKS_GLOBAL double* rec = recy + (size_t)row * P.nx + fi;
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        start(rec[(size_t)R_LAM * nfy], rec[(size_t)R_VY * nfy], h, st.ys[h][fr][0],
-              st.ys[h][fr][1], lane);
-    }
   }
+  if constexpr (!kFill && sizeof(T) == 8) store_records();
   if (lost && (valid || ghost_w)) *P.flag = 1;
   __syncthreads();
   // the workgroup's chunks kCh g .. kCh g + kCh - 1 of the quadrant's kCh G chunks
