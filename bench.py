@@ -26,11 +26,11 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "5f1b9002a1ceacde6a595e0c9eee1da5c665af1dc74d65d594c187ebbca0b416",
-    "fp64": 1.3082e9,
-    "fp32_store": 0.7e9,
+    "source_sha256": "d4d734a62d5e699d0802bbd8d46254a9141cf69391b5d1ac1d6a6fc399fcdb12",
+    "fp64": 1.311e9,
+    "fp32_store": 0.6994e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
-    "valu_fp64": 1.0221e8,
+    "valu_fp64": 1.0102e8,
 }
 # VALU issue ceiling: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles at
 # 2.4 GHz (FP64 FMA runs at this full rate on MI355X: 78.6 TFLOP/s)

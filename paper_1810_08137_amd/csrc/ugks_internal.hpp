@@ -168,6 +168,7 @@ struct PlanTotals {
   int red;                     // workgroups of the chunk-sum launch (0: not launched)
   int shak;                    // the instances use the Shakhov model (all or none)
   int upd_ch;                  // velocity chunks per update workgroup (1 or 2)
+  int upd_nodes;               // the update chunks split a quadrant's nodes, not its u lines
   int periodic;                // some instance has a periodic halo (the ghost kernel runs)
   int channel;                 // some instance is a channel (ghost columns from the update)
 };

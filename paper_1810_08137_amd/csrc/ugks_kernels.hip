@@ -1307,7 +1307,7 @@ __device__ __forceinline__ void y_face(const PairStage<T>& st, int fr, int lane,
 // FP32 storage 4% slower, its registers then spill); the Shakhov variant has no registers to
 // spare beyond 1.  The ring only works because nothing else in the loop is a vector load: the
 // next v node is a scalar load (UGKS_CONST), so waiting for it never waits for f loads.
-template <typename S, int SU, bool kShak, int kAhead = kShak ? 1 : 2>
+template <typename S, int SU, bool kShak, bool kNode, int kAhead = kShak ? 1 : 2>
 __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<S>& st,
                                               const S (*sk)[4][kWave], int lane, int sv,
                                               int jb, bool store0, int g, int G, int gv, int Gv,
@@ -1349,14 +1349,32 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
   const T qn0 = st.qg[r0][0][lane], q10 = st.qg[r0][1][lane];
   const T qn1 = st.qg[r1][0][lane], q11 = st.qg[r1][1][lane];
   const T two_idx = T(2.0 * P.inv_dx), two_idy = T(2.0 * P.inv_dy);
-  int a0, a1;
-  chunk_range(hu.count, g, G, a0, a1);
-  // this workgroup's v nodes of the half: chunk gv of Gv, vn nodes from node vf
-  int c0, c1;
-  chunk_range(hv.count, gv, Gv, c0, c1);
-  const int vn = c1 - c0, vf = hv.first + c0 * hv.step;
-  for (int a = a0; a < a1; ++a) {
+  // this workgroup's v nodes of the half: chunk gv of Gv, vh nodes from node vf
+  int vc0, vc1;
+  chunk_range(hv.count, gv, Gv, vc0, vc1);
+  const int vh = vc1 - vc0, vf = hv.first + vc0 * hv.step;
+  // Chunk g of the quadrant: whole u lines, or (kNode, chosen by the plan where the lines do
+  // not divide evenly) its share of all nodes, which may start and end inside a line, at the
+  // groups of NB nodes that the loop below takes at a time: every node is then computed at the
+  // same place of the unrolled loop, with the same rounding, however the chunks lie.
+  constexpr int NB = kAhead + 1;
+  const int vg = (vh + NB - 1) / NB;  // groups of a line
+  int a, vs = 0, left;  // the first line, its first group, groups to compute
+  if constexpr (kNode) {
+    int n0, n1;
+    chunk_range(hu.count * vg, g, G, n0, n1);
+    a = n0 / vg;
+    vs = n0 - a * vg;
+    left = n1 - n0;
+  } else {
+    int a1;
+    chunk_range(hu.count, g, G, a, a1);
+    left = (a1 - a) * vg;
+  }
+  for (; left > 0; ++a) {
     const int k = hu.first + a * hu.step;
+    const int c0 = vs * NB, vn = min(vh - c0, left * NB);  // vn nodes of this line, from node c0
+    const int v0 = vf + c0 * hv.step;
     const T u = T(((const UGKS_CONST double*)P.uk)[k]);  // a scalar load
     const T au = fabs(u);
     const T ucx = u * two_idx;
@@ -1365,9 +1383,9 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
     };
     // planes (read and written) and v nodes are walked with running pointers
     const long long pstep = (long long)hv.step * P.PS;
-    const UGKS_GLOBAL S* pnext = plane_of(fin, P, k * P.M) + (long long)vf * P.PS;
-    UGKS_GLOBAL S* wcur = plane_of(fout, P, k * P.M) + (long long)vf * P.PS;
-    const UGKS_CONST double* vp = (const UGKS_CONST double*)(P.vm + vf);
+    const UGKS_GLOBAL S* pnext = plane_of(fin, P, k * P.M + v0);
+    UGKS_GLOBAL S* wcur = plane_of(fout, P, k * P.M + v0);
+    const UGKS_CONST double* vp = (const UGKS_CONST double*)(P.vm + v0);
     // loads run kAhead nodes ahead of the node computed; past the last node of the chunk they
     // read its plane again
     int nl = 0;
@@ -1379,7 +1397,6 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
       return v;
     };
     // the first nodes' stencil values, requested before the node's tables are formed
-    constexpr int NB = kAhead + 1;
     Vals ring[NB];
 #pragma unroll
     for (int d = 0; d < kAhead; ++d) ring[d] = load_next();
@@ -1457,7 +1474,27 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
     T em = st.ys[hf][fmid_r][0][lane], rm = st.ys[hf][fmid_r][1][lane];
     T eo = st.ys[hf][fout_r][0][lane], ro = st.ys[hf][fout_r][1][lane];
     T vv = T(*vp);
-    auto node = [&](const Vals& x) {
+    auto advance = [&]() {
+      gauss_next(ex0, rx0, qx0);
+      gauss_next(ex1, rx1, qx1);
+      gauss_next(ei, ri, qyi);
+      gauss_next(em, rm, qym);
+      gauss_next(eo, ro, qyo);
+      gauss_next(en0, rn0, qn0);
+      gauss_next(e10, r10, q10);
+      gauss_next(en1, rn1, qn1);
+      gauss_next(e11, r11, q11);
+    };
+    // a chunk that starts inside the line runs its recurrences from the stage's starts, so
+    // that the values do not depend on where the chunks end
+    if constexpr (kNode)
+      for (int n = 0; n < c0; ++n) advance();
+    // g^n + g^{n+1} of both cells with one product fused, formed where the recurrences advance
+    // to a place of the unrolled loop other than its first
+    T gf0{}, gf1{};
+    // place: of the node in the unrolled loop, or -1 in its remainder
+    auto node = [&](const Vals& x, auto place_c) {
+      constexpr int place = decltype(place_c)::value;
       const T vnext = T(vp[hv.step]);  // the next node (read one ahead; past the end a pad)
       const T av = fabs(vv);
       const T avcy = av * two_idy;
@@ -1495,8 +1532,8 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
         g0 = fma(e10, T(1) + horner(s10, vv), en0 * (T(1) + horner(sn0, vv)));
         g1 = fma(e11, T(1) + horner(s11, vv), en1 * (T(1) + horner(sn1, vv)));
       } else {
-        g0 = e10 + en0;
-        g1 = e11 + en1;
+        g0 = place > 0 ? gf0 : e10 + en0;
+        g1 = place > 0 ? gf1 : e11 + en1;
       }
       const T f0 = fma(Af0, x.C, fma(AdF0, (Fxi0 - Fxo0) + (Fyi - Fym), g0));
       const T f1 = fma(Af1, x.D, fma(AdF1, (Fxi1 - Fxo1) + (Fym - Fyo), g1));
@@ -1507,32 +1544,38 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
       wcur += pstep;
       vp += hv.step;
       vv = vnext;
-      gauss_next(ex0, rx0, qx0);
-      gauss_next(ex1, rx1, qx1);
-      gauss_next(ei, ri, qyi);
-      gauss_next(em, rm, qym);
-      gauss_next(eo, ro, qyo);
-      gauss_next(en0, rn0, qn0);
-      gauss_next(e10, r10, q10);
-      gauss_next(en1, rn1, qn1);
-      gauss_next(e11, r11, q11);
+      const T pe0 = e10, pr0 = r10, pe1 = e11, pr1 = r11;
+      const T pn0 = en0, qr0 = rn0, pn1 = en1, qr1 = rn1;
+      advance();
+      if constexpr (!kShak && place == 0) {
+        gf0 = fma(pe0, pr0, en0);
+        gf1 = fma(pe1, pr1, en1);
+      } else if constexpr (!kShak && place > 0 && place + 1 < NB) {
+        gf0 = fma(pn0, qr0, e10);
+        gf1 = fma(pn1, qr1, e11);
+      }
     };
     // NB value sets in a ring: slot s holds node c + s, loaded kAhead nodes earlier
     int c = 0;
     for (; c + NB <= vn; c += NB) {
-#pragma unroll
-      for (int s = 0; s < NB; ++s) {
-        ring[(s + kAhead) % NB] = load_next();
-        node(ring[s]);
+      ring[kAhead] = load_next();
+      node(ring[0], std::integral_constant<int, 0>());
+      ring[0] = load_next();
+      node(ring[1], std::integral_constant<int, 1>());
+      if constexpr (NB == 3) {
+        ring[1] = load_next();
+        node(ring[2], std::integral_constant<int, 2>());
       }
     }
 #pragma unroll
     for (int s = 0; s < NB; ++s) {
       if (c + s < vn) {
         ring[(s + kAhead) % NB] = load_next();
-        node(ring[s]);
+        node(ring[s], std::integral_constant<int, -1>());
       }
     }
+    left -= vg - vs;
+    vs = 0;
   }
 }
 
@@ -1601,8 +1644,8 @@ __device__ __forceinline__ void ghost_fill_quadrant(const KParams& P, const Pair
   }
 }
 
-// The body of the update kernel; kShak: the Shakhov collision model.
-template <typename S, bool kShak, int kCh, bool kFill = false>
+// The body of the update kernel; kShak: the Shakhov collision model; kNode: chunks by node.
+template <typename S, bool kShak, int kCh, bool kFill = false, bool kNode = false>
 __device__ __forceinline__ void update_body(const PlanView& pv) {
   typedef S T;  // arithmetic type of the per-velocity work (and of the LDS stage)
   __shared__ PairStage<T> st;
@@ -1955,10 +1998,10 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
     return;
   }
   if (quad_su(q) > 0)
-    pair_quadrant<S, 1, kShak>(P, st, sk, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
+    pair_quadrant<S, 1, kShak, kNode>(P, st, sk, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
                                valid || ghost_w, ghost_lane, fin, fout, i);
   else
-    pair_quadrant<S, -1, kShak>(P, st, sk, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
+    pair_quadrant<S, -1, kShak, kNode>(P, st, sk, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
                                 valid || ghost_w, ghost_lane, fin, fout, i);
 }
 
@@ -1976,6 +2019,16 @@ __global__ __launch_bounds__(kWave* kQuads* kCh)
 __attribute__((amdgpu_waves_per_eu(kUpdateWaves<S, false>)))
 void update_kernel(PlanView pv) {
   update_body<S, false, kCh>(pv);
+}
+
+// The chunks of this form split a quadrant's nodes instead of its u lines (update_by_node).  A
+// kernel of its own: the few registers it takes more would spill in the FP32-storage form
+// (400 x 100 x 40^2, which takes whole lines: 181 us without, 188 us with it).
+template <typename S, int kCh>
+__global__ __launch_bounds__(kWave* kQuads* kCh)
+__attribute__((amdgpu_waves_per_eu(kUpdateWaves<S, false>)))
+void update_kernel_nodes(PlanView pv) {
+  update_body<S, false, kCh, false, true>(pv);
 }
 
 template <typename S, int kCh>
@@ -2046,6 +2099,22 @@ int update_chunks_single(long long base, long long slots, int cap, int per_wg, i
   return best;
 }
 
+// Whether the update kernel's G chunks of a quadrant split its nodes evenly (by node) rather than
+// its u lines: K u nodes and vh v nodes of the longer halves.  The longest chunk sets the time.
+// In nodes of the v loop, a line's setup (its cubics and u Gaussians) counts as four and running
+// the recurrences to a node inside a line as a sixth of a node each.  Whole lines win where they
+// divide evenly (400 x 100 x 40^2: 20 lines over 4 chunks); 80 x 40 x 49^2 (25 lines over 12
+// chunks, the longest 3) went from 62.6 to 54.8 us by node, 200 x 50 x 101^2 (51 over 10) from
+// 575 to 545, 120 x 60 x 29^2 in FP32 storage (15 over 14) from 39 to 35.
+bool update_by_node(int K, int vh, int G) {
+  constexpr int NB = 3;  // nodes of a group
+  const int lines = K - K / 2, vg = (vh + NB - 1) / NB;
+  const int whole = (lines + G - 1) / G;
+  const int len = (lines * vg + G - 1) / G;  // groups
+  const int touched = len > 1 ? (len - 2) / vg + 2 : 1;
+  return 6 * NB * len + 24 * touched + vh < whole * (6 * vh + 24);
+}
+
 int update_vsplit(int nx, int ny, int K, int M, int NC, int fp32, int shak, int cap) {
   const long long base = (long long)((nx + kTileU - 1) / kTileU) * ((ny + 1) / 2) * NC;
   const int umax = std::max(1, std::min(K / 2, 16));
@@ -2113,6 +2182,12 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
     img[q].gsplit = insts[q].P.gmax;
     const int cap = cap_of(insts[q].P, per_wg);
     img[q].usplit = U < cap ? U : cap;
+  }
+  // a batch's chunks are few and long: whole lines
+  if (n == 1 && !shak) {
+    const KParams& P = insts[0].P;
+    const int vh = ((P.M - P.M / 2) + P.vsplit - 1) / P.vsplit;
+    t.upd_nodes = update_by_node(P.K, vh, per_wg * img[0].usplit) ? 1 : 0;
   }
   for (int q = 0; q < n; ++q) {
     const KParams& P = insts[q].P;
@@ -2229,6 +2304,13 @@ hipError_t launch_phase(const PlanView& pv, const PlanTotals& t, int fp32, int p
           update_kernel_shakhov<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(pv);
         else
           update_kernel_shakhov<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+      } else if (t.upd_nodes) {
+        if (fp32)
+          update_kernel_nodes<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+        else if (t.upd_ch == 2)
+          update_kernel_nodes<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+        else
+          update_kernel_nodes<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
       } else {
         if (fp32)
           update_kernel<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
