@@ -26,9 +26,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "d4d734a62d5e699d0802bbd8d46254a9141cf69391b5d1ac1d6a6fc399fcdb12",
-    "fp64": 1.311e9,
-    "fp32_store": 0.6994e9,
+    "source_sha256": "d41040447602b537c43ef7e71b3bf88c56090f9c8031c06fbeadde974da7ed4d",
+    "fp64": 1.3056e9,
+    "fp32_store": 0.7e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
     "valu_fp64": 1.0102e8,
 }

@@ -190,6 +190,7 @@ struct Shape {
   int Lx, Ly;
   size_t PS;  // values per velocity plane
   size_t nc;
+  size_t ncs;  // cells of the moment sums: those of the mesh and the two ghost columns
 };
 
 bool shape_ok(const ugks_mesh* mesh, const ugks_vgrid* vg, Shape& s, std::string& why) {
@@ -237,6 +238,7 @@ bool shape_ok(const ugks_mesh* mesh, const ugks_vgrid* vg, Shape& s, std::string
   s.Ly = s.ny + 2 * kHalo;
   s.PS = round_up((size_t)s.Lx * (size_t)s.Ly, (size_t)kWave);
   s.nc = (size_t)s.nx * s.ny;
+  s.ncs = s.nc + 2 * (size_t)s.ny;
   return true;
 }
 
@@ -267,14 +269,13 @@ bool collision_of(const ugks_opts* o, const Shape& s, bool& shak, std::string& w
 
 Layout layout_of(const Shape& s, int prec, int chunks, bool shak) {
   const size_t ss = prec == UGKS_FP32_STORE ? 4 : 8;
-  const size_t sizes[15] = {
+  const size_t sizes[14] = {
       (size_t)s.NC * s.NV * s.PS * ss,          // f0: NC NV planes
       (size_t)s.NC * s.NV * s.PS * ss,          // f1
       s.nc * 4 * 8,                             // W0
       s.nc * 4 * 8,                             // W1
       2 * (size_t)s.ny * 4 * 8,                 // Wg
-      (size_t)s.NC * chunks * s.nc * (shak ? kSlotsShakhov : kSlots) * 8,  // hs: partial sums
-      (size_t)s.NC * chunks * 2 * s.ny * kGhostSums * 8,  // hsg: parts of the ghost sums
+      (size_t)s.NC * chunks * s.ncs * (shak ? kSlotsShakhov : kSlots) * 8,  // hs: partial sums
       (size_t)s.NC * s.ny * (s.nx + 1) * kRec * 8,  // recx
       (size_t)s.NC * (s.ny + 1) * s.nx * kRec * 8,  // recy
       (size_t)(s.K + 6 * s.M) * 8,              // wk, wm, vmom
@@ -286,7 +287,7 @@ Layout layout_of(const Shape& s, int prec, int chunks, bool shak) {
   };
   Layout L{};
   size_t off = 0;
-  for (int b = 0; b < 15; ++b) {
+  for (int b = 0; b < 14; ++b) {
     L.off[b] = off;
     off += round_up(sizes[b], kAlign);
   }
@@ -303,30 +304,28 @@ void carve(ugks_handle* h, const Layout& L, const Shape& s) {
   B.W[1] = reinterpret_cast<double*>(base + L.off[3]);
   B.Wg = reinterpret_cast<double*>(base + L.off[4]);
   B.hs = reinterpret_cast<double*>(base + L.off[5]);
-  B.hsg = reinterpret_cast<double*>(base + L.off[6]);
-  B.recx = reinterpret_cast<double*>(base + L.off[7]);
-  B.recy = reinterpret_cast<double*>(base + L.off[8]);
-  B.wk = reinterpret_cast<double*>(base + L.off[9]);
-  B.uk = reinterpret_cast<double*>(base + L.off[10]);
-  B.vm = reinterpret_cast<double*>(base + L.off[11]);
-  B.xi_in = reinterpret_cast<double*>(base + L.off[12]);
-  B.flag = reinterpret_cast<int*>(base + L.off[12] + round_up((size_t)s.ny * 8, 64));
+  B.recx = reinterpret_cast<double*>(base + L.off[6]);
+  B.recy = reinterpret_cast<double*>(base + L.off[7]);
+  B.wk = reinterpret_cast<double*>(base + L.off[8]);
+  B.uk = reinterpret_cast<double*>(base + L.off[9]);
+  B.vm = reinterpret_cast<double*>(base + L.off[10]);
+  B.xi_in = reinterpret_cast<double*>(base + L.off[11]);
+  B.flag = reinterpret_cast<int*>(base + L.off[11] + round_up((size_t)s.ny * 8, 64));
   B.rmax = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(B.flag) + 64);
   B.tsum = reinterpret_cast<double*>(reinterpret_cast<char*>(B.flag) + 80);
-  h->plan_dev = base + L.off[13];
-  h->plan_static = base + L.off[14];
+  h->plan_dev = base + L.off[12];
+  h->plan_static = base + L.off[13];
 }
 
-// The transient buffers of one step (hs, hsg, recx, recy: layout entries 5..8) are
+// The transient buffers of one step (hs, recx, recy: layout entries 5..7) are
 // contiguous in the workspace; their size, and the same buffers carved out of `base`.  The
 // ghost states Wg (entry 4) are not transient: the update kernel of a step writes those of
 // the next.
-size_t transient_bytes(const Layout& L) { return L.off[9] - L.off[5]; }
+size_t transient_bytes(const Layout& L) { return L.off[8] - L.off[5]; }
 void carve_transient(const Layout& L, char* base, Inst& I) {
   I.hs = gp(reinterpret_cast<double*>(base + (L.off[5] - L.off[5])));
-  I.hsg = gp(reinterpret_cast<double*>(base + (L.off[6] - L.off[5])));
-  I.recx = gp(reinterpret_cast<double*>(base + (L.off[7] - L.off[5])));
-  I.recy = gp(reinterpret_cast<double*>(base + (L.off[8] - L.off[5])));
+  I.recx = gp(reinterpret_cast<double*>(base + (L.off[6] - L.off[5])));
+  I.recy = gp(reinterpret_cast<double*>(base + (L.off[7] - L.off[5])));
 }
 
 hipEvent_t pool_get(ugks_handle* h) {
@@ -435,6 +434,7 @@ void fill_constants(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, c
   P.a4_c = 4.0 / (double)(2 + s.dof);
   P.shak = shak ? 1 : 0;
   P.nslot = shak ? kSlotsShakhov : kSlots;
+  P.ncs = (long long)s.ncs;
   P.pr_c = shak ? 1.0 - opts->prandtl : 0.0;
   P.Lx = s.Lx;
   P.Ly = s.Ly;
@@ -547,7 +547,6 @@ void make_inst(const KParams& P, const Buffers& B, int prec, Inst& I) {
   I.gsplit = 1;
   I.Wg = gp(B.Wg);
   I.hs = gp(B.hs);
-  I.hsg = gp(B.hsg);
   I.recx = gp(B.recx);
   I.recy = gp(B.recy);
   I.cur = 0;

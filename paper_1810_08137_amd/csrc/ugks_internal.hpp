@@ -31,7 +31,6 @@ constexpr int kSlots = 64;     // per-cell outgoing moment sums: 4 faces x 16
 constexpr int kSlotHeat = 64;
 constexpr int kSlotCell = 68;
 constexpr int kSlotsShakhov = 76;
-constexpr int kGhostSums = 17;  // sums of a channel ghost cell towards the domain: 16 + the heat sum
 constexpr int kRec = 32;       // doubles per interface record
 constexpr int kHalo = 2;       // halo columns / rows on each side of a velocity plane
 constexpr int kMaxNodes = 1024;  // nodes per velocity axis
@@ -74,6 +73,7 @@ struct KParams {
   double a4_c;      // 4/(2 + dof): its energy coefficient, a4 = a4_c lambda^2/rho (...)
   int shak;         // Shakhov collision model (else BGK)
   int nslot;        // per-cell sums per velocity chunk: kSlots, or kSlotsShakhov
+  long long ncs;    // cells of one such sum: those of the mesh and the two ghost columns
   double pr_c;      // 1 - Prandtl number (Shakhov)
   int Lx, Ly;       // padded row length and row count of a plane
   int bc, collisionless, inlet_fixed_u;
@@ -111,9 +111,9 @@ struct Buffers {
   void* f[2];       // [NC NV][PS] storage type
   double* W[2];     // [nx*ny][4], ping-pong with f
   double* Wg;       // [2][ny][4]
-  double* hs;       // [NC gmax][nslot][nx*ny]: partial g of sum q of face side s of cell c at
-                    // ((g nslot) + 16 s + q) nx ny + c; chunks of H after those of G
-  double* hsg;      // [NC G][2][ny][kGhostSums]: the chunks' parts, added into the first
+  double* hs;       // [NC gmax][nslot][ncs]: partial g of sum q of face side s of cell c at
+                    // ((g nslot) + 16 s + q) ncs + c; chunks of H after those of G.  The inlet
+                    // ghost of row j is cell nx ny + j, the outlet ghost nx ny + ny + j
   double* recx;     // [NC][32][ny (nx+1)]: records of G, then of H, field-major
   double* recy;     // [NC][32][(ny+1) nx]
   double* wk;       // [K], followed by wm [M], then vmom [M][5]
@@ -126,7 +126,7 @@ struct Buffers {
 };
 
 struct Layout {
-  size_t off[15];
+  size_t off[14];
   size_t total;
 };
 
@@ -138,7 +138,6 @@ struct Inst {
   UGKS_GLOBAL double* W[2];
   UGKS_GLOBAL double* Wg;
   UGKS_GLOBAL double* hs;
-  UGKS_GLOBAL double* hsg;
   UGKS_GLOBAL double* recx;
   UGKS_GLOBAL double* recy;
   int cur;   // f[(cur + step) & 1] and W[(cur + step) & 1] are read, the others written
@@ -156,16 +155,17 @@ struct PlanView {
   const Inst* inst;
   const int* off_sums;   // one workgroup per (row segment, velocity chunk) of the moment kernel
   const int* off_upd;    // one workgroup per (row segment, velocity chunk) of the update kernel
-  const int* off_face;   // 256 faces per workgroup
+  const int* off_face;   // 256 faces per workgroup (instances with one part of every sum)
   const int* off_ghost;  // periodic: the halo frame of every plane (a channel has none)
-  const int* off_red;    // chunk-sum workgroups (instances with more than one chunk)
+  const int* off_red;    // red_faces per workgroup (instances with several parts of every sum)
   int ninst;
   int step;              // steps enqueued since the plan's `cur` values were taken
 };
 
 struct PlanTotals {
   int sums, upd, face, ghost;  // workgroups of each launch
-  int red;                     // workgroups of the chunk-sum launch (0: not launched)
+  int red;                     // workgroups of the chunked interface launch (0: not launched)
+  int red_faces, red_waves;    // its faces (16, 32 or 64) and wavefronts (8 or 4) per workgroup
   int shak;                    // the instances use the Shakhov model (all or none)
   int upd_ch;                  // velocity chunks per update workgroup (1 or 2)
   int upd_nodes;               // the update chunks split a quadrant's nodes, not its u lines

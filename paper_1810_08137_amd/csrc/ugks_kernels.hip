@@ -4,10 +4,9 @@
 //   ghost   periodic box only: the periodic images into the halo of every velocity plane
 //   sums    per cell and velocity: limited slopes of f, the upwind reconstruction at the
 //           cell's outgoing faces and their velocity moments (S1 and the sums of S7); in a
-//           channel also the sums of the inlet and outlet ghost columns (Sec. 3.A); a solver
-//           that splits its velocities into chunks adds the chunks' partial sums in a second,
-//           small launch
-//   faces   per interface: add the two sides' sums, then the scalar part of the flux
+//           channel also the sums of the inlet and outlet ghost columns (Sec. 3.A)
+//   faces   per interface: add the two sides' sums (and their parts, where a solver splits its
+//           velocities into chunks), then the scalar part of the flux
 //           (S2-S5: Maxwellian moments, time weights, micro slopes, equilibrium flux) into a
 //           record of folded coefficients
 //   update  per cell and velocity: the distribution flux at the faces (S6, S8), then Eq. (4)
@@ -533,7 +532,7 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(PlanView pv) {
   const int g = hpart ? gg - G : gg;
   const UGKS_GLOBAL S* f = static_cast<const UGKS_GLOBAL S*>(I->f[(I->cur + pv.step) & 1]) +
                            (hpart ? (long long)P.NV * P.PS : 0ll);
-  UGKS_GLOBAL double* hs = I->hs + (size_t)gg * P.nslot * ((size_t)P.nx * P.ny);
+  UGKS_GLOBAL double* hs = I->hs + (size_t)gg * P.nslot * (size_t)P.ncs;
   const int i = t * kTileS - 1 + lane;
   const bool valid = lane >= 1 && lane <= kTileS && i < P.nx;
   // channel ghost columns (i = -1, nx): their sums towards the domain are the ghost sums of
@@ -770,15 +769,16 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(PlanView pv) {
     }
   }
   __syncthreads();
-  const size_t nc = (size_t)P.nx * P.ny;
+  const size_t nc = (size_t)P.ncs;
   // the inlet ghost's sums towards +x (waves 0 and 3), the outlet ghost's towards -x (waves
-  // 1 and 2): this chunk's part, added over the chunks by the interface kernel
+  // 1 and 2)
   if (ghost_wave && ghost && q == (i < 0 ? 0 : 2)) {
-    const int ox = q == 0 ? 3 : 2, side = i < 0 ? 0 : 1;
-    UGKS_GLOBAL double* gs = I->hsg + (((size_t)gg * 2 + side) * P.ny + j) * kGhostSums;
+    const int ox = q == 0 ? 3 : 2, fx = q == 0 ? S_XP : S_XM;
+    const size_t cell = (size_t)P.nx * P.ny + (size_t)(i < 0 ? 0 : P.ny) + j;
 #pragma unroll
-    for (int r = 0; r < kR; ++r) gs[r] = ax[r] + red[ox][r][lane];
-    if constexpr (kR < kGhostSums) gs[kGhostSums - 1] = 0.0;  // no heat sum without Shakhov
+    for (int r = 0; r < 16; ++r)
+      hs[(size_t)(16 * fx + r) * nc + cell] = ax[r] + red[ox][r][lane];
+    if constexpr (kShak) hs[(size_t)(kSlotHeat + fx) * nc + cell] = ax[16] + red[ox][16][lane];
   }
   if (valid && (q == 0 || q == 2)) {
     const size_t cell = (size_t)j * P.nx + i;
@@ -802,43 +802,6 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(PlanView pv) {
       }
     }
   }
-}
-
-// With several velocity chunks per quadrant, or the chunks of H, the moment kernel leaves
-// NC G partial sums per value; one thread per (sum, cell) adds them, in chunk order, into the
-// first.
-__global__ __launch_bounds__(256) void chunk_sum_kernel(PlanView pv) {
-  const int b = blockIdx.x;
-  const int ii = find_inst(pv.off_red, pv.ninst, b);
-  const Inst* __restrict__ I = inst_at(pv, ii);
-  const KParams P = I->P;
-  const size_t nc = (size_t)P.nx * P.ny;
-  size_t e = (size_t)(b - first_block(pv.off_red, ii)) * blockDim.x + threadIdx.x;
-  UGKS_GLOBAL double* at;
-  size_t gstride;
-  if (e < (size_t)P.nslot * nc) {
-    at = I->hs + e;
-    gstride = (size_t)P.nslot * nc;
-  } else {
-    // a channel's ghost sums (2 ny rows of kGhostSums per chunk)
-    e -= (size_t)P.nslot * nc;
-    gstride = 2 * (size_t)P.ny * kGhostSums;
-    if (P.bc != UGKS_BC_CHANNEL || e >= gstride) return;
-    at = I->hsg + e;
-  }
-  // the chunks are added in chunk order; their loads go out eight at a time (a load per
-  // loop trip would wait out one memory latency per chunk)
-  const int n = I->gsplit * P.NC;
-  double x = at[0];
-  for (int g0 = 1; g0 < n; g0 += 8) {
-    double v[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = g0 + k < n ? at[(size_t)(g0 + k) * gstride] : 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (g0 + k < n) x += v[k];
-  }
-  at[0] = x;
 }
 
 // S2-S5 at one interior interface, local frame.  S = [W0, Wt, Q1, Q2].  Writes the local
@@ -1005,80 +968,82 @@ __device__ void interface_scalars(const KParams& P, double dt, const double* S, 
   V0 = p0.V;
 }
 
-// One thread per interface: x-faces first (ny rows of nx+1), then y-faces (ny+1 rows of nx).
-// With internal degrees of freedom each face also gets the record of H, nfx (nfy) records
-// after those of G; it repeats the macroscopic flux, so either record serves Eq. (4).
-__global__ __launch_bounds__(256) void faces_kernel(PlanView pv) {
-  const int b = blockIdx.x;
-  const int ii = find_inst(pv.off_face, pv.ninst, b);
-  const Inst* __restrict__ I = inst_at(pv, ii);
-  const KParams P = I->P;
-  const UGKS_GLOBAL double* hs = I->hs;
-  const UGKS_GLOBAL double* hsg = I->hsg;
-  const UGKS_GLOBAL double* W = I->W[(I->cur + pv.step) & 1];
-  const double dt = step_dt(P, (I->cur + pv.step) & 1);
-  const UGKS_GLOBAL double* Wg = I->Wg;
-  UGKS_GLOBAL double* recx = I->recx;
-  UGKS_GLOBAL double* recy = I->recy;
-  const long e = (long)(b - first_block(pv.off_face, ii)) * blockDim.x + threadIdx.x;
-  // the update kernel of this step takes the max rate of W^{n+1} into the other slot
-  if (e == 0) P.rmax[((I->cur + pv.step) & 1) ^ 1] = 0ull;
-  const long nfx = (long)P.ny * (P.nx + 1);
-  const long nfy = (long)(P.ny + 1) * P.nx;
+// One interface of a solver: face (i, j) of the x family (the left face of cell (i, j), i up to
+// nx) or of the y family (its lower face, j up to ny), number e of its family.
+template <bool kX>
+struct Face {
+  static constexpr bool x = kX;
+  int i, j;
+  size_t e, nf;        // number in the family, faces of the family
+  bool gl, gr;         // the side below / above is a channel's inlet / outlet ghost column
+  bool wall;           // a channel wall
+  unsigned cl, cr;     // the cells below and above (periodic images; a ghost's cell of the
+                       // moment sums; beyond a wall some cell, unused)
+};
+template <bool x>
+__device__ __forceinline__ Face<x> face_at(const KParams& P, long e) {
+  Face<x> f;
   const bool chan = P.bc == UGKS_BC_CHANNEL;
-  const size_t nc = (size_t)P.nx * P.ny;
-  double S[16], F[4];
-  double U0, V0, T3 = 0.0;
-  if (e < nfx) {
-    const int j = (int)(e / (P.nx + 1)), i = (int)(e % (P.nx + 1));
-    // a channel's ghost side: the ghost sums the moment kernel left (the chunk-sum kernel has
-    // added the parts of the velocity chunks into the first)
-    const bool gL = chan && i == 0, gR = chan && i == P.nx;
-    const size_t cl = (size_t)j * P.nx + wrap(i - 1, P.nx);
-    const size_t cr = (size_t)j * P.nx + wrap(i, P.nx);
-    const UGKS_GLOBAL double* sL = gL ? hsg + (size_t)j * kGhostSums : hs + 16 * S_XP * nc + cl;
-    const UGKS_GLOBAL double* sR =
-        gR ? hsg + ((size_t)P.ny + j) * kGhostSums : hs + 16 * S_XM * nc + cr;
-    const size_t stL = gL ? 1 : nc, stR = gR ? 1 : nc;
-    const UGKS_GLOBAL double* WL = gL ? Wg + 4 * (size_t)j : W + 4 * cl;
-    const UGKS_GLOBAL double* WR = gR ? Wg + 4 * ((size_t)P.ny + j) : W + 4 * cr;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) S[q] = sL[q * stL] + sR[q * stR];
-    if (P.shak)  // the heat sums of the two sides
-      T3 = (gL ? sL[16] : hs[(kSlotHeat + S_XP) * nc + cl]) +
-           (gR ? sR[16] : hs[(kSlotHeat + S_XM) * nc + cr]);
-    double wl[4], wr[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      wl[q] = WL[q];
-      wr[q] = WR[q];
-    }
-    const RecRef rec{recx + e, (size_t)nfx};
-    const RecRef recH{recx + (size_t)nfx * kRec + e, (size_t)nfx};
-    if (P.NC > 1)
-      interface_scalars<true>(P, dt, S, wl, wr, P.dx, P.dy, F, rec, recH, U0, V0);
-    else
-      interface_scalars<false>(P, dt, S, wl, wr, P.dx, P.dy, F, rec, recH, U0, V0, T3);
-    for (int c = 0; c < P.NC; ++c) {
-      const RecRef r = c ? recH : rec;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r[R_FX + q] = F[q];
-      r[R_UX] = U0;
-      r[R_VY] = V0;
-    }
-    return;
+  const int row = x ? P.nx + 1 : P.nx;
+  f.e = (size_t)e;
+  f.nf = x ? (size_t)P.ny * (P.nx + 1) : (size_t)(P.ny + 1) * P.nx;
+  f.j = (int)(e / row);
+  f.i = (int)(e - (long)f.j * row);
+  f.gl = x && chan && f.i == 0;
+  f.gr = x && chan && f.i == P.nx;
+  f.wall = !x && chan && (f.j == 0 || f.j == P.ny);
+  const unsigned ghost = (unsigned)P.nx * P.ny + f.j;
+  if (x) {
+    f.cl = f.gl ? ghost : (unsigned)(f.j * P.nx + wrap(f.i - 1, P.nx));
+    f.cr = f.gr ? ghost + P.ny : (unsigned)(f.j * P.nx + wrap(f.i, P.nx));
+  } else {
+    f.cl = (unsigned)(wrap(f.j - 1, P.ny) * P.nx + f.i);
+    f.cr = (unsigned)(wrap(f.j, P.ny) * P.nx + f.i);
   }
-  if (e >= nfx + nfy) return;
-  const long e2 = e - nfx;
-  const int j = (int)(e2 / P.nx), i = (int)(e2 % P.nx);
-  const RecRef rec{recy + e2, (size_t)nfy};
-  const RecRef recH{recy + (size_t)nfy * kRec + e2, (size_t)nfy};
-  if (chan && (j == 0 || j == P.ny)) {
+  return f;
+}
+
+// Slot of sum q towards face side s (16: the Shakhov model's heat sum) of a part of the sums.
+__device__ __forceinline__ long long slot_of(int s, int q) {
+  return q < 16 ? 16 * s + q : kSlotHeat + s;
+}
+
+// W of the cells (or ghosts) below and above a face, in its local frame.
+template <bool kX>
+__device__ __forceinline__ void face_sides(const Inst* __restrict__ I, const KParams& P,
+                                           int parity, const Face<kX>& f, double* wl,
+                                           double* wr) {
+  const UGKS_GLOBAL double* W = I->W[parity];
+  const UGKS_GLOBAL double* Wg = I->Wg;
+  const UGKS_GLOBAL double* WL = f.gl ? Wg + 4 * (size_t)f.j : W + 4 * (size_t)f.cl;
+  const UGKS_GLOBAL double* WR = f.gr ? Wg + 4 * ((size_t)P.ny + f.j) : W + 4 * (size_t)f.cr;
+  const int n = f.x ? 1 : 2, t = 3 - n;
+  wl[0] = WL[0];
+  wl[1] = WL[n];
+  wl[2] = WL[t];
+  wl[3] = WL[3];
+  wr[0] = WR[0];
+  wr[1] = WR[n];
+  wr[2] = WR[t];
+  wr[3] = WR[3];
+}
+
+// The record(s) of one face from its sums S (both sides added; a wall: those of its cell) and
+// heat sum T3.  With internal degrees of freedom each face also gets the record of H, nf
+// records after that of G; it repeats the macroscopic flux, so either record serves Eq. (4).
+template <bool kX>
+__device__ __forceinline__ void face_record(const Inst* __restrict__ I, const KParams& P,
+                                            double dt, const Face<kX>& f, const double* S,
+                                            double T3, const double* wl, const double* wr) {
+  UGKS_GLOBAL double* r0 = (f.x ? I->recx : I->recy) + f.e;
+  const RecRef rec{r0, f.nf};
+  const RecRef recH{r0 + f.nf * kRec, f.nf};
+  // global components of the local (normal, tangential) axes
+  const int fn = f.x ? R_FX + 1 : R_FX + 2, ft = f.x ? R_FX + 2 : R_FX + 1;
+  if (f.wall) {
     // diffuse wall: sums of the wall-row cell towards the wall; local frame (v, u)
-    const bool top = j == P.ny;
-    const size_t c = (size_t)(top ? P.ny - 1 : 0) * P.nx + i;
-    const UGKS_GLOBAL double* Q1s = hs + (16 * (top ? S_YP : S_YM) + 8) * nc + c;
-    const double Q1[4] = {Q1s[0], Q1s[nc], Q1s[2 * nc], Q1s[3 * nc]};
+    const bool top = f.j == P.ny;
+    const double* Q1 = S + 8;
     const double den = top ? P.wall_den_top : P.wall_den_bot;
     const double* Gw = top ? P.wall_G_top : P.wall_G_bot;
     const double rho_w = -Q1[0] / den;
@@ -1106,28 +1071,194 @@ __global__ __launch_bounds__(256) void faces_kernel(PlanView pv) {
     if (!(rho_w > 0.0) || !isfinite(rho_w)) *P.flag = 1;
     return;
   }
-  const size_t cl = (size_t)wrap(j - 1, P.ny) * P.nx + i;
-  const size_t cr = (size_t)wrap(j, P.ny) * P.nx + i;
-  const UGKS_GLOBAL double* sL = hs + 16 * S_YP * nc + cl;
-  const UGKS_GLOBAL double* sR = hs + 16 * S_YM * nc + cr;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) S[q] = sL[q * nc] + sR[q * nc];
-  if (P.shak) T3 = hs[(kSlotHeat + S_YP) * nc + cl] + hs[(kSlotHeat + S_YM) * nc + cr];
-  const double wl[4] = {W[4 * cl], W[4 * cl + 2], W[4 * cl + 1], W[4 * cl + 3]};
-  const double wr[4] = {W[4 * cr], W[4 * cr + 2], W[4 * cr + 1], W[4 * cr + 3]};
+  double F[4], U0, V0;
+  const double dn = f.x ? P.dx : P.dy, len = f.x ? P.dy : P.dx;
   if (P.NC > 1)
-    interface_scalars<true>(P, dt, S, wl, wr, P.dy, P.dx, F, rec, recH, U0, V0);
+    interface_scalars<true>(P, dt, S, wl, wr, dn, len, F, rec, recH, U0, V0);
   else
-    interface_scalars<false>(P, dt, S, wl, wr, P.dy, P.dx, F, rec, recH, U0, V0, T3);
+    interface_scalars<false>(P, dt, S, wl, wr, dn, len, F, rec, recH, U0, V0, T3);
   for (int c = 0; c < P.NC; ++c) {
     const RecRef r = c ? recH : rec;
     r[R_FX + 0] = F[0];
-    r[R_FX + 1] = F[2];
-    r[R_FX + 2] = F[1];
+    r[fn] = F[1];
+    r[ft] = F[2];
     r[R_FX + 3] = F[3];
-    r[R_UX] = V0;  // local (normal, tangential) = global (y, x)
-    r[R_VY] = U0;
+    r[f.x ? R_UX : R_VY] = U0;
+    r[f.x ? R_VY : R_UX] = V0;
   }
+}
+
+// The update kernel of this step takes the max rate of W^{n+1} into the other slot.
+__device__ __forceinline__ void clear_rate(const KParams& P, int parity) {
+  P.rmax[parity ^ 1] = 0ull;
+}
+
+// Instances with one part of every sum: one thread per interface, the workgroups of the x faces
+// (ny rows of nx+1) first, then those of the y faces (ny+1 rows of nx).
+template <bool kX>
+__device__ __forceinline__ void face_direct(const Inst* __restrict__ I, const KParams& P,
+                                            int parity, long e) {
+  const Face<kX> f = face_at<kX>(P, e);
+  if (e >= (long)f.nf) return;
+  // a wall takes the sums of its cell alone, which lies above the bottom and below the top
+  const bool nol = f.wall && f.j == 0, nor = f.wall && f.j != 0;
+  auto sum_at = [&](int side, int q, unsigned c) {
+    return ldb((const UGKS_GLOBAL double*)I->hs + slot_of(side, q) * P.ncs, c * 8u);
+  };
+  double S[16], T3 = 0.0, wl[4], wr[4];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const double a = sum_at(kX ? S_XP : S_YP, q, f.cl), c = sum_at(kX ? S_XM : S_YM, q, f.cr);
+    S[q] = nol ? c : (nor ? a : a + c);
+  }
+  if (P.shak) T3 = sum_at(kX ? S_XP : S_YP, 16, f.cl) + sum_at(kX ? S_XM : S_YM, 16, f.cr);
+  face_sides(I, P, parity, f, wl, wr);
+  face_record(I, P, step_dt(P, parity), f, S, T3, wl, wr);
+}
+__global__ __launch_bounds__(256) void faces_kernel(PlanView pv) {
+  const int b = blockIdx.x;
+  const int ii = find_inst(pv.off_face, pv.ninst, b);
+  const Inst* __restrict__ I = inst_at(pv, ii);
+  const KParams P = I->P;
+  const int parity = (I->cur + pv.step) & 1;
+  const int local = b - first_block(pv.off_face, ii);
+  if (local == 0 && threadIdx.x == 0) clear_rate(P, parity);
+  const int bx = (P.ny * (P.nx + 1) + 255) / 256;
+  if (local < bx)
+    face_direct<true>(I, P, parity, (long)local * 256 + threadIdx.x);
+  else
+    face_direct<false>(I, P, parity, (long)(local - bx) * 256 + threadIdx.x);
+}
+
+// Instances whose moment kernel leaves several parts of every sum (velocity chunks, the chunks of
+// H): a workgroup takes kF faces of one family.  Its threads first add the parts of the faces' 32
+// sums (16 from each side) in chunk order, kIt sums a thread, all loads of a sum in flight at
+// once; they meet in LDS, and one wavefront goes on to the records.  Each sum is towards one
+// face, so no part is read twice and no launch of its own is needed for the sums (it took 4.6 us
+// of launch and latency on any mesh).  What is left is bound by latency: 1.5 us for the plan, 2 for
+// the sums, 3.5 for the chain of interface_scalars.  On a small mesh with many parts (40 x 20: 14)
+// 64 faces a workgroup would have 27 CUs read everything (4.3 us for the sums), so the plan
+// takes 16 or 32 faces there.  The Shakhov model's cell moments, which the update kernel reads,
+// are added by the workgroups after those of the faces, one thread per moment and cell.
+template <bool kX, int kF, int kNW>
+__device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, const KParams& P,
+                                                int parity, long first, int lane, int w,
+                                                double (*red)[kF]) {
+  constexpr int kSub = kWave / kF;            // sums a wavefront takes side by side
+  constexpr int kStep = kNW * kSub, kIt = 32 / kStep;
+  const int n = I->gsplit * P.NC;
+  const long nf = kX ? (long)P.ny * (P.nx + 1) : (long)(P.ny + 1) * P.nx;
+  const int fl = lane % kF, sub = lane / kF;
+  const bool mine = first + fl < nf;
+  const Face<kX> f = face_at<kX>(P, mine ? first + fl : nf - 1);
+  double wl[4], wr[4];
+  if (w == 0) face_sides(I, P, parity, f, wl, wr);
+  // Sums u0 + it kStep (u < 16: sum u of the cell below the face, else sum u - 16 of the cell
+  // above it; 32, 33: their heat sums), up to kParts parts at a time (past the last part it is
+  // read again and not added).  With kF = 64 a wavefront's sum is uniform and its slot goes into
+  // the base; else the slot is a lane's, in the 32-bit offset (the plan sees to the size).
+  const long long part = (long long)P.nslot * P.ncs;
+  auto add = [&](int u0, auto count_c, auto parts_c) {
+    constexpr int kN = decltype(count_c)::value, kParts = decltype(parts_c)::value;
+    const UGKS_GLOBAL double* base[kN];
+    unsigned off[kN];
+    double a[kN];
+#pragma unroll
+    for (int it = 0; it < kN; ++it) {
+      const int u = u0 + it * kStep;
+      const bool above = u < 32 ? u >= 16 : u == 33;
+      const long long slot = slot_of(above ? (kX ? S_XM : S_YM) : (kX ? S_XP : S_YP),
+                                     u < 32 ? u & 15 : 16);
+      const unsigned c = above ? f.cr : f.cl;
+      base[it] = I->hs + (kSub == 1 ? slot * P.ncs : 0);
+      off[it] = ((kSub == 1 ? 0u : (unsigned)(slot * P.ncs)) + c) * 8u;
+      a[it] = 0.0;
+    }
+    long long at = 0;
+    for (int g0 = 0; g0 < n; g0 += kParts) {
+      double v[kN][kParts];
+#pragma unroll
+      for (int k = 0; k < kParts; ++k) {
+#pragma unroll
+        for (int it = 0; it < kN; ++it) v[it][k] = ldb(base[it] + at, off[it]);
+        at += g0 + k + 1 < n ? part : 0;
+      }
+#pragma unroll
+      for (int k = 0; k < kParts; ++k) {
+#pragma unroll
+        for (int it = 0; it < kN; ++it) a[it] += g0 + k < n ? v[it][k] : 0.0;
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < kN; ++it) red[u0 + it * kStep][fl] = a[it];
+  };
+  using It = std::integral_constant<int, kIt>;
+  const int u0 = w * kSub + sub;
+  if (n <= 2)
+    add(u0, It(), std::integral_constant<int, 2>());
+  else if (n <= 4)
+    add(u0, It(), std::integral_constant<int, 4>());
+  else if (n <= 6 || kIt == 8)
+    add(u0, It(), std::integral_constant<int, 6>());
+  else if (n <= 9)
+    add(u0, It(), std::integral_constant<int, 9>());
+  else if (n <= 12)
+    add(u0, It(), std::integral_constant<int, 12>());
+  else
+    add(u0, It(), std::integral_constant<int, 16>());
+  if (P.shak && w >= kNW - 2 && sub == 0)
+    add(32 + w - (kNW - 2), std::integral_constant<int, 1>(), std::integral_constant<int, 8>());
+  __syncthreads();
+  if (w != 0 || sub != 0 || !mine) return;
+  // a wall takes the sums of its cell alone, which lies above the bottom and below the top
+  const bool nol = f.wall && f.j == 0, nor = f.wall && f.j != 0;
+  double S[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const double a = red[q][fl], c = red[16 + q][fl];
+    S[q] = nol ? c : (nor ? a : a + c);
+  }
+  face_record(I, P, step_dt(P, parity), f, S, P.shak ? red[32][fl] + red[33][fl] : 0.0, wl, wr);
+}
+
+template <int kF, int kNW>
+__global__ __launch_bounds__(kWave* kNW)
+__attribute__((amdgpu_waves_per_eu(2))) void faces_kernel_chunks(PlanView pv) {
+  __shared__ double red[34][kF];
+  const int b = blockIdx.x;
+  const int ii = find_inst(pv.off_red, pv.ninst, b);
+  const Inst* __restrict__ I = inst_at(pv, ii);
+  const KParams P = I->P;
+  const int parity = (I->cur + pv.step) & 1;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int local = b - first_block(pv.off_red, ii);
+  if (local == 0 && threadIdx.x == 0) clear_rate(P, parity);
+  const int bx = (P.ny * (P.nx + 1) + kF - 1) / kF;
+  const int by = ((P.ny + 1) * P.nx + kF - 1) / kF;
+  if (local < bx) {
+    faces_of_chunks<true, kF, kNW>(I, P, parity, (long)local * kF, lane, w, red);
+    return;
+  }
+  if (local < bx + by) {
+    faces_of_chunks<false, kF, kNW>(I, P, parity, (long)(local - bx) * kF, lane, w, red);
+    return;
+  }
+  const int n = I->gsplit * P.NC;
+  const size_t nc = (size_t)P.ncs;
+  const size_t e = (size_t)(local - bx - by) * (kWave * kNW) + threadIdx.x;
+  if (e >= (size_t)(kSlotsShakhov - kSlotCell) * nc) return;
+  UGKS_GLOBAL double* at = I->hs + (size_t)kSlotCell * nc + e;
+  double x = at[0];
+  for (int g0 = 1; g0 < n; g0 += 8) {
+    double v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = g0 + k < n ? at[(size_t)(g0 + k) * P.nslot * nc] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (g0 + k < n) x += v[k];
+  }
+  at[0] = x;
 }
 
 // ------------------------------------------------------------------ update kernel
@@ -1934,7 +2065,7 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
     }
     if constexpr (kShak) {
       // heat flux of f^n about U^n from the cell's raw moments (moment kernel, chunk 0)
-      const size_t nc = (size_t)P.nx * P.ny;
+      const size_t nc = (size_t)P.ncs;
       const UGKS_GLOBAL double* cm = I->hs + (size_t)kSlotCell * nc + cc;
       double m[8];
 #pragma unroll
@@ -2189,24 +2320,36 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
     const int vh = ((P.M - P.M / 2) + P.vsplit - 1) / P.vsplit;
     t.upd_nodes = update_by_node(P.K, vh, per_wg * img[0].usplit) ? 1 : 0;
   }
+  // Faces and wavefronts per workgroup of the chunked interface kernel: 16 or 32 faces while each
+  // workgroup (eight wavefronts, whose registers fill a CU) still has a CU of its own, then 64,
+  // with four wavefronts where even those would be more than one to a CU.
+  long long wide = 0;
+  for (int q = 0; q < n; ++q) {
+    const KParams& P = insts[q].P;
+    if (img[q].gsplit * P.NC > 1) wide += P.ny * (P.nx + 1LL) + (P.ny + 1LL) * P.nx;
+  }
+  t.red_faces = wide <= 250 * 16 ? 16 : (wide <= 250 * 32 ? 32 : 64);
+  t.red_waves = wide <= 250 * 64 ? 8 : 4;
   for (int q = 0; q < n; ++q) {
     const KParams& P = insts[q].P;
     const int G = img[q].gsplit * P.NC;  // chunks of G, then those of H
-    const int nf = P.ny * (P.nx + 1) + (P.ny + 1) * P.nx;
+    const int nfx = P.ny * (P.nx + 1), nfy = (P.ny + 1) * P.nx;
     off[0][q] = t.sums;
     off[1][q] = t.upd;
     off[2][q] = t.face;
     off[3][q] = t.ghost;
     off[4][q] = t.red;
     off[5][q] = 0;
-    if (G > 1)  // the per-cell sums, and a channel's ghost sums
-      t.red += (int)(((long long)P.nslot * P.nx * P.ny +
-                      (P.bc == UGKS_BC_CHANNEL ? 2LL * P.ny * kGhostSums : 0) + 255) /
-                     256);
     t.shak = t.shak || P.shak;
     t.sums += ((P.nx + kTileS - 1) / kTileS) * P.ny * G;
     t.upd += ((P.nx + kTileU - 1) / kTileU) * ((P.ny + 1) / 2) * img[q].usplit * P.vsplit * P.NC;
-    t.face += (nf + 255) / 256;
+    if (G > 1)
+      t.red += (nfx + t.red_faces - 1) / t.red_faces + (nfy + t.red_faces - 1) / t.red_faces +
+               (P.shak ? ((kSlotsShakhov - kSlotCell) * (int)P.ncs + kWave * t.red_waves - 1) /
+                             (kWave * t.red_waves)
+                       : 0);
+    else
+      t.face += (nfx + 255) / 256 + (nfy + 255) / 256;
     if (P.bc == UGKS_BC_CHANNEL) {
       t.channel = 1;
     } else {
@@ -2285,14 +2428,21 @@ hipError_t launch_phase(const PlanView& pv, const PlanTotals& t, int fp32, int p
         else
           sums_kernel<double, false><<<(unsigned)t.sums, kWave * kQuads, 0, s>>>(pv);
       }
-      if (t.red > 0) {
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        chunk_sum_kernel<<<(unsigned)t.red, 256, 0, s>>>(pv);
-      }
       break;
     case 2:
-      faces_kernel<<<(unsigned)t.face, 256, 0, s>>>(pv);
+      if (t.red > 0) {
+        if (t.red_faces == 16)
+          faces_kernel_chunks<16, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(pv);
+        else if (t.red_faces == 32)
+          faces_kernel_chunks<32, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(pv);
+        else if (t.red_waves == 8)
+          faces_kernel_chunks<64, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(pv);
+        else
+          faces_kernel_chunks<64, 4><<<(unsigned)t.red, kWave * 4, 0, s>>>(pv);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
+      if (t.face > 0) faces_kernel<<<(unsigned)t.face, 256, 0, s>>>(pv);
       break;
     default: {
       // FP32 storage runs one chunk per workgroup (build_plan never asks for two)
