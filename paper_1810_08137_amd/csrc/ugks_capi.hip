@@ -3,6 +3,7 @@
 // sequence on the caller's stream.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -12,6 +13,8 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "ugks_internal.hpp"
@@ -119,6 +122,59 @@ void* scratch_address(int device, std::string& why) {
   return g_scratch_ptr[device];
 }
 
+// Pinned host blocks through which the state goes between the planes and the caller's buffers,
+// kept while a handle or a batch lives (allocating one costs more than a small copy), at most
+// kPinnedKept of them.  A block belongs to one call from get to put, so calls on any threads
+// and streams share the pool.
+constexpr size_t kPinnedBytes = (size_t)2 << 20;
+constexpr int kPinnedKept = 8;
+class PinnedPool {
+ public:
+  void* get() {
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      if (nfree_ > 0) return free_[--nfree_];
+    }
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kPinnedBytes, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    return p;
+  }
+  void put(void* p) {
+    if (!p) return;
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      if (users_ > 0 && nfree_ < kPinnedKept) {
+        free_[nfree_++] = p;
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+  void add_user() {
+    std::lock_guard<std::mutex> lock(m_);
+    ++users_;
+  }
+  void drop_user() {
+    void* drop[kPinnedKept];
+    int n = 0;
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      if (--users_ > 0) return;
+      while (nfree_ > 0) drop[n++] = free_[--nfree_];
+    }
+    while (n > 0) (void)hipHostFree(drop[--n]);
+  }
+
+ private:
+  std::mutex m_;
+  void* free_[kPinnedKept] = {};
+  int nfree_ = 0, users_ = 0;
+};
+PinnedPool g_pinned;
+
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int fail(ugks_handle* h, int code, const char* fmt, const char* detail = "") {
@@ -129,12 +185,6 @@ int fail(ugks_handle* h, int code, const char* fmt, const char* detail = "") {
   else
     std::memcpy(g_create_error, buf, sizeof buf);
   return code;
-}
-
-// Position of cell c = j nx + i inside a velocity plane.
-size_t plane_index(const KParams& P, size_t c) {
-  const size_t j = c / (size_t)P.nx, i = c - j * (size_t)P.nx;
-  return (j + kHalo) * (size_t)P.Lx + i + kHalo;
 }
 
 int hip_fail(ugks_handle* h, hipError_t e, const char* what) {
@@ -337,6 +387,121 @@ hipEvent_t pool_get(ugks_handle* h) {
   hipEvent_t e = nullptr;
   if (hipEventCreate(&e) != hipSuccess) return nullptr;
   return e;
+}
+
+// The distribution between the planes of the current f and the caller's canonical host array,
+// in pieces of one pinned block: whole cells, or where one cell is larger than a block a range of
+// its velocities.  The device transposes a piece into (out of) a block while the host copies the
+// one before it; large arrays are copied by several host threads, each on its own pieces and
+// blocks, since one thread's copy is slower than the host link.
+struct StatePieces {
+  ugks_handle* h;
+  double* host;
+  bool out;
+  long long nc;
+  int nvt;            // values of a cell
+  int cells, vels;    // of a piece
+  long long count;    // pieces
+};
+// Pieces first, first + stride, ...
+hipError_t move_pieces(const StatePieces& sp, long long first, long long stride) {
+  ugks_handle* h = sp.h;
+  void* blk[2] = {g_pinned.get(), nullptr};
+  if (first + stride < sp.count) blk[1] = g_pinned.get();
+  hipEvent_t ev[2] = {};
+  hipError_t e = blk[0] ? hipSetDevice(h->device) : hipErrorOutOfMemory;
+  const int nb = blk[1] ? 2 : 1;
+  for (int b = 0; b < nb && e == hipSuccess; ++b)
+    e = hipEventCreateWithFlags(&ev[b], hipEventDisableTiming);
+  void* f = h->B.f[h->steps & 1];
+  const int fp32 = h->inst.fp32;
+  const long long per_row = (sp.nvt + sp.vels - 1) / sp.vels;
+  struct At {
+    long long c0;
+    int ncell, v0, nvel;
+  };
+  auto at = [&](long long p) {
+    const long long c0 = p / per_row * sp.cells;
+    const int v0 = (int)(p % per_row) * sp.vels;
+    return At{c0, (int)std::min<long long>(sp.cells, sp.nc - c0), v0,
+              std::min(sp.vels, sp.nvt - v0)};
+  };
+  auto host_at = [&](const At& a) { return sp.host + a.c0 * sp.nvt + a.v0; };
+  auto bytes = [&](const At& a) { return (size_t)a.ncell * a.nvel * 8; };  // contiguous
+  auto launch = [&](long long p, int b) {
+    const At a = at(p);
+    hipError_t r = launch_state(h->P, f, fp32, sp.out, a.c0, a.ncell, a.v0, a.nvel,
+                                static_cast<double*>(blk[b]), h->stream);
+    return r == hipSuccess ? hipEventRecord(ev[b], h->stream) : r;
+  };
+  if (sp.out) {
+    // the next piece is under way while this one is copied
+    if (e == hipSuccess && first < sp.count) e = launch(first, 0);
+    int b = 0;
+    for (long long p = first; p < sp.count && e == hipSuccess; p += stride) {
+      const long long next = p + stride;
+      if (nb == 2 && next < sp.count) e = launch(next, b ^ 1);
+      if (e == hipSuccess) e = hipEventSynchronize(ev[b]);
+      if (e != hipSuccess) break;
+      const At a = at(p);
+      std::memcpy(host_at(a), blk[b], bytes(a));
+      if (nb == 2)
+        b ^= 1;
+      else if (next < sp.count)
+        e = launch(next, 0);
+    }
+  } else {
+    bool used[2] = {false, false};
+    int b = 0;
+    for (long long p = first; p < sp.count && e == hipSuccess; p += stride) {
+      if (used[b]) e = hipEventSynchronize(ev[b]);
+      if (e != hipSuccess) break;
+      const At a = at(p);
+      std::memcpy(blk[b], host_at(a), bytes(a));
+      e = launch(p, b);
+      used[b] = true;
+      b = nb == 2 ? b ^ 1 : b;
+    }
+  }
+  // no block goes back while the device may still use it
+  for (int b = 0; b < nb; ++b)
+    if (ev[b]) {
+      if (e == hipSuccess)
+        e = hipEventSynchronize(ev[b]);
+      else
+        (void)hipStreamSynchronize(h->stream);
+      (void)hipEventDestroy(ev[b]);
+    }
+  g_pinned.put(blk[0]);
+  g_pinned.put(blk[1]);
+  return e;
+}
+hipError_t move_state(ugks_handle* h, double* host, bool out) {
+  StatePieces sp{h, host, out, (long long)h->P.nx * h->P.ny, h->P.NV * h->P.NC, 0, 0, 0};
+  const long long cap = (long long)(kPinnedBytes / 8);
+  sp.vels = (int)std::min<long long>(sp.nvt, cap);
+  sp.cells = (int)std::max<long long>(1, std::min<long long>(sp.nc, cap / sp.nvt));
+  sp.count = (sp.nc + sp.cells - 1) / sp.cells * ((sp.nvt + sp.vels - 1) / sp.vels);
+  // a thread for every four pieces (8 MB), at most four
+  const int nt = (int)std::min<long long>(4, (sp.count + 3) / 4);
+  std::thread th[3];
+  hipError_t e[4] = {};
+  int started = 0;
+  for (; started < nt - 1; ++started) {
+    const int t = started;
+    try {
+      th[t] = std::thread([&sp, &e, t, nt] { e[t + 1] = move_pieces(sp, t + 1, nt); });
+    } catch (const std::system_error&) {
+      break;  // the caller's thread takes the pieces of the threads that did not start
+    }
+  }
+  e[0] = move_pieces(sp, 0, nt);
+  for (int t = started + 1; t < nt; ++t)
+    if (e[0] == hipSuccess) e[0] = move_pieces(sp, t, nt);
+  for (int t = 0; t < started; ++t) th[t].join();
+  for (int t = 1; t < 4; ++t)
+    if (e[0] == hipSuccess) e[0] = e[t];
+  return e[0];
 }
 
 // Enqueue one step of a plan: four launches, each bracketed by timing events when enabled.
@@ -735,6 +900,7 @@ int ugks_create(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, const
     delete h;
     return rc;
   }
+  g_pinned.add_user();
   *out = h;
   return UGKS_OK;
 }
@@ -825,6 +991,7 @@ int ugks_destroy(ugks_handle* h) {
   for (auto e : h->pool) (void)hipEventDestroy(e);
   if (h->owns_ws) (void)hipFree(h->ws);
   delete h;
+  g_pinned.drop_user();
   return UGKS_OK;
 }
 
@@ -876,15 +1043,8 @@ int ugks_get_state(ugks_handle* h, double* f, double* W) {
   Busy b(h);
   if (!b.ok) return fail(h, UGKS_E_BUSY, "handle in use%s");
   if (h->poisoned) return poisoned_fail(h);
-  const size_t nc = (size_t)h->P.nx * h->P.ny, NV = (size_t)h->P.NV * h->P.NC;
-  const size_t PS = (size_t)h->P.PS;
-  hipError_t e = hipSuccess;
-  std::vector<char> raw;
-  if (f) {
-    raw.resize(NV * PS * h->ssize);
-    e = hipMemcpyAsync(raw.data(), h->B.f[h->steps & 1], raw.size(), hipMemcpyDeviceToHost,
-                       h->stream);
-  }
+  const size_t nc = (size_t)h->P.nx * h->P.ny;
+  hipError_t e = f ? move_state(h, f, true) : hipSuccess;
   if (e == hipSuccess && W)
     e = hipMemcpyAsync(W, h->B.W[h->steps & 1], nc * 4 * 8, hipMemcpyDeviceToHost, h->stream);
   int flag = 0;
@@ -892,17 +1052,6 @@ int ugks_get_state(ugks_handle* h, double* f, double* W) {
     e = hipMemcpyAsync(&flag, h->B.flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "reading the state");
-  if (f) {
-    for (size_t c = 0; c < nc; ++c) {
-      const size_t at = plane_index(h->P, c);
-      for (size_t v = 0; v < NV; ++v) {
-        const size_t sl = v * PS + at;
-        f[c * NV + v] = h->prec == UGKS_FP32_STORE
-                            ? (double)reinterpret_cast<const float*>(raw.data())[sl]
-                            : reinterpret_cast<const double*>(raw.data())[sl];
-      }
-    }
-  }
   if (flag) return fail(h, UGKS_E_STATE, "invalid state flagged on the device%s");
   return UGKS_OK;
 }
@@ -912,25 +1061,8 @@ int ugks_set_state(ugks_handle* h, const double* f, const double* W) {
   Busy b(h);
   if (!b.ok) return fail(h, UGKS_E_BUSY, "handle in use%s");
   if (h->poisoned) return poisoned_fail(h);
-  const size_t nc = (size_t)h->P.nx * h->P.ny, NV = (size_t)h->P.NV * h->P.NC;
-  const size_t PS = (size_t)h->P.PS;
-  std::vector<char> raw;
-  hipError_t e = hipSuccess;
-  if (f) {
-    raw.assign(NV * PS * h->ssize, 0);
-    for (size_t c = 0; c < nc; ++c) {
-      const size_t at = plane_index(h->P, c);
-      for (size_t v = 0; v < NV; ++v) {
-        const size_t sl = v * PS + at;
-        if (h->prec == UGKS_FP32_STORE)
-          reinterpret_cast<float*>(raw.data())[sl] = (float)f[c * NV + v];
-        else
-          reinterpret_cast<double*>(raw.data())[sl] = f[c * NV + v];
-      }
-    }
-    e = hipMemcpyAsync(h->B.f[h->steps & 1], raw.data(), raw.size(), hipMemcpyHostToDevice,
-                       h->stream);
-  }
+  const size_t nc = (size_t)h->P.nx * h->P.ny;
+  hipError_t e = f ? move_state(h, const_cast<double*>(f), false) : hipSuccess;
   if (e == hipSuccess && W)
     e = hipMemcpyAsync(h->B.W[h->steps & 1], W, nc * 4 * 8, hipMemcpyHostToDevice, h->stream);
   // the adaptive step of the next step follows the new W
@@ -938,7 +1070,7 @@ int ugks_set_state(ugks_handle* h, const double* f, const double* W) {
   if (e == hipSuccess && W)
     e = hipMemcpyAsync(h->B.rmax + (h->steps & 1), &rb, sizeof rb, hipMemcpyHostToDevice,
                        h->stream);
-  // the ghost columns and ghost states of the new state (the host image's halo is zero)
+  // the ghost columns and ghost states of the new state (the rest of the halo stays zero)
   if (e == hipSuccess) {
     PlanView pv = h->pv;
     pv.step = (int)(h->steps & 1);
@@ -1020,6 +1152,7 @@ int ugks_batch_create(void* stream, int max_instances, ugks_batch** out) {
     (void)hipGetLastError();
     return fail(nullptr, UGKS_E_NOMEM, "batch plan allocation failed%s");
   }
+  g_pinned.add_user();
   *out = b;
   return UGKS_OK;
 }
@@ -1151,6 +1284,7 @@ int ugks_batch_destroy(ugks_batch* b) {
   if (b->plan_dev) (void)hipFree(b->plan_dev);
   if (b->plan_host) (void)hipHostFree(b->plan_host);
   delete b;
+  g_pinned.drop_user();
   return UGKS_OK;
 }
 

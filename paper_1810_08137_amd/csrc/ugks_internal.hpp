@@ -195,6 +195,10 @@ hipError_t launch_poison(const PlanView& pv, int fp32, long long nvalues, hipStr
 // (after the initial state and after ugks_set_state; the update kernel writes those of the
 // next step in every step), with the update kernel's own arithmetic.
 hipError_t launch_ghost_fill(const PlanView& pv, const PlanTotals& t, int fp32, hipStream_t s);
+// Cells [c0, c0 + ncell) by velocities [v0, v0 + nvel) (of the NC NV values of a cell) of the
+// plane buffer f to (out) or from the canonical image img in pinned host memory.
+hipError_t launch_state(const KParams& P, void* f, int fp32, bool out, long long c0, int ncell,
+                        int v0, int nvel, double* img, hipStream_t s);
 hipError_t launch_step(const PlanView& pv, const PlanTotals& t, int fp32, hipStream_t s,
                        hipEvent_t* ev /* 8 events or NULL */);
 hipError_t launch_phase(const PlanView& pv, const PlanTotals& t, int fp32, int phase,
