@@ -26,9 +26,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "0b1ea27e543d3c7160223441a30319974acddb932b2e7ac6ac62eb973f78f43b",
-    "fp64": 1.3108e9,
-    "fp32_store": 0.6984e9,
+    "source_sha256": "8e0c2759411ab1bfe65e6d55276fd095559c4e92e422f4ebeb71adcc050fdd1d",
+    "fp64": 1.3078e9,
+    "fp32_store": 0.6998e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
     "valu_fp64": 1.0102e8,
 }

@@ -957,26 +957,25 @@ int ugks_moments(ugks_handle* h, double* host_out) {
   if (!b.ok) return fail(h, UGKS_E_BUSY, "handle in use%s");
   if (h->poisoned) return poisoned_fail(h);
   const size_t nc = (size_t)h->P.nx * h->P.ny;
-  std::vector<double> W(4 * nc);
-  int flag = 0;
-  hipError_t e = hipMemcpyAsync(W.data(), h->B.W[h->steps & 1], W.size() * 8,
-                                hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(&flag, h->B.flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "reading W");
-  bool bad = flag != 0;
-  for (size_t c = 0; c < nc; ++c) {
-    const double* w = &W[4 * c];
-    const double rho = w[0], U = w[1] / rho, V = w[2] / rho;
-    const double T = (w[3] - 0.5 * rho * (U * U + V * V)) / (h->P.lam_c * rho);
-    host_out[4 * c + 0] = rho;
-    host_out[4 * c + 1] = U;
-    host_out[4 * c + 2] = V;
-    host_out[4 * c + 3] = T;
-    if (!(rho > 0) || !(T > 0) || !std::isfinite(U) || !std::isfinite(V) || !std::isfinite(T))
-      bad = true;
+  // through a pinned block: its first 64 bytes hold the mark of an invalid state
+  constexpr size_t kHead = 64, kCells = (kPinnedBytes - kHead) / 32;
+  char* blk = static_cast<char*>(g_pinned.get());
+  if (!blk) return hip_fail(h, hipErrorOutOfMemory, "pinned memory for the moments");
+  int* mark = reinterpret_cast<int*>(blk);
+  *mark = 0;
+  const double* W = h->B.W[h->steps & 1];
+  hipError_t e = hipSuccess;
+  for (size_t c0 = 0; c0 < nc && e == hipSuccess; c0 += kCells) {
+    const size_t n = std::min(kCells, nc - c0);
+    e = launch_moments(W + 4 * c0, (int)n, h->P.lam_c, h->B.flag,
+                       reinterpret_cast<double*>(blk + kHead), mark, h->stream);
+    const hipError_t es = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess) e = es;
+    if (e == hipSuccess) std::memcpy(host_out + 4 * c0, blk + kHead, n * 32);
   }
+  const bool bad = *mark != 0;
+  g_pinned.put(blk);
+  if (e != hipSuccess) return hip_fail(h, e, "reading the moments");
   if (bad) return fail(h, UGKS_E_STATE, "invalid state (NaN, rho <= 0 or T <= 0)%s");
   return UGKS_OK;
 }

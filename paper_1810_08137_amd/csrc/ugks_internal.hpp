@@ -199,6 +199,10 @@ hipError_t launch_ghost_fill(const PlanView& pv, const PlanTotals& t, int fp32, 
 // plane buffer f to (out) or from the canonical image img in pinned host memory.
 hipError_t launch_state(const KParams& P, void* f, int fp32, bool out, long long c0, int ncell,
                         int v0, int nvel, double* img, hipStream_t s);
+// (rho, U, V, T) of the n cells of W into pinned host memory; *bad (there too) becomes 1 if one of
+// them is invalid or *flag is set.
+hipError_t launch_moments(const double* W, int n, double lam_c, const int* flag, double* out,
+                          int* bad, hipStream_t s);
 hipError_t launch_step(const PlanView& pv, const PlanTotals& t, int fp32, hipStream_t s,
                        hipEvent_t* ev /* 8 events or NULL */);
 hipError_t launch_phase(const PlanView& pv, const PlanTotals& t, int fp32, int phase,

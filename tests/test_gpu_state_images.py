@@ -41,3 +41,26 @@ def test_state_goes_out_and_back(form):
             assert np.array_equal(x, y)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("mesh", [(1, 1), (7, 5), (300, 219)], ids=str)
+def test_moments_are_those_of_the_state(mesh):
+    """(300 x 219 cells: more than one piece.)  The primitive variables of W, operation by
+    operation, so the values are the same bits."""
+    case = dict(WL.CHANNEL_DEFAULTS, nx=mesh[0], ny=mesh[1], lx=2.0, ly=1.0, nu=8, nv=8, umax=4.0,
+                vmax=4.0, kn=0.1, seed=4, dof=1)
+    kn, kw = WL.solver_kwargs(case, "fp64")
+    s = ugks.Solver(kn, **kw)
+    s.step(2)
+    _, W = ugks.ugks_get_state(s.h, want_f=False)
+    m = s.moments()
+    rho, U, V = W[..., 0], W[..., 1] / W[..., 0], W[..., 2] / W[..., 0]
+    T = (W[..., 3] - 0.5 * rho * (U * U + V * V)) / (0.75 * rho)
+    assert np.array_equal(m, np.stack([rho, U, V, T], -1))
+    # an invalid cell anywhere is reported, after the values are written
+    W[-1, -1, 3] = -1.0
+    s.set_state(W=W)
+    with pytest.raises(ugks.UgksError) as e:
+        s.moments()
+    assert e.value.code == ugks.UGKS_E_STATE
+    s.close()
