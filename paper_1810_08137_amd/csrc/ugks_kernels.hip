@@ -28,8 +28,11 @@
 // kernels (heat sums; equilibria times (1 + S)).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <type_traits>
 
 #include "ugks_internal.hpp"
@@ -298,10 +301,15 @@ __device__ __forceinline__ double step_dt(const KParams& P, int parity) {
 __device__ __forceinline__ int wrap(int i, int n) { return ((i % n) + n) % n; }
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
-// Workgroups are handed to the 8 XCDs round-robin; renumber them so that each XCD works
-// through one contiguous range (its own L2 then serves the rows its neighbours also read).
-__device__ __forceinline__ int xcd_block(int b, int nb) {
-  const int q = nb / 8, r = nb % 8, x = b % 8, i = b / 8;
+// Workgroups are handed to the 8 XCDs round-robin; renumber the n of one instance, whose blocks
+// start at a multiple of 8, so that each XCD works through one contiguous range of them (its own
+// L2 then serves the rows its neighbours also read) and all XCDs work on every instance.  -1: one
+// of the blocks that fill the instance up to a multiple of 8.
+constexpr int kXcd = 8;
+__host__ __device__ __forceinline__ int xcd_round(int n) { return (n + kXcd - 1) / kXcd * kXcd; }
+__device__ __forceinline__ int xcd_block(int local, int n) {
+  const int q = n / kXcd, r = n % kXcd, x = local % kXcd, i = local / kXcd;
+  if (i >= q + (x < r ? 1 : 0)) return -1;
   return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
@@ -521,13 +529,15 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(PlanView pv) {
   __shared__ double cellred[kShak ? 3 : 1][8][kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int b = xcd_block(blockIdx.x, gridDim.x);
-  const int ii = find_inst(pv.off_sums, pv.ninst, b);
+  const int ii = find_inst(pv.off_sums, pv.ninst, blockIdx.x);
   const Inst* __restrict__ I = inst_at(pv, ii);
   const KParams P = I->P;
   const int G = I->gsplit;
+  const int ntx = (P.nx + kTileS - 1) / kTileS;
+  const int b = xcd_block(blockIdx.x - first_block(pv.off_sums, ii), ntx * P.ny * G * P.NC);
+  if (b < 0) return;
   int t, gg, j;
-  cell_block(b - first_block(pv.off_sums, ii), P.ny, (P.nx + kTileS - 1) / kTileS, t, gg, j);
+  cell_block(b, P.ny, ntx, t, gg, j);
   const bool hpart = gg >= G;  // planes of H
   const int g = hpart ? gg - G : gg;
   const UGKS_GLOBAL S* f = static_cast<const UGKS_GLOBAL S*>(I->f[(I->cur + pv.step) & 1]) +
@@ -1787,15 +1797,17 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
   // wavefront w: quadrant q, and c, which of the workgroup's kCh velocity chunks
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q = w & 3, c = w >> 2;
-  const int b = xcd_block(blockIdx.x, gridDim.x);
-  const int ii = find_inst(pv.off_upd, pv.ninst, b);
+  const int ii = find_inst(pv.off_upd, pv.ninst, blockIdx.x);
   const Inst* __restrict__ I = inst_at(pv, ii);
   const KParams P = I->P;
   const int parity = (I->cur + pv.step) & 1;
   const int G = I->usplit, Gv = P.vsplit;
+  const int ntx = (P.nx + kTileU - 1) / kTileU;
+  const int b = xcd_block(blockIdx.x - first_block(pv.off_upd, ii),
+                          ntx * ((P.ny + 1) / 2) * G * Gv * P.NC);
+  if (b < 0) return;
   int t, gg, pb;
-  cell_block(b - first_block(pv.off_upd, ii), (P.ny + 1) / 2, (P.nx + kTileU - 1) / kTileU, t,
-             gg, pb);
+  cell_block(b, (P.ny + 1) / 2, ntx, t, gg, pb);
   const int jb = min(2 * pb, P.ny - 2);       // rows jb, jb + 1
   const bool store0 = jb == 2 * pb && jb >= 0;  // row jb is this pair's to write
   // chunk gg: u chunk g of G fastest, then v chunk gv of Gv; chunks G Gv.. update H: its
@@ -2018,7 +2030,7 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
                   (unsigned long long)__double_as_longlong(rate));
     }
     // the simulated time advances by this step's dt (one thread of the instance)
-    if (!kFill && b == first_block(pv.off_upd, ii) && w == 0 && lane == 0)
+    if (!kFill && b == 0 && w == 0 && lane == 0)
       *P.tsum += step_dt(P, parity);
     Prim pn{}, p1{};
     double Af = 1.0, AdF = 1.0 / P.area, A1 = 0.0, An = 0.0;
@@ -2334,13 +2346,29 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
   const char* d = static_cast<const char*>(dev);
   const size_t inst_bytes = ((sizeof(Inst) * (size_t)n + 255) / 256) * 256;
   const size_t off_bytes = (((size_t)(n + 1) * sizeof(int) + 255) / 256) * 256;
-  std::memcpy(h, insts, sizeof(Inst) * (size_t)n);
+  // The instances with the longest workgroups first (their nodes per quadrant), so that a launch
+  // ends on short ones.  Twelve FP32-storage solves of the serving shapes (190M updates a step):
+  // 1174 us in the callers' order with one XCD range over all instances, 1022 with the range per
+  // instance (some XCDs had only long workgroups), 949 with this order as well.  More and smaller
+  // chunks for the longer instances gained nothing further.
+  Inst* img = reinterpret_cast<Inst*>(h);
+  {
+    std::unique_ptr<int[]> order(n > 1 ? new (std::nothrow) int[n] : nullptr);
+    if (order) {
+      for (int q = 0; q < n; ++q) order[q] = q;
+      auto nodes = [&](int q) { return (long long)insts[q].P.K * insts[q].P.M; };
+      std::sort(order.get(), order.get() + n, [&](int a, int b) {
+        return nodes(a) != nodes(b) ? nodes(a) > nodes(b) : a < b;
+      });
+    }
+    for (int q = 0; q < n; ++q) std::memcpy(img + q, insts + (order ? order[q] : q), sizeof(Inst));
+    insts = img;
+  }
   int* off[6];
   for (int a = 0; a < 6; ++a) off[a] = reinterpret_cast<int*>(h + inst_bytes + a * off_bytes);
   PlanTotals t{};
   // each instance keeps the velocity chunks it was created with, in any plan, so that its
   // sums are added in the same order whether it is stepped alone or in a batch
-  Inst* img = reinterpret_cast<Inst*>(h);
   long long upd_base = 0;  // update workgroups of all instances with one chunk
   for (int q = 0; q < n; ++q) {
     const KParams& P = insts[q].P;
@@ -2405,8 +2433,9 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
     off[4][q] = t.red;
     off[5][q] = 0;
     t.shak = t.shak || P.shak;
-    t.sums += ((P.nx + kTileS - 1) / kTileS) * P.ny * G;
-    t.upd += ((P.nx + kTileU - 1) / kTileU) * ((P.ny + 1) / 2) * img[q].usplit * P.vsplit * P.NC;
+    t.sums += xcd_round(((P.nx + kTileS - 1) / kTileS) * P.ny * G);
+    t.upd += xcd_round(((P.nx + kTileU - 1) / kTileU) * ((P.ny + 1) / 2) * img[q].usplit *
+                       P.vsplit * P.NC);
     if (G > 1)
       t.red += (nfx + t.red_faces - 1) / t.red_faces + (nfy + t.red_faces - 1) / t.red_faces +
                (P.shak ? ((kSlotsShakhov - kSlotCell) * (int)P.ncs + kWave * t.red_waves - 1) /

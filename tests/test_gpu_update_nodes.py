@@ -55,3 +55,26 @@ def test_chunks_by_node_match_the_oracle(form):
     case, precision = _case(form)
     tol = PR.FP64_TOL if precision == "fp64" else PR.FP32_STORE_TOL
     PR.run_and_compare(case, 3, precision=precision, tol=tol, label=f"by node {form}")
+
+
+def test_a_batch_in_any_order_steps_as_alone():
+    """A plan takes its instances in the order of their velocity counts: whatever order the
+    caller's list has, every member steps to the bits it has alone."""
+    shapes = [(50, 12, 24), (61, 7, 48), (9, 3, 32), (100, 25, 24), (1, 1, 48), (130, 5, 33)]
+    alone, members = [], []
+    for n, (nx, ny, nv) in enumerate(shapes):
+        case = dict(WL.CHANNEL_DEFAULTS, lx=2.0, ly=1.0, umax=5.0, vmax=5.0, kn=0.1, seed=n,
+                    nx=nx, ny=ny, nu=nv, nv=nv, bc=n % 2)
+        alone.append(_solver(case, "fp64"))
+        members.append(_solver(case, "fp64"))
+    batch = ugks.Batch(len(shapes))
+    for order in ([0, 1, 2, 3, 4, 5], [5, 3, 1, 4, 2, 0], [2, 5]):
+        batch.step([members[k] for k in order], 2)
+        for k in order:
+            alone[k].step(2)
+    for a, b in zip(alone, members):
+        for x, y in zip(a.state(), b.state()):
+            assert np.array_equal(x, y)
+        a.close()
+        b.close()
+    batch.close()
