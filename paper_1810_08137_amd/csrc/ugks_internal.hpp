@@ -156,7 +156,7 @@ struct PlanView {
   const int* off_sums;   // one workgroup per (row segment, velocity chunk) of the moment kernel
   const int* off_upd;    // one workgroup per (row segment, velocity chunk) of the update kernel
   const int* off_face;   // 256 faces per workgroup (instances with one part of every sum)
-  const int* off_ghost;  // periodic: the halo frame of every plane (a channel has none)
+  const int* off_ghost;  // periodic: the halo rows of every plane (a channel has none)
   const int* off_red;    // red_faces per workgroup (instances with several parts of every sum)
   int ninst;
   int step;              // steps enqueued since the plan's `cur` values were taken
