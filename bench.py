@@ -26,11 +26,11 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "d463f92da29743862d33562d23551efb57850d219bda12a7b70fe055c62c422b",
-    "fp64": 1.3093e9,
-    "fp32_store": 0.7012e9,
+    "source_sha256": "d63bfcbf341446fdbaf71a08b582a8cf459539c5142adc4ae5cb35da9a817d4d",
+    "fp64": 1.34e9,
+    "fp32_store": 0.7009e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
-    "valu_fp64": 1.0098e8,
+    "valu_fp64": 1.0107e8,
 }
 # VALU issue ceiling: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles at
 # 2.4 GHz (FP64 FMA runs at this full rate on MI355X: 78.6 TFLOP/s)
