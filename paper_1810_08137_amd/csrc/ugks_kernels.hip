@@ -201,23 +201,31 @@ __device__ __forceinline__ double collision_time(const Prim& p, double mu_ref) {
   return 2.0 * mu_ref * sqrt(p.lam) / p.rho;
 }
 
-// Moments of the normalised 1D Maxwellian along one axis: full line, u > 0, u < 0.
-__device__ void axis_moments(double U, double lam, double* full, double* pos, double* neg) {
-  const double edge = exp(-lam * U * U) / (2.0 * sqrt(kPi * lam));
-  const double sl = sqrt(lam);
-  full[0] = 1.0;
-  full[1] = U;
-  pos[0] = 0.5 * erfc(-sl * U);
-  neg[0] = 0.5 * erfc(sl * U);
-  pos[1] = U * pos[0] + edge;
-  neg[1] = U * neg[0] - edge;
+// Moments 0..6 of the normalised 1D Maxwellian along one axis: full line, and one half of it
+// (side 0: u > 0, 1: u < 0), from their first two and the factors c[n] of the recurrence.
+__device__ __forceinline__ void axis_factors(double lam, double* c) {
 #pragma unroll
-  for (int n = 2; n < 7; ++n) {
-    const double c = (double)(n - 1) / (2.0 * lam);
-    full[n] = U * full[n - 1] + c * full[n - 2];
-    pos[n] = U * pos[n - 1] + c * pos[n - 2];
-    neg[n] = U * neg[n - 1] + c * neg[n - 2];
-  }
+  for (int n = 2; n < 7; ++n) c[n] = (double)(n - 1) / (2.0 * lam);
+}
+__device__ __forceinline__ void axis_full(double U, const double* c, double* m) {
+  m[0] = 1.0;
+  m[1] = U;
+#pragma unroll
+  for (int n = 2; n < 7; ++n) m[n] = U * m[n - 1] + c[n] * m[n - 2];
+}
+__device__ __forceinline__ void axis_half_line(double U, const double* c, double m0, double edge,
+                                               int side, double* m) {
+  m[0] = m0;
+  m[1] = U * m[0] + (side == 0 ? edge : -edge);
+#pragma unroll
+  for (int n = 2; n < 7; ++n) m[n] = U * m[n - 1] + c[n] * m[n - 2];
+}
+__device__ __forceinline__ double axis_edge(double U, double lam) {
+  return exp(-lam * U * U) / (2.0 * sqrt(kPi * lam));
+}
+__device__ __forceinline__ double axis_m0(double U, double lam, int side) {
+  const double sU = sqrt(lam) * U;
+  return 0.5 * erfc(side == 0 ? -sU : sU);
 }
 
 // Gaussian moments of the internal coordinates xi at lambda: x2 = <|xi|^2> = dof/(2 lambda),
@@ -809,12 +817,6 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(PlanView pv) {
   }
 }
 
-// S2-S5 at one interior interface, local frame.  S = [W0, Wt, Q1, Q2].  Writes the local
-// macroscopic flux to F and the folded coefficients of the distribution flux to rec; with
-// internal degrees of freedom (kXi) also those of H to recH.  Averaged over xi, the energy
-// term c_4 psi_4 of a slope c contributes c_4 (un^2 + ut^2 + s)/2 to the polynomial of G with
-// s = <|xi|^2> = x2, and to that of H, whose Maxwellian is x2 times that of G, with
-// s = <|xi|^4>/<|xi|^2> = x4/x2: the constant shifts e0, e1 and e2 by c_4 s/2.
 // Heat flux q = sum w c |c|^2 f / 2 about (U, V) from raw sums of f: m0 = sum f, mn = sum un f,
 // mt = sum ut f, mnn, mnt, mtt = sum un^2 f, un ut f, ut^2 f, Kn = sum un |c|^2 f,
 // Kt = sum ut |c|^2 f, K0 = sum |c|^2 f (|c|^2 = un^2 + ut^2).
@@ -859,81 +861,67 @@ __device__ __forceinline__ void fold_shakhov(RecRef rec, const Prim& p0,
   rec[R_ER + 3] = fma(km, d[7], rec[R_ER + 3]);
 }
 
-template <bool kXi>
-__device__ void interface_scalars(const KParams& P, double dt, const double* S, const double* WL,
-                                  const double* WR, double dn, double len, double* F,
-                                  RecRef rec, RecRef recH,
-                                  double& U0, double& V0, double T3 = 0.0) {
-  const double* W0 = S;
-  const double* Wt = S + 4;
-  const double* Q1 = S + 8;
-  const double* Q2 = S + 12;
-  if (P.collisionless) {
-    const double Mt4 = dt, Mt5 = 0.5 * dt * dt;
+// A face of a collisionless gas: free transport alone.
+__device__ __forceinline__ void free_flux(double dt, const double* Q1, const double* Q2, double len,
+                                          int NC, double* F, RecRef rec, RecRef recH) {
+  const double Mt4 = dt, Mt5 = 0.5 * dt * dt;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) F[q] = len * (Mt4 * Q1[q] - Mt5 * Q2[q]);
+  for (int q = 0; q < 4; ++q) F[q] = len * (Mt4 * Q1[q] - Mt5 * Q2[q]);
+  for (int c = 0; c < NC; ++c) {
+    const RecRef r = c ? recH : rec;
 #pragma unroll
-    for (int q = 0; q < 13; ++q) rec[R_E + q] = 0.0;
-    rec[R_GC] = 0.0;
-    rec[R_LAM] = 0.0;
-    rec[R_M4] = len * Mt4;
-    rec[R_M5] = len * Mt5;
-    rec[R_KIND] = K_FREE;
-    if constexpr (kXi) {
-#pragma unroll
-      for (int q = R_GC; q < kRec; ++q) recH[q] = rec[q];
-    }
-    U0 = V0 = 0.0;
-    return;
+    for (int q = 0; q < 13; ++q) r[R_E + q] = 0.0;
+    r[R_GC] = 0.0;
+    r[R_LAM] = 0.0;
+    r[R_M4] = len * Mt4;
+    r[R_M5] = len * Mt5;
+    r[R_KIND] = K_FREE;
   }
-  Prim p0;
-  if (!prim_of(W0, p0, P.lam_c)) *P.flag = 1;
+}
+
+template <bool kXi>
+__device__ __forceinline__ Xi xi_of(const KParams& P, const Prim& p0) {
   Xi xi{0.0, 0.0};
   if constexpr (kXi) {
     xi.x2 = (double)P.dof / (2.0 * p0.lam);
     xi.x4 = (double)(P.dof * (P.dof + 2)) / (4.0 * p0.lam * p0.lam);
   }
-  const double tau0 = collision_time(p0, P.mu_ref);
-  double Mt[5];
-  time_weights(dt, tau0, Mt);
-  double swL[4], swR[4], aL[4], aR[4], b[4], A[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    swL[q] = (W0[q] - WL[q]) / (0.5 * dn);
-    swR[q] = (WR[q] - W0[q]) / (0.5 * dn);
-  }
-  micro_slope(p0, swL, aL, P.q_c, P.a4_c);
-  micro_slope(p0, swR, aR, P.q_c, P.a4_c);
-  micro_slope(p0, Wt, b, P.q_c, P.a4_c);
-  double mu[7], mp[7], mn[7], mv[7], tp[7], tn[7];
-  axis_moments(p0.U, p0.lam, mu, mp, mn);
-  axis_moments(p0.V, p0.lam, mv, tp, tn);
-  double m1[4], m2[4], m3[4], sA[4];
-  mpsi_c<kXi>(mp, mv, 1, 0, xi, aL, m1);
-  mpsi_c<kXi>(mn, mv, 1, 0, xi, aR, m2);
-  mpsi_c<kXi>(mu, mv, 0, 1, xi, b, m3);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) sA[q] = -p0.rho * (m1[q] + m2[q] + m3[q]);
-  micro_slope(p0, sA, A, P.q_c, P.a4_c);
-  double e0[4], eL[4], eR[4], eb[4], eA[4];
-  mpsi<kXi>(mu, mv, 1, 0, xi, e0);
-  mpsi_c<kXi>(mp, mv, 2, 0, xi, aL, eL);
-  mpsi_c<kXi>(mn, mv, 2, 0, xi, aR, eR);
-  mpsi_c<kXi>(mu, mv, 1, 1, xi, b, eb);
-  mpsi_c<kXi>(mu, mv, 1, 0, xi, A, eA);
-  // Shakhov: heat flux of the reconstruction at the interface (local frame); T3 is the sum of
-  // ut c2h f_hat, the other raw sums are W0 and Q1
-  double qh[2] = {0.0, 0.0};
+  return xi;
+}
+
+// Shakhov: heat flux of the reconstruction at the interface (local frame); T3 is the sum of
+// ut c2h f_hat, the other raw sums are W0 and Q1.
+__device__ __forceinline__ void face_heat(const KParams& P, const Prim& p0, const double* W0,
+                                          const double* Q1, double T3, double* qh) {
+  qh[0] = qh[1] = 0.0;
   if (P.shak)
     heat_flux(W0[0], W0[1], W0[2], Q1[1], Q1[2], 2.0 * W0[3] - Q1[1], 2.0 * Q1[3], 2.0 * T3,
               2.0 * W0[3], p0.U, p0.V, qh);
+}
+
+// The macroscopic flux of an interior face: its equilibrium part from the moments e0 .. eA of
+// u g0, of its slopes on both sides and in time, and of A; free transport from Q1 and Q2.
+__device__ __forceinline__ void macro_flux(const KParams& P, const Prim& p0, const double* Mt,
+                                           const double* e0, const double* eL, const double* eR,
+                                           const double* eb, const double* eA, const double* Q1,
+                                           const double* Q2, const double* qh, double len,
+                                           double* F) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     double feq = p0.rho * (Mt[0] * e0[q] + Mt[1] * (eL[q] + eR[q] + eb[q]) + Mt[2] * eA[q]);
     if (q == 3 && P.shak) feq = fma(Mt[0] * P.pr_c, qh[0], feq);
     F[q] = len * (feq + Mt[3] * Q1[q] - Mt[4] * Q2[q]);
   }
-  // folded polynomial of the equilibrium part of the distribution flux
+}
+
+// The folded polynomial of the equilibrium part of the distribution flux, and what else of the
+// record does not depend on the macroscopic flux.
+template <bool kXi>
+__device__ __forceinline__ void fold_record(const KParams& P, const Prim& p0, const Xi& xi,
+                                            const double* Mt, const double* aL,
+                                            const double* aR, const double* b,
+                                            const double* A, const double* qh, double len,
+                                            RecRef rec, RecRef recH) {
   rec[R_E + 0] = Mt[0] + Mt[2] * A[0];
   rec[R_E + 1] = Mt[1] * aL[0] + Mt[2] * A[1];
   rec[R_E + 2] = Mt[1] * b[0] + Mt[2] * A[2];
@@ -969,6 +957,60 @@ __device__ void interface_scalars(const KParams& P, double dt, const double* S, 
     rec[R_E + 2] = fma(sg, e8, rec[R_E + 2]);
     rec[R_ER + 0] = fma(sg, e7r, rec[R_ER + 0]);
   }
+}
+
+// S2-S5 at one interior interface, local frame.  S = [W0, Wt, Q1, Q2].  Writes the local
+// macroscopic flux to F and the folded coefficients of the distribution flux to rec; with
+// internal degrees of freedom (kXi) also those of H to recH.  Averaged over xi, the energy
+// term c_4 psi_4 of a slope c contributes c_4 (un^2 + ut^2 + s)/2 to the polynomial of G with
+// s = <|xi|^2> = x2, and to that of H, whose Maxwellian is x2 times that of G, with
+// s = <|xi|^4>/<|xi|^2> = x4/x2: the constant shifts e0, e1 and e2 by c_4 s/2.
+template <bool kXi>
+__device__ void interface_scalars(const KParams& P, double dt, const double* S, const double* WL,
+                                  const double* WR, double dn, double len, double* F,
+                                  RecRef rec, RecRef recH,
+                                  double& U0, double& V0, double T3 = 0.0) {
+  const double* W0 = S;
+  const double* Wt = S + 4;
+  const double* Q1 = S + 8;
+  const double* Q2 = S + 12;
+  Prim p0;
+  if (!prim_of(W0, p0, P.lam_c)) *P.flag = 1;
+  const Xi xi = xi_of<kXi>(P, p0);
+  double Mt[5];
+  time_weights(dt, collision_time(p0, P.mu_ref), Mt);
+  double swL[4], swR[4], aL[4], aR[4], b[4], A[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    swL[q] = (W0[q] - WL[q]) / (0.5 * dn);
+    swR[q] = (WR[q] - W0[q]) / (0.5 * dn);
+  }
+  micro_slope(p0, swL, aL, P.q_c, P.a4_c);
+  micro_slope(p0, swR, aR, P.q_c, P.a4_c);
+  micro_slope(p0, Wt, b, P.q_c, P.a4_c);
+  double c[7], mu[7], mp[7], mn[7], mv[7];
+  axis_factors(p0.lam, c);
+  const double edge = axis_edge(p0.U, p0.lam);
+  axis_full(p0.U, c, mu);
+  axis_half_line(p0.U, c, axis_m0(p0.U, p0.lam, 0), edge, 0, mp);
+  axis_half_line(p0.U, c, axis_m0(p0.U, p0.lam, 1), edge, 1, mn);
+  axis_full(p0.V, c, mv);
+  double m1[4], m2[4], m3[4], sA[4];
+  mpsi_c<kXi>(mp, mv, 1, 0, xi, aL, m1);
+  mpsi_c<kXi>(mn, mv, 1, 0, xi, aR, m2);
+  mpsi_c<kXi>(mu, mv, 0, 1, xi, b, m3);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sA[q] = -p0.rho * (m1[q] + m2[q] + m3[q]);
+  micro_slope(p0, sA, A, P.q_c, P.a4_c);
+  double e0[4], eL[4], eR[4], eb[4], eA[4], qh[2];
+  mpsi<kXi>(mu, mv, 1, 0, xi, e0);
+  mpsi_c<kXi>(mp, mv, 2, 0, xi, aL, eL);
+  mpsi_c<kXi>(mn, mv, 2, 0, xi, aR, eR);
+  mpsi_c<kXi>(mu, mv, 1, 1, xi, b, eb);
+  mpsi_c<kXi>(mu, mv, 1, 0, xi, A, eA);
+  face_heat(P, p0, W0, Q1, T3, qh);
+  macro_flux(P, p0, Mt, e0, eL, eR, eb, eA, Q1, Q2, qh, len, F);
+  fold_record<kXi>(P, p0, xi, Mt, aL, aR, b, A, qh, len, rec, recH);
   U0 = p0.U;
   V0 = p0.V;
 }
@@ -1033,49 +1075,87 @@ __device__ __forceinline__ void face_sides(const Inst* __restrict__ I, const KPa
   wr[3] = WR[3];
 }
 
-// The record(s) of one face from its sums S (both sides added; a wall: those of its cell) and
-// heat sum T3.  With internal degrees of freedom each face also gets the record of H, nf
+// Records of one face.  With internal degrees of freedom each face also gets the record of H, nf
 // records after that of G; it repeats the macroscopic flux, so either record serves Eq. (4).
+template <bool kX>
+__device__ __forceinline__ RecRef record_at(const Inst* __restrict__ I, const Face<kX>& f, int c) {
+  return RecRef{(kX ? I->recx : I->recy) + f.e + (size_t)c * f.nf * kRec, f.nf};
+}
+// The macroscopic flux F in the local frame.
+template <bool kX>
+__device__ __forceinline__ void put_flux(const RecRef& r, const double* F) {
+  r[R_FX + 0] = F[0];
+  r[kX ? R_FX + 1 : R_FX + 2] = F[1];
+  r[kX ? R_FX + 2 : R_FX + 1] = F[2];
+  r[R_FX + 3] = F[3];
+}
+// The interface velocity in the local frame.
+template <bool kX>
+__device__ __forceinline__ void put_velocity(const RecRef& r, double U0, double V0) {
+  r[kX ? R_UX : R_VY] = U0;
+  r[kX ? R_VY : R_UX] = V0;
+}
+
+// The record(s) of a channel wall from the sums S of its cell.
+template <bool kX>
+__device__ __forceinline__ void wall_record(const Inst* __restrict__ I, const KParams& P,
+                                            double dt, const Face<kX>& f, const double* S) {
+  const RecRef rec = record_at(I, f, 0), recH = record_at(I, f, 1);
+  // diffuse wall: sums of the wall-row cell towards the wall; local frame (v, u)
+  const bool top = f.j == P.ny;
+  const double* Q1 = S + 8;
+  const double den = top ? P.wall_den_top : P.wall_den_bot;
+  const double* Gw = top ? P.wall_G_top : P.wall_G_bot;
+  const double rho_w = -Q1[0] / den;
+  const double s = P.dx * dt;
+  double Fl[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) Fl[q] = s * (Q1[q] + rho_w * Gw[q]);
+  // H leaves the wall with kap_w times the Maxwellian of G
+  for (int c = 0; c < P.NC; ++c) {
+    const RecRef r = c ? recH : rec;
+    put_flux<kX>(r, Fl);
+    r[R_GC] = s * rho_w * P.lam_w / kPi * (c ? P.kap_w : 1.0);
+    r[R_LAM] = P.lam_w;
+    r[R_UX] = 0.0;
+    r[R_VY] = 0.0;
+    r[R_M4] = s;
+    r[R_M5] = 0.0;
+    r[R_KIND] = K_WALL;
+#pragma unroll
+    for (int q = 0; q < 13; ++q) r[R_E + q] = 0.0;  // a wall carries no polynomial
+  }
+  if (!(rho_w > 0.0) || !isfinite(rho_w)) *P.flag = 1;
+}
+
+// The record(s) of an interior face of a collisionless gas from its sums S.
+template <bool kX>
+__device__ __forceinline__ void free_record(const Inst* __restrict__ I, const KParams& P,
+                                            double dt, const Face<kX>& f, const double* S) {
+  const RecRef rec = record_at(I, f, 0), recH = record_at(I, f, 1);
+  double F[4];
+  free_flux(dt, S + 8, S + 12, kX ? P.dy : P.dx, P.NC, F, rec, recH);
+  for (int c = 0; c < P.NC; ++c) {
+    put_flux<kX>(c ? recH : rec, F);
+    put_velocity<kX>(c ? recH : rec, 0.0, 0.0);
+  }
+}
+
+// The record(s) of one face from its sums S (both sides added; a wall: those of its cell) and
+// heat sum T3.
 template <bool kX>
 __device__ __forceinline__ void face_record(const Inst* __restrict__ I, const KParams& P,
                                             double dt, const Face<kX>& f, const double* S,
                                             double T3, const double* wl, const double* wr) {
-  UGKS_GLOBAL double* r0 = (f.x ? I->recx : I->recy) + f.e;
-  const RecRef rec{r0, f.nf};
-  const RecRef recH{r0 + f.nf * kRec, f.nf};
-  // global components of the local (normal, tangential) axes
-  const int fn = f.x ? R_FX + 1 : R_FX + 2, ft = f.x ? R_FX + 2 : R_FX + 1;
   if (f.wall) {
-    // diffuse wall: sums of the wall-row cell towards the wall; local frame (v, u)
-    const bool top = f.j == P.ny;
-    const double* Q1 = S + 8;
-    const double den = top ? P.wall_den_top : P.wall_den_bot;
-    const double* Gw = top ? P.wall_G_top : P.wall_G_bot;
-    const double rho_w = -Q1[0] / den;
-    const double s = P.dx * dt;
-    double Fl[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) Fl[q] = s * (Q1[q] + rho_w * Gw[q]);
-    // H leaves the wall with kap_w times the Maxwellian of G
-    for (int c = 0; c < P.NC; ++c) {
-      const RecRef r = c ? recH : rec;
-      r[R_FX + 0] = Fl[0];
-      r[R_FX + 1] = Fl[2];
-      r[R_FX + 2] = Fl[1];
-      r[R_FX + 3] = Fl[3];
-      r[R_GC] = s * rho_w * P.lam_w / kPi * (c ? P.kap_w : 1.0);
-      r[R_LAM] = P.lam_w;
-      r[R_UX] = 0.0;
-      r[R_VY] = 0.0;
-      r[R_M4] = s;
-      r[R_M5] = 0.0;
-      r[R_KIND] = K_WALL;
-#pragma unroll
-      for (int q = 0; q < 13; ++q) r[R_E + q] = 0.0;  // a wall carries no polynomial
-    }
-    if (!(rho_w > 0.0) || !isfinite(rho_w)) *P.flag = 1;
+    wall_record(I, P, dt, f, S);
     return;
   }
+  if (P.collisionless) {
+    free_record(I, P, dt, f, S);
+    return;
+  }
+  const RecRef rec = record_at(I, f, 0), recH = record_at(I, f, 1);
   double F[4], U0, V0;
   const double dn = f.x ? P.dx : P.dy, len = f.x ? P.dy : P.dx;
   if (P.NC > 1)
@@ -1084,12 +1164,8 @@ __device__ __forceinline__ void face_record(const Inst* __restrict__ I, const KP
     interface_scalars<false>(P, dt, S, wl, wr, dn, len, F, rec, recH, U0, V0, T3);
   for (int c = 0; c < P.NC; ++c) {
     const RecRef r = c ? recH : rec;
-    r[R_FX + 0] = F[0];
-    r[fn] = F[1];
-    r[ft] = F[2];
-    r[R_FX + 3] = F[3];
-    r[f.x ? R_UX : R_VY] = U0;
-    r[f.x ? R_VY : R_UX] = V0;
+    put_flux<kX>(r, F);
+    put_velocity<kX>(r, U0, V0);
   }
 }
 
@@ -1135,20 +1211,171 @@ __global__ __launch_bounds__(256) void faces_kernel(PlanView pv) {
     face_direct<false>(I, P, parity, (long)(local - bx) * 256 + threadIdx.x);
 }
 
+// The chain of interface_scalars for kF faces of one family, with its independent parts on the
+// kNW wavefronts of a workgroup (lanes: faces).  The chain is about 2000 FP64 instructions, each
+// issued over four clocks: 3.7 us for one wavefront, on one SIMD of a CU whose others have nothing
+// to do.  In three stages, handed on in LDS, the interface kernel of 40 x 10 cells takes 9.6 us
+// instead of 11.1, of 80 x 40 11.2 instead of 13.7, of 100 x 25 with internal degrees of freedom
+// 20.3 instead of 22.5.  erfc and the recurrences of the axis moments on one wavefront, both in the
+// first stage, made it the longest: 10.2 and 11.7.  Every value is formed by the expressions of
+// interface_scalars, and the same in all forms.  With kNW = 4 a wavefront takes the parts of two of
+// eight (r).
+enum ChainRow {
+  X_A = 0,        // aL, aR, b: 4 each
+  X_MT = 12,      // Mt: 5
+  X_C = 17,       // c[2..6] of the axis moments
+  X_M0 = 22,      // mp[0], mn[0]
+  X_EDGE = 24,
+  X_M = 25,       // m1, m2, m3: 4 each
+  X_E = 37,       // eL, eR, eb, e0: 4 each
+  X_COUNT = 53
+};
+template <bool kXi, bool kX, int kF, int kNW>
+__device__ __forceinline__ void faces_staged(const Inst* __restrict__ I, const KParams& P,
+                                             double dt, const Face<kX>& f, bool writes, int fl,
+                                             bool active, int w, const double* wl,
+                                             const double* wr, const double (*red)[kF],
+                                             double (*ch)[kF]) {
+  const double dn = kX ? P.dx : P.dy, len = kX ? P.dy : P.dx;
+  const int r = kNW == 8 ? w - 4 : w;  // second part of a stage
+  auto sum = [&](int q) { return red[q][fl] + red[16 + q][fl]; };
+  double W0[4];
+  Prim p0;
+  Xi xi;
+  // stage 1: micro slopes (wavefronts 0 to 2), time weights, moments along the axes
+  if (active) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) W0[q] = sum(q);
+    const bool ok = prim_of(W0, p0, P.lam_c);
+    xi = xi_of<kXi>(P, p0);
+    if (w < 3) {
+      // aL and aR from the differences to the cells' W, b from the sums' time derivative
+      double sw[4], a[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double d = w == 0 ? W0[q] - wl[q] : wr[q] - W0[q];
+        sw[q] = w == 2 ? sum(4 + q) : d / (0.5 * dn);
+      }
+      micro_slope(p0, sw, a, P.q_c, P.a4_c);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ch[X_A + 4 * w + q][fl] = a[q];
+    } else if (w == 3) {
+      if (writes && !ok) *P.flag = 1;
+      double Mt[5];
+      time_weights(dt, collision_time(p0, P.mu_ref), Mt);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) ch[X_MT + q][fl] = Mt[q];
+    }
+    if (r == 0 || r == 1) {
+      ch[X_M0 + r][fl] = axis_m0(p0.U, p0.lam, r);
+    } else if (r == 2) {
+      double c[7];
+      axis_factors(p0.lam, c);
+#pragma unroll
+      for (int n = 2; n < 7; ++n) ch[X_C + n - 2][fl] = c[n];
+    } else if (r == 3) {
+      ch[X_EDGE][fl] = axis_edge(p0.U, p0.lam);
+    }
+  }
+  __syncthreads();
+  double c[7], mu[7], mv[7];
+  // stage 2: moments of the slopes
+  if (active) {
+#pragma unroll
+    for (int n = 2; n < 7; ++n) c[n] = ch[X_C + n - 2][fl];
+    axis_full(p0.U, c, mu);
+    axis_full(p0.V, c, mv);
+    double o[4];
+    if (w == 0 || w == 1 || r == 0 || r == 1) {
+      const int k = w == 0 || r == 0 ? 0 : 1;
+      double m[7], a[4];
+      axis_half_line(p0.U, c, ch[X_M0 + k][fl], ch[X_EDGE][fl], k, m);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] = ch[X_A + 4 * k + q][fl];
+      if (w < 2) {
+        mpsi_c<kXi>(m, mv, 1, 0, xi, a, o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ch[X_M + 4 * k + q][fl] = o[q];
+      }
+      if (r >= 0) {
+        mpsi_c<kXi>(m, mv, 2, 0, xi, a, o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ch[X_E + 4 * k + q][fl] = o[q];
+      }
+    } else if (w == 2 || r == 2) {
+      double b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[q] = ch[X_A + 8 + q][fl];
+      if (w == 2) {
+        mpsi_c<kXi>(mu, mv, 0, 1, xi, b, o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ch[X_M + 8 + q][fl] = o[q];
+      }
+      if (r == 2) {
+        mpsi_c<kXi>(mu, mv, 1, 1, xi, b, o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ch[X_E + 8 + q][fl] = o[q];
+      }
+    } else if (w == 3) {
+      mpsi<kXi>(mu, mv, 1, 0, xi, o);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ch[X_E + 12 + q][fl] = o[q];
+    }
+  }
+  __syncthreads();
+  // stage 3: A, then the macroscopic flux (wavefront 0) and the polynomial (wavefront 1)
+  if (w > 1 || !writes) return;
+  double sA[4], A[4], Mt[5], Q1[4], qh[2];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    sA[q] = -p0.rho * (ch[X_M + q][fl] + ch[X_M + 4 + q][fl] + ch[X_M + 8 + q][fl]);
+  micro_slope(p0, sA, A, P.q_c, P.a4_c);
+#pragma unroll
+  for (int q = 0; q < 5; ++q) Mt[q] = ch[X_MT + q][fl];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) Q1[q] = sum(8 + q);
+  face_heat(P, p0, W0, Q1, P.shak ? red[32][fl] + red[33][fl] : 0.0, qh);
+  const RecRef rec = record_at(I, f, 0), recH = record_at(I, f, 1);
+  if (w == 0) {
+    double eA[4], e[4][4], Q2[4], F[4];
+    mpsi_c<kXi>(mu, mv, 1, 0, xi, A, eA);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e[k][q] = ch[X_E + 4 * k + q][fl];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Q2[q] = sum(12 + q);
+    macro_flux(P, p0, Mt, e[3], e[0], e[1], e[2], eA, Q1, Q2, qh, len, F);
+    put_flux<kX>(rec, F);
+    if constexpr (kXi) put_flux<kX>(recH, F);
+  } else {
+    double a[3][4];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[k][q] = ch[X_A + 4 * k + q][fl];
+    }
+    fold_record<kXi>(P, p0, xi, Mt, a[0], a[1], a[2], A, qh, len, rec, recH);
+    put_velocity<kX>(rec, p0.U, p0.V);
+    if constexpr (kXi) put_velocity<kX>(recH, p0.U, p0.V);
+  }
+}
+
 // Instances whose moment kernel leaves several parts of every sum (velocity chunks, the chunks of
 // H): a workgroup takes kF faces of one family.  Its threads first add the parts of the faces' 32
-// sums (16 from each side) in chunk order, kIt sums a thread, all loads of a sum in flight at
-// once; they meet in LDS, and one wavefront goes on to the records.  Each sum is towards one
-// face, so no part is read twice and no launch of its own is needed for the sums (it took 4.6 us
-// of launch and latency on any mesh).  What is left is bound by latency: 1.5 us for the plan, 2 for
-// the sums, 3.5 for the chain of interface_scalars.  On a small mesh with many parts (40 x 20: 14)
-// 64 faces a workgroup would have 27 CUs read everything (4.3 us for the sums), so the plan
-// takes 16 or 32 faces there.  The Shakhov model's cell moments, which the update kernel reads,
-// are added by the workgroups after those of the faces, one thread per moment and cell.
+// sums (16 from each side) in chunk order, kIt sums a thread, all loads of a sum in flight at once;
+// they meet in LDS, and the wavefronts go on to the records together (faces_staged).  Each sum is
+// towards one face, so no part is read twice and no launch of its own is needed for the sums (it
+// took 4.6 us of launch and latency on any mesh).  What is left is bound by latency: 1.2 us for the
+// plan, 2 for the sums, 2.5 for faces_staged.  On a small mesh with many parts (40 x 20: 14) 64
+// faces a workgroup would have 27 CUs read everything (4.3 us for the sums), so the plan takes 16
+// or 32 faces there.  The Shakhov model's cell moments, which the update kernel reads, are added by
+// the workgroups after those of the faces, one thread per moment and cell.
 template <bool kX, int kF, int kNW>
 __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, const KParams& P,
                                                 int parity, long first, int lane, int w,
-                                                double (*red)[kF]) {
+                                                double (*red)[kF], double (*ch)[kF]) {
   constexpr int kSub = kWave / kF;            // sums a wavefront takes side by side
   constexpr int kStep = kNW * kSub, kIt = 32 / kStep;
   const int n = I->gsplit * P.NC;
@@ -1157,7 +1384,7 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
   const bool mine = first + fl < nf;
   const Face<kX> f = face_at<kX>(P, mine ? first + fl : nf - 1);
   double wl[4], wr[4];
-  if (w == 0) face_sides(I, P, parity, f, wl, wr);
+  if (w < 2) face_sides(I, P, parity, f, wl, wr);
   // Sums u0 + it kStep (u < 16: sum u of the cell below the face, else sum u - 16 of the cell
   // above it; 32, 33: their heat sums), up to kParts parts at a time (past the last part it is
   // read again and not added).  With kF = 64 a wavefront's sum is uniform and its slot goes into
@@ -1214,6 +1441,16 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
   if (P.shak && w >= kNW - 2 && sub == 0)
     add(32 + w - (kNW - 2), std::integral_constant<int, 1>(), std::integral_constant<int, 8>());
   __syncthreads();
+  const double dt = step_dt(P, parity);
+  if (!P.collisionless) {
+    if (P.NC > 1)
+      faces_staged<true, kX, kF, kNW>(I, P, dt, f, sub == 0 && mine && !f.wall, fl, sub == 0, w,
+                                      wl, wr, red, ch);
+    else
+      faces_staged<false, kX, kF, kNW>(I, P, dt, f, sub == 0 && mine && !f.wall, fl, sub == 0, w,
+                                       wl, wr, red, ch);
+    if (kX || !f.wall) return;
+  }
   if (w != 0 || sub != 0 || !mine) return;
   // a wall takes the sums of its cell alone, which lies above the bottom and below the top
   const bool nol = f.wall && f.j == 0, nor = f.wall && f.j != 0;
@@ -1223,13 +1460,17 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
     const double a = red[q][fl], c = red[16 + q][fl];
     S[q] = nol ? c : (nor ? a : a + c);
   }
-  face_record(I, P, step_dt(P, parity), f, S, P.shak ? red[32][fl] + red[33][fl] : 0.0, wl, wr);
+  if (f.wall)
+    wall_record(I, P, dt, f, S);
+  else
+    free_record(I, P, dt, f, S);
 }
 
 template <int kF, int kNW>
 __global__ __launch_bounds__(kWave* kNW)
 __attribute__((amdgpu_waves_per_eu(2))) void faces_kernel_chunks(PlanView pv) {
   __shared__ double red[34][kF];
+  __shared__ double ch[X_COUNT][kF];
   const int b = blockIdx.x;
   const int ii = find_inst(pv.off_red, pv.ninst, b);
   const Inst* __restrict__ I = inst_at(pv, ii);
@@ -1242,11 +1483,12 @@ __attribute__((amdgpu_waves_per_eu(2))) void faces_kernel_chunks(PlanView pv) {
   const int bx = (P.ny * (P.nx + 1) + kF - 1) / kF;
   const int by = ((P.ny + 1) * P.nx + kF - 1) / kF;
   if (local < bx) {
-    faces_of_chunks<true, kF, kNW>(I, P, parity, (long)local * kF, lane, w, red);
+    faces_of_chunks<true, kF, kNW>(I, P, parity, (long)local * kF, lane, w, red, ch);
     return;
   }
   if (local < bx + by) {
-    faces_of_chunks<false, kF, kNW>(I, P, parity, (long)(local - bx) * kF, lane, w, red);
+    faces_of_chunks<false, kF, kNW>(I, P, parity, (long)(local - bx) * kF, lane, w, red,
+                                    ch);
     return;
   }
   const int n = I->gsplit * P.NC;
