@@ -844,7 +844,7 @@ struct RecRef {
   }
 };
 
-__device__ __forceinline__ void fold_shakhov(RecRef rec, const Prim& p0,
+__device__ __forceinline__ void fold_shakhov(double* e, const Prim& p0,
                                              const double* q, double km) {
   const double lam = p0.lam, U = p0.U, V = p0.V;
   const double Q0 = q[0] * U + q[1] * V;
@@ -854,11 +854,11 @@ __device__ __forceinline__ void fold_shakhov(RecRef rec, const Prim& p0,
                        -l4 * Q0,          -l4 * U * q[0],          -l4 * (V * q[0] + U * q[1]),
                        -l4 * V * q[1],    l4 * q[0],               l4 * q[1]};
 #pragma unroll
-  for (int n = 0; n < 9; ++n) rec[R_E + n] = fma(km, d[n], rec[R_E + n]);
-  rec[R_ER + 0] = fma(km, d[1], rec[R_ER + 0]);
-  rec[R_ER + 1] = fma(km, d[4], rec[R_ER + 1]);
-  rec[R_ER + 2] = fma(km, d[5], rec[R_ER + 2]);
-  rec[R_ER + 3] = fma(km, d[7], rec[R_ER + 3]);
+  for (int n = 0; n < 9; ++n) e[n] = fma(km, d[n], e[n]);
+  e[9] = fma(km, d[1], e[9]);
+  e[10] = fma(km, d[4], e[10]);
+  e[11] = fma(km, d[5], e[11]);
+  e[12] = fma(km, d[7], e[12]);
 }
 
 // A face of a collisionless gas: free transport alone.
@@ -914,69 +914,66 @@ __device__ __forceinline__ void macro_flux(const KParams& P, const Prim& p0, con
   }
 }
 
-// The folded polynomial of the equilibrium part of the distribution flux, and what else of the
-// record does not depend on the macroscopic flux.
+// The folded polynomial of the equilibrium part of the distribution flux of G, or of H (kXi), and
+// what else of the record does not depend on the macroscopic flux.  It is formed in registers and
+// stored once: stored and read back to be folded further, the two records of a face took 7 us of
+// the interface kernel of 100 x 25 cells, and 3 with the Shakhov model (130 x 37). Averaged over
+// xi, the energy term c_4 psi_4 of a slope c contributes c_4 (un^2 + ut^2 + s)/2 to the polynomial
+// of G with s = <|xi|^2> = x2, and to that of H, whose Maxwellian is x2 times that of G, with s =
+// <|xi|^4>/<|xi|^2> = x4/x2: the constant shifts e0, e1 and e2 by c_4 s/2.
 template <bool kXi>
 __device__ __forceinline__ void fold_record(const KParams& P, const Prim& p0, const Xi& xi,
                                             const double* Mt, const double* aL,
                                             const double* aR, const double* b,
                                             const double* A, const double* qh, double len,
-                                            RecRef rec, RecRef recH) {
-  rec[R_E + 0] = Mt[0] + Mt[2] * A[0];
-  rec[R_E + 1] = Mt[1] * aL[0] + Mt[2] * A[1];
-  rec[R_E + 2] = Mt[1] * b[0] + Mt[2] * A[2];
-  rec[R_E + 3] = Mt[2] * A[3];
-  rec[R_E + 4] = Mt[1] * aL[1];
-  rec[R_E + 5] = Mt[1] * (aL[2] + b[1]);
-  rec[R_E + 6] = Mt[1] * b[2];
-  rec[R_E + 7] = Mt[1] * aL[3];
-  rec[R_E + 8] = Mt[1] * b[3];
-  rec[R_ER + 0] = Mt[1] * aR[0] + Mt[2] * A[1];
-  rec[R_ER + 1] = Mt[1] * aR[1];
-  rec[R_ER + 2] = Mt[1] * (aR[2] + b[1]);
-  rec[R_ER + 3] = Mt[1] * aR[3];
-  if (P.shak) fold_shakhov(rec, p0, qh, Mt[0] * P.pr_c * p0.lam * p0.lam / p0.rho);
-  rec[R_GC] = len * p0.rho * p0.lam / kPi;
+                                            bool h, RecRef rec) {
+  double e[13] = {Mt[0] + Mt[2] * A[0],
+                  Mt[1] * aL[0] + Mt[2] * A[1],
+                  Mt[1] * b[0] + Mt[2] * A[2],
+                  Mt[2] * A[3],
+                  Mt[1] * aL[1],
+                  Mt[1] * (aL[2] + b[1]),
+                  Mt[1] * b[2],
+                  Mt[1] * aL[3],
+                  Mt[1] * b[3],
+                  // R_ER
+                  Mt[1] * aR[0] + Mt[2] * A[1],
+                  Mt[1] * aR[1],
+                  Mt[1] * (aR[2] + b[1]),
+                  Mt[1] * aR[3]};
+  if (P.shak) fold_shakhov(e, p0, qh, Mt[0] * P.pr_c * p0.lam * p0.lam / p0.rho);
+  double gc = len * p0.rho * p0.lam / kPi;
+  if constexpr (kXi) {
+    const double sc = h ? 0.5 * xi.x4 / xi.x2 : 0.5 * xi.x2;
+    e[0] = fma(sc, e[3], e[0]);
+    e[1] = fma(sc, e[7], e[1]);
+    e[2] = fma(sc, e[8], e[2]);
+    e[9] = fma(sc, e[12], e[9]);
+    if (h) gc *= xi.x2;
+  }
+#pragma unroll
+  for (int q = 0; q < 13; ++q) rec[R_E + q] = e[q];
+  rec[R_GC] = gc;
   rec[R_LAM] = p0.lam;
   rec[R_M4] = len * Mt[3];
   rec[R_M5] = len * Mt[4];
   rec[R_KIND] = K_INTERIOR;
-  if constexpr (kXi) {
-#pragma unroll
-    for (int q = R_GC; q < kRec; ++q) recH[q] = rec[q];
-    recH[R_GC] = rec[R_GC] * xi.x2;
-    const double sh = 0.5 * xi.x4 / xi.x2, sg = 0.5 * xi.x2;
-    const double e3 = rec[R_E + 3], e7 = rec[R_E + 7], e8 = rec[R_E + 8];
-    const double e7r = rec[R_ER + 3];
-    recH[R_E + 0] = fma(sh, e3, rec[R_E + 0]);
-    recH[R_E + 1] = fma(sh, e7, rec[R_E + 1]);
-    recH[R_E + 2] = fma(sh, e8, rec[R_E + 2]);
-    recH[R_ER + 0] = fma(sh, e7r, rec[R_ER + 0]);
-    rec[R_E + 0] = fma(sg, e3, rec[R_E + 0]);
-    rec[R_E + 1] = fma(sg, e7, rec[R_E + 1]);
-    rec[R_E + 2] = fma(sg, e8, rec[R_E + 2]);
-    rec[R_ER + 0] = fma(sg, e7r, rec[R_ER + 0]);
-  }
 }
 
-// S2-S5 at one interior interface, local frame.  S = [W0, Wt, Q1, Q2].  Writes the local
-// macroscopic flux to F and the folded coefficients of the distribution flux to rec; with
-// internal degrees of freedom (kXi) also those of H to recH.  Averaged over xi, the energy
-// term c_4 psi_4 of a slope c contributes c_4 (un^2 + ut^2 + s)/2 to the polynomial of G with
-// s = <|xi|^2> = x2, and to that of H, whose Maxwellian is x2 times that of G, with
-// s = <|xi|^4>/<|xi|^2> = x4/x2: the constant shifts e0, e1 and e2 by c_4 s/2.
-template <bool kXi>
-__device__ void interface_scalars(const KParams& P, double dt, const double* S, const double* WL,
-                                  const double* WR, double dn, double len, double* F,
-                                  RecRef rec, RecRef recH,
-                                  double& U0, double& V0, double T3 = 0.0) {
+// S2-S5 at one interior interface, local frame (internal degrees of freedom: faces_staged).
+// S = [W0, Wt, Q1, Q2].  Writes the local macroscopic flux to F, the folded coefficients of the
+// distribution flux to rec.
+__device__ __forceinline__ void interface_scalars(const KParams& P, double dt, const double* S,
+                                                  const double* WL, const double* WR, double dn,
+                                                  double len, double* F, RecRef rec, double& U0,
+                                                  double& V0, double T3) {
   const double* W0 = S;
   const double* Wt = S + 4;
   const double* Q1 = S + 8;
   const double* Q2 = S + 12;
   Prim p0;
   if (!prim_of(W0, p0, P.lam_c)) *P.flag = 1;
-  const Xi xi = xi_of<kXi>(P, p0);
+  const Xi xi{0.0, 0.0};
   double Mt[5];
   time_weights(dt, collision_time(p0, P.mu_ref), Mt);
   double swL[4], swR[4], aL[4], aR[4], b[4], A[4];
@@ -996,21 +993,21 @@ __device__ void interface_scalars(const KParams& P, double dt, const double* S, 
   axis_half_line(p0.U, c, axis_m0(p0.U, p0.lam, 1), edge, 1, mn);
   axis_full(p0.V, c, mv);
   double m1[4], m2[4], m3[4], sA[4];
-  mpsi_c<kXi>(mp, mv, 1, 0, xi, aL, m1);
-  mpsi_c<kXi>(mn, mv, 1, 0, xi, aR, m2);
-  mpsi_c<kXi>(mu, mv, 0, 1, xi, b, m3);
+  mpsi_c<false>(mp, mv, 1, 0, xi, aL, m1);
+  mpsi_c<false>(mn, mv, 1, 0, xi, aR, m2);
+  mpsi_c<false>(mu, mv, 0, 1, xi, b, m3);
 #pragma unroll
   for (int q = 0; q < 4; ++q) sA[q] = -p0.rho * (m1[q] + m2[q] + m3[q]);
   micro_slope(p0, sA, A, P.q_c, P.a4_c);
   double e0[4], eL[4], eR[4], eb[4], eA[4], qh[2];
-  mpsi<kXi>(mu, mv, 1, 0, xi, e0);
-  mpsi_c<kXi>(mp, mv, 2, 0, xi, aL, eL);
-  mpsi_c<kXi>(mn, mv, 2, 0, xi, aR, eR);
-  mpsi_c<kXi>(mu, mv, 1, 1, xi, b, eb);
-  mpsi_c<kXi>(mu, mv, 1, 0, xi, A, eA);
+  mpsi<false>(mu, mv, 1, 0, xi, e0);
+  mpsi_c<false>(mp, mv, 2, 0, xi, aL, eL);
+  mpsi_c<false>(mn, mv, 2, 0, xi, aR, eR);
+  mpsi_c<false>(mu, mv, 1, 1, xi, b, eb);
+  mpsi_c<false>(mu, mv, 1, 0, xi, A, eA);
   face_heat(P, p0, W0, Q1, T3, qh);
   macro_flux(P, p0, Mt, e0, eL, eR, eb, eA, Q1, Q2, qh, len, F);
-  fold_record<kXi>(P, p0, xi, Mt, aL, aR, b, A, qh, len, rec, recH);
+  fold_record<false>(P, p0, xi, Mt, aL, aR, b, A, qh, len, false, rec);
   U0 = p0.U;
   V0 = p0.V;
 }
@@ -1141,8 +1138,9 @@ __device__ __forceinline__ void free_record(const Inst* __restrict__ I, const KP
   }
 }
 
-// The record(s) of one face from its sums S (both sides added; a wall: those of its cell) and
-// heat sum T3.
+// The record of one face from its sums S (both sides added; a wall: those of its cell) and heat
+// sum T3, for solvers with one part of every sum (which have no internal degrees of freedom: H
+// makes a second part).
 template <bool kX>
 __device__ __forceinline__ void face_record(const Inst* __restrict__ I, const KParams& P,
                                             double dt, const Face<kX>& f, const double* S,
@@ -1155,18 +1153,11 @@ __device__ __forceinline__ void face_record(const Inst* __restrict__ I, const KP
     free_record(I, P, dt, f, S);
     return;
   }
-  const RecRef rec = record_at(I, f, 0), recH = record_at(I, f, 1);
+  const RecRef rec = record_at(I, f, 0);
   double F[4], U0, V0;
-  const double dn = f.x ? P.dx : P.dy, len = f.x ? P.dy : P.dx;
-  if (P.NC > 1)
-    interface_scalars<true>(P, dt, S, wl, wr, dn, len, F, rec, recH, U0, V0);
-  else
-    interface_scalars<false>(P, dt, S, wl, wr, dn, len, F, rec, recH, U0, V0, T3);
-  for (int c = 0; c < P.NC; ++c) {
-    const RecRef r = c ? recH : rec;
-    put_flux<kX>(r, F);
-    put_velocity<kX>(r, U0, V0);
-  }
+  interface_scalars(P, dt, S, wl, wr, kX ? P.dx : P.dy, kX ? P.dy : P.dx, F, rec, U0, V0, T3);
+  put_flux<kX>(rec, F);
+  put_velocity<kX>(rec, U0, V0);
 }
 
 // The update kernel of this step takes the max rate of W^{n+1} into the other slot.
@@ -1211,15 +1202,14 @@ __global__ __launch_bounds__(256) void faces_kernel(PlanView pv) {
     face_direct<false>(I, P, parity, (long)(local - bx) * 256 + threadIdx.x);
 }
 
-// The chain of interface_scalars for kF faces of one family, with its independent parts on the
-// kNW wavefronts of a workgroup (lanes: faces).  The chain is about 2000 FP64 instructions, each
-// issued over four clocks: 3.7 us for one wavefront, on one SIMD of a CU whose others have nothing
-// to do.  In three stages, handed on in LDS, the interface kernel of 40 x 10 cells takes 9.6 us
-// instead of 11.1, of 80 x 40 11.2 instead of 13.7, of 100 x 25 with internal degrees of freedom
-// 20.3 instead of 22.5.  erfc and the recurrences of the axis moments on one wavefront, both in the
-// first stage, made it the longest: 10.2 and 11.7.  Every value is formed by the expressions of
-// interface_scalars, and the same in all forms.  With kNW = 4 a wavefront takes the parts of two of
-// eight (r).
+// The chain of interface_scalars for kF faces of one family, with its independent parts on the kNW
+// wavefronts of a workgroup (lanes: faces).  The chain is about 2000 FP64 instructions, each issued
+// over four clocks: 3.7 us for one wavefront, on one SIMD of a CU whose others have nothing to do.
+// In three stages, handed on in LDS, the interface kernel of 40 x 10 cells takes 9.6 us instead of
+// 11.1, of 80 x 40 11.2 instead of 13.7.  erfc and the recurrences of the axis moments on one
+// wavefront, both in the first stage, made it the longest: 10.2 and 11.7.  Every value is formed by
+// the expressions of interface_scalars, and the same in all forms.  With kNW = 4 a wavefront takes
+// the parts of two of eight (r).
 enum ChainRow {
   X_A = 0,        // aL, aR, b: 4 each
   X_MT = 12,      // Mt: 5
@@ -1323,8 +1313,8 @@ __device__ __forceinline__ void faces_staged(const Inst* __restrict__ I, const K
     }
   }
   __syncthreads();
-  // stage 3: A, then the macroscopic flux (wavefront 0) and the polynomial (wavefront 1)
-  if (w > 1 || !writes) return;
+  // stage 3: A, then the macroscopic flux (wavefront 0) and the polynomial of G (1) and H (2)
+  if (w > (kXi ? 2 : 1) || !writes) return;
   double sA[4], A[4], Mt[5], Q1[4], qh[2];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -1335,7 +1325,6 @@ __device__ __forceinline__ void faces_staged(const Inst* __restrict__ I, const K
 #pragma unroll
   for (int q = 0; q < 4; ++q) Q1[q] = sum(8 + q);
   face_heat(P, p0, W0, Q1, P.shak ? red[32][fl] + red[33][fl] : 0.0, qh);
-  const RecRef rec = record_at(I, f, 0), recH = record_at(I, f, 1);
   if (w == 0) {
     double eA[4], e[4][4], Q2[4], F[4];
     mpsi_c<kXi>(mu, mv, 1, 0, xi, A, eA);
@@ -1347,8 +1336,8 @@ __device__ __forceinline__ void faces_staged(const Inst* __restrict__ I, const K
 #pragma unroll
     for (int q = 0; q < 4; ++q) Q2[q] = sum(12 + q);
     macro_flux(P, p0, Mt, e[3], e[0], e[1], e[2], eA, Q1, Q2, qh, len, F);
-    put_flux<kX>(rec, F);
-    if constexpr (kXi) put_flux<kX>(recH, F);
+#pragma unroll
+    for (int k = 0; k < (kXi ? 2 : 1); ++k) put_flux<kX>(record_at(I, f, k), F);
   } else {
     double a[3][4];
 #pragma unroll
@@ -1356,9 +1345,9 @@ __device__ __forceinline__ void faces_staged(const Inst* __restrict__ I, const K
 #pragma unroll
       for (int q = 0; q < 4; ++q) a[k][q] = ch[X_A + 4 * k + q][fl];
     }
-    fold_record<kXi>(P, p0, xi, Mt, a[0], a[1], a[2], A, qh, len, rec, recH);
+    const RecRef rec = record_at(I, f, w - 1);
+    fold_record<kXi>(P, p0, xi, Mt, a[0], a[1], a[2], A, qh, len, w == 2, rec);
     put_velocity<kX>(rec, p0.U, p0.V);
-    if constexpr (kXi) put_velocity<kX>(recH, p0.U, p0.V);
   }
 }
 
