@@ -1,7 +1,8 @@
 """Build the gfx950 library libugks.so in-tree with hipcc.
 
 All HIP code is compiled with packed FP32 arithmetic disabled
-(-Xclang -target-feature -Xclang -packed-fp32-ops).
+(-Xclang -target-feature -Xclang -packed-fp32-ops), and with the first kernel arguments
+preloaded into scalar registers (-amdgpu-kernarg-preload-count).
 """
 import os
 import subprocess
@@ -15,6 +16,7 @@ SOURCES = ["ugks_kernels.hip", "ugks_capi.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=8",
          "-I" + os.path.join(ROOT, "include")]
 
 

@@ -394,17 +394,18 @@ __device__ __forceinline__ int first_block(const int* off_generic, int ii) {
   return ((int_cptr)off_generic)[ii];
 }
 
-// The plan is read-only for the whole launch.
-__device__ __forceinline__ const Inst* inst_at(const PlanView& pv, int ii) {
-  return pv.inst + ii;
-}
+// The kernels of a step take the members of the plan view that they need one by one (inst, the
+// offsets of their workgroups off, ninst, step): such arguments come in scalar registers with the
+// wavefront (-amdgpu-kernarg-preload-count), where a structure is read from memory, 0.4 us at the
+// start of every launch (a step of 40 x 10 cells 28.2 -> 27.6 us).  The plan is read-only for the
+// whole launch.
 
 // ================================================================== kernels
 // Discrete Maxwellian of each cell's W (initial state), one thread per plane value; the
 // planes of H hold dof/(2 lambda) times those of G.
 template <typename S>
 __global__ __launch_bounds__(256) void init_kernel(PlanView pv) {
-  const Inst* __restrict__ I = inst_at(pv, 0);
+  const Inst* __restrict__ I = pv.inst;
   const KParams P = I->P;
   UGKS_GLOBAL S* f = static_cast<UGKS_GLOBAL S*>(I->f[I->cur]);
   const UGKS_GLOBAL double* W = I->W[I->cur];
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(256) void init_kernel(PlanView pv) {
 // step that failed to write one of these values would leave a NaN in the state.
 template <typename S>
 __global__ __launch_bounds__(256) void poison_kernel(PlanView pv) {
-  const Inst* __restrict__ I = inst_at(pv, 0);
+  const Inst* __restrict__ I = pv.inst;
   const KParams P = I->P;
   const int nxt = (I->cur + pv.step + 1) & 1;
   UGKS_GLOBAL S* f = static_cast<UGKS_GLOBAL S*>(I->f[nxt]);
@@ -496,13 +497,15 @@ __host__ __device__ __forceinline__ int ghost_blocks(int nx) {
   return (2 * kHalo * nx + kGhostThreads - 1) / kGhostThreads;  // of one plane
 }
 template <typename S>
-__global__ __launch_bounds__(kGhostThreads) void ghost_kernel(PlanView pv) {
+__global__ __launch_bounds__(kGhostThreads) void ghost_kernel(const Inst* inst,
+                                                              const int* off, int ninst,
+                                                              int step) {
   const int b = blockIdx.x;
-  const int ii = find_inst(pv.off_ghost, pv.ninst, b);
-  const Inst* __restrict__ I = inst_at(pv, ii);
+  const int ii = find_inst(off, ninst, b);
+  const Inst* __restrict__ I = inst + ii;
   const KParams P = I->P;
-  UGKS_GLOBAL S* f = static_cast<UGKS_GLOBAL S*>(I->f[(I->cur + pv.step) & 1]);
-  const int local = b - first_block(pv.off_ghost, ii);
+  UGKS_GLOBAL S* f = static_cast<UGKS_GLOBAL S*>(I->f[(I->cur + step) & 1]);
+  const int local = b - first_block(off, ii);
   const int bpp = ghost_blocks(P.nx);
   const int p = local / bpp;
   const int e = (local - p * bpp) * kGhostThreads + threadIdx.x;
@@ -526,24 +529,25 @@ __global__ __launch_bounds__(kGhostThreads) void ghost_kernel(PlanView pv) {
 // of the reconstruction (c2h = (un^2 + ut^2)/2) and, per cell, eight raw moments of f for
 // the heat fluxes.
 template <typename S, bool kShak>
-__global__ __launch_bounds__(kWave* kQuads) void sums_kernel(PlanView pv) {
+__global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, const int* off,
+                                                               int ninst, int step) {
   constexpr int kR = kShak ? 17 : 16;
   __shared__ double red[4][kR][kWave];
   __shared__ double cellred[kShak ? 3 : 1][8][kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ii = find_inst(pv.off_sums, pv.ninst, blockIdx.x);
-  const Inst* __restrict__ I = inst_at(pv, ii);
+  const int ii = find_inst(off, ninst, blockIdx.x);
+  const Inst* __restrict__ I = inst + ii;
   const KParams P = I->P;
   const int G = I->gsplit;
   const int ntx = (P.nx + kTileS - 1) / kTileS;
-  const int b = xcd_block(blockIdx.x - first_block(pv.off_sums, ii), ntx * P.ny * G * P.NC);
+  const int b = xcd_block(blockIdx.x - first_block(off, ii), ntx * P.ny * G * P.NC);
   if (b < 0) return;
   int t, gg, j;
   cell_block(b, P.ny, ntx, t, gg, j);
   const bool hpart = gg >= G;  // planes of H
   const int g = hpart ? gg - G : gg;
-  const UGKS_GLOBAL S* f = static_cast<const UGKS_GLOBAL S*>(I->f[(I->cur + pv.step) & 1]) +
+  const UGKS_GLOBAL S* f = static_cast<const UGKS_GLOBAL S*>(I->f[(I->cur + step) & 1]) +
                            (hpart ? (long long)P.NV * P.PS : 0ll);
   UGKS_GLOBAL double* hs = I->hs + (size_t)gg * P.nslot * (size_t)P.ncs;
   const int i = t * kTileS - 1 + lane;
@@ -1187,13 +1191,14 @@ __device__ __forceinline__ void face_direct(const Inst* __restrict__ I, const KP
   face_sides(I, P, parity, f, wl, wr);
   face_record(I, P, step_dt(P, parity), f, S, T3, wl, wr);
 }
-__global__ __launch_bounds__(256) void faces_kernel(PlanView pv) {
+__global__ __launch_bounds__(256) void faces_kernel(const Inst* inst, const int* off,
+                                                    int ninst, int step) {
   const int b = blockIdx.x;
-  const int ii = find_inst(pv.off_face, pv.ninst, b);
-  const Inst* __restrict__ I = inst_at(pv, ii);
+  const int ii = find_inst(off, ninst, b);
+  const Inst* __restrict__ I = inst + ii;
   const KParams P = I->P;
-  const int parity = (I->cur + pv.step) & 1;
-  const int local = b - first_block(pv.off_face, ii);
+  const int parity = (I->cur + step) & 1;
+  const int local = b - first_block(off, ii);
   if (local == 0 && threadIdx.x == 0) clear_rate(P, parity);
   const int bx = (P.ny * (P.nx + 1) + 255) / 256;
   if (local < bx)
@@ -1457,17 +1462,19 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
 
 template <int kF, int kNW>
 __global__ __launch_bounds__(kWave* kNW)
-__attribute__((amdgpu_waves_per_eu(2))) void faces_kernel_chunks(PlanView pv) {
+__attribute__((amdgpu_waves_per_eu(2))) void faces_kernel_chunks(const Inst* inst,
+                                                                  const int* off, int ninst,
+                                                                  int step) {
   __shared__ double red[34][kF];
   __shared__ double ch[X_COUNT][kF];
   const int b = blockIdx.x;
-  const int ii = find_inst(pv.off_red, pv.ninst, b);
-  const Inst* __restrict__ I = inst_at(pv, ii);
+  const int ii = find_inst(off, ninst, b);
+  const Inst* __restrict__ I = inst + ii;
   const KParams P = I->P;
-  const int parity = (I->cur + pv.step) & 1;
+  const int parity = (I->cur + step) & 1;
   const int lane = threadIdx.x & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int local = b - first_block(pv.off_red, ii);
+  const int local = b - first_block(off, ii);
   if (local == 0 && threadIdx.x == 0) clear_rate(P, parity);
   const int bx = (P.ny * (P.nx + 1) + kF - 1) / kF;
   const int by = ((P.ny + 1) * P.nx + kF - 1) / kF;
@@ -2025,7 +2032,7 @@ __device__ __forceinline__ void ghost_fill_quadrant(const KParams& P, const Pair
 
 // The body of the update kernel; kShak: the Shakhov collision model; kNode: chunks by node.
 template <typename S, bool kShak, int kCh, bool kFill = false, bool kNode = false>
-__device__ __forceinline__ void update_body(const PlanView& pv) {
+__device__ __forceinline__ void update_body(const Inst* inst, const int* off, int ninst, int step) {
   typedef S T;  // arithmetic type of the per-velocity work (and of the LDS stage)
   __shared__ PairStage<T> st;
   // Shakhov: (1 - Pr)(lambda^2/rho) q of each lane's cell at t^n and t^{n+1}, per row
@@ -2035,13 +2042,13 @@ __device__ __forceinline__ void update_body(const PlanView& pv) {
   // wavefront w: quadrant q, and c, which of the workgroup's kCh velocity chunks
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q = w & 3, c = w >> 2;
-  const int ii = find_inst(pv.off_upd, pv.ninst, blockIdx.x);
-  const Inst* __restrict__ I = inst_at(pv, ii);
+  const int ii = find_inst(off, ninst, blockIdx.x);
+  const Inst* __restrict__ I = inst + ii;
   const KParams P = I->P;
-  const int parity = (I->cur + pv.step) & 1;
+  const int parity = (I->cur + step) & 1;
   const int G = I->usplit, Gv = P.vsplit;
   const int ntx = (P.nx + kTileU - 1) / kTileU;
-  const int b = xcd_block(blockIdx.x - first_block(pv.off_upd, ii),
+  const int b = xcd_block(blockIdx.x - first_block(off, ii),
                           ntx * ((P.ny + 1) / 2) * G * Gv * P.NC);
   if (b < 0) return;
   int t, gg, pb;
@@ -2400,8 +2407,8 @@ constexpr int kUpdateWaves = sizeof(S) == 8 || kShak ? 2 : 4;
 template <typename S, int kCh>
 __global__ __launch_bounds__(kWave* kQuads* kCh)
 __attribute__((amdgpu_waves_per_eu(kUpdateWaves<S, false>)))
-void update_kernel(PlanView pv) {
-  update_body<S, false, kCh>(pv);
+void update_kernel(const Inst* inst, const int* off, int ninst, int step) {
+  update_body<S, false, kCh>(inst, off, ninst, step);
 }
 
 // The chunks of this form split a quadrant's nodes instead of its u lines (update_by_node).  A
@@ -2410,15 +2417,15 @@ void update_kernel(PlanView pv) {
 template <typename S, int kCh>
 __global__ __launch_bounds__(kWave* kQuads* kCh)
 __attribute__((amdgpu_waves_per_eu(kUpdateWaves<S, false>)))
-void update_kernel_nodes(PlanView pv) {
-  update_body<S, false, kCh, false, true>(pv);
+void update_kernel_nodes(const Inst* inst, const int* off, int ninst, int step) {
+  update_body<S, false, kCh, false, true>(inst, off, ninst, step);
 }
 
 template <typename S, int kCh>
 __global__ __launch_bounds__(kWave* kQuads* kCh)
 __attribute__((amdgpu_waves_per_eu(kUpdateWaves<S, true>)))
-void update_kernel_shakhov(PlanView pv) {
-  update_body<S, true, kCh>(pv);
+void update_kernel_shakhov(const Inst* inst, const int* off, int ninst, int step) {
+  update_body<S, true, kCh>(inst, off, ninst, step);
 }
 
 // The update kernel's fill mode (any collision model: a ghost Maxwellian carries no Shakhov
@@ -2426,8 +2433,8 @@ void update_kernel_shakhov(PlanView pv) {
 template <typename S, int kCh>
 __global__ __launch_bounds__(kWave* kQuads* kCh)
 __attribute__((amdgpu_waves_per_eu(kUpdateWaves<S, false>)))
-void ghost_fill_kernel(PlanView pv) {
-  update_body<S, false, kCh, true>(pv);
+void ghost_fill_kernel(const Inst* inst, const int* off, int ninst, int step) {
+  update_body<S, false, kCh, true>(inst, off, ninst, step);
 }
 
 // ================================================================== host images
@@ -2748,81 +2755,86 @@ hipError_t launch_moments(const double* W, int n, double lam_c, const int* flag,
   return hipGetLastError();
 }
 
-// phase 0 ghosts, 1 moment sums, 2 interface scalars, 3 cell update
 hipError_t launch_ghost_fill(const PlanView& pv, const PlanTotals& t, int fp32, hipStream_t s) {
   if (!t.channel) return hipSuccess;
   const unsigned nt = (unsigned)(kWave * kQuads * t.upd_ch);
+  const Inst* in = pv.inst;
+  const int ni = pv.ninst, st = pv.step;
   if (fp32)
-    ghost_fill_kernel<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+    ghost_fill_kernel<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
   else if (t.upd_ch == 2)
-    ghost_fill_kernel<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+    ghost_fill_kernel<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
   else
-    ghost_fill_kernel<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+    ghost_fill_kernel<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
   return hipGetLastError();
 }
 
+// phase 0 ghosts, 1 moment sums, 2 interface scalars, 3 cell update
 hipError_t launch_phase(const PlanView& pv, const PlanTotals& t, int fp32, int phase,
                         hipStream_t s) {
+  const Inst* in = pv.inst;
+  const int ni = pv.ninst, st = pv.step;
+  constexpr unsigned kSumWg = kWave * kQuads;
   switch (phase) {
     case 0:
       if (t.ghost == 0) return hipSuccess;  // no periodic instance
       if (fp32)
-        ghost_kernel<float><<<(unsigned)t.ghost, kGhostThreads, 0, s>>>(pv);
+        ghost_kernel<float><<<(unsigned)t.ghost, kGhostThreads, 0, s>>>(in, pv.off_ghost, ni, st);
       else
-        ghost_kernel<double><<<(unsigned)t.ghost, kGhostThreads, 0, s>>>(pv);
+        ghost_kernel<double><<<(unsigned)t.ghost, kGhostThreads, 0, s>>>(in, pv.off_ghost, ni, st);
       break;
     case 1:
       if (t.shak) {
         if (fp32)
-          sums_kernel<float, true><<<(unsigned)t.sums, kWave * kQuads, 0, s>>>(pv);
+          sums_kernel<float, true><<<(unsigned)t.sums, kSumWg, 0, s>>>(in, pv.off_sums, ni, st);
         else
-          sums_kernel<double, true><<<(unsigned)t.sums, kWave * kQuads, 0, s>>>(pv);
+          sums_kernel<double, true><<<(unsigned)t.sums, kSumWg, 0, s>>>(in, pv.off_sums, ni, st);
       } else {
         if (fp32)
-          sums_kernel<float, false><<<(unsigned)t.sums, kWave * kQuads, 0, s>>>(pv);
+          sums_kernel<float, false><<<(unsigned)t.sums, kSumWg, 0, s>>>(in, pv.off_sums, ni, st);
         else
-          sums_kernel<double, false><<<(unsigned)t.sums, kWave * kQuads, 0, s>>>(pv);
+          sums_kernel<double, false><<<(unsigned)t.sums, kSumWg, 0, s>>>(in, pv.off_sums, ni, st);
       }
       break;
     case 2:
       if (t.red > 0) {
         if (t.red_faces == 16)
-          faces_kernel_chunks<16, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(pv);
+          faces_kernel_chunks<16, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(in, pv.off_red, ni, st);
         else if (t.red_faces == 32)
-          faces_kernel_chunks<32, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(pv);
+          faces_kernel_chunks<32, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(in, pv.off_red, ni, st);
         else if (t.red_waves == 8)
-          faces_kernel_chunks<64, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(pv);
+          faces_kernel_chunks<64, 8><<<(unsigned)t.red, kWave * 8, 0, s>>>(in, pv.off_red, ni, st);
         else
-          faces_kernel_chunks<64, 4><<<(unsigned)t.red, kWave * 4, 0, s>>>(pv);
+          faces_kernel_chunks<64, 4><<<(unsigned)t.red, kWave * 4, 0, s>>>(in, pv.off_red, ni, st);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
-      if (t.face > 0) faces_kernel<<<(unsigned)t.face, 256, 0, s>>>(pv);
+      if (t.face > 0) faces_kernel<<<(unsigned)t.face, 256, 0, s>>>(in, pv.off_face, ni, st);
       break;
     default: {
       // FP32 storage runs one chunk per workgroup (build_plan never asks for two)
       const unsigned nt = (unsigned)(kWave * kQuads * t.upd_ch);
       if (t.shak) {
         if (fp32)
-          update_kernel_shakhov<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel_shakhov<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
         else if (t.upd_ch == 2)
-          update_kernel_shakhov<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel_shakhov<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
         else
-          update_kernel_shakhov<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel_shakhov<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
       } else if (t.upd_nodes) {
         if (fp32)
-          update_kernel_nodes<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel_nodes<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
         else if (t.upd_ch == 2)
-          update_kernel_nodes<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel_nodes<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
         else
-          update_kernel_nodes<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel_nodes<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
       } else {
         if (fp32)
-          update_kernel<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel<float, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
         else if (t.upd_ch == 2)
-          update_kernel<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel<double, 2><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
         else
-          update_kernel<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(pv);
+          update_kernel<double, 1><<<(unsigned)t.upd, nt, 0, s>>>(in, pv.off_upd, ni, st);
       }
     }
   }
