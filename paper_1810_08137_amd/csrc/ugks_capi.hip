@@ -175,6 +175,24 @@ class PinnedPool {
 };
 PinnedPool g_pinned;
 
+// Hands a block back after work on `stream` that ended with e.  Where that was an error the device
+// may still use the block: it waits again, also where a capture on some other stream refuses
+// ordinary waits (work put into a capture on this one does not run), and a block that cannot be
+// waited for is not handed back.
+void put_block(void* blk, hipError_t e, hipStream_t stream) {
+  if (blk && e != hipSuccess) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool done = (hipStreamIsCapturing(stream, &status) == hipSuccess &&
+                       status != hipStreamCaptureStatusNone) ||
+                      hipStreamSynchronize(stream) == hipSuccess;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!done) return;
+  }
+  g_pinned.put(blk);
+}
+
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int fail(ugks_handle* h, int code, const char* fmt, const char* detail = "") {
@@ -466,14 +484,11 @@ hipError_t move_pieces(const StatePieces& sp, long long first, long long stride)
   // no block goes back while the device may still use it
   for (int b = 0; b < nb; ++b)
     if (ev[b]) {
-      if (e == hipSuccess)
-        e = hipEventSynchronize(ev[b]);
-      else
-        (void)hipStreamSynchronize(h->stream);
+      if (e == hipSuccess) e = hipEventSynchronize(ev[b]);
       (void)hipEventDestroy(ev[b]);
     }
-  g_pinned.put(blk[0]);
-  g_pinned.put(blk[1]);
+  put_block(blk[0], e, h->stream);
+  put_block(blk[1], e, h->stream);
   return e;
 }
 hipError_t move_state(ugks_handle* h, double* host, bool out) {
@@ -904,8 +919,7 @@ int ugks_create(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, const
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) rc = hip_fail(nullptr, e, "initial state");
   }
-  if (rc != UGKS_OK) (void)hipStreamSynchronize(h->stream);  // the block may still be read
-  g_pinned.put(blk);
+  put_block(blk, rc == UGKS_OK ? hipSuccess : e, h->stream);
   if (rc != UGKS_OK) {
     g_pinned.drop_user();
     if (h->owns_ws) (void)hipFree(h->ws);
@@ -985,7 +999,7 @@ int ugks_moments(ugks_handle* h, double* host_out) {
     if (e == hipSuccess) std::memcpy(host_out + 4 * c0, blk + kHead, n * 32);
   }
   const bool bad = *mark != 0;
-  g_pinned.put(blk);
+  put_block(blk, e, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "reading the moments");
   if (bad) return fail(h, UGKS_E_STATE, "invalid state (NaN, rho <= 0 or T <= 0)%s");
   return UGKS_OK;
