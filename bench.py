@@ -26,9 +26,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "c5326a62242a539b8077b7d3c7e63210a9a4cd909cb3df65497a42b7d5afd8f5",
-    "fp64": 1.3388e9,
-    "fp32_store": 0.6993e9,
+    "source_sha256": "8f4732c106abcbc87a269a831a337bb491fa02957559a090989e63ca755a9f4a",
+    "fp64": 1.339e9,
+    "fp32_store": 0.6997e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
     "valu_fp64": 1.0107e8,
 }

@@ -578,7 +578,24 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, c
   for (int r = 0; r < (kShak ? 8 : 1); ++r) cm[r] = 0.0;
   int a0, a1;
   chunk_range(hu.count, g, G, a0, a1);
+  // The wavefronts of a SIMD are issued oldest first, so the later ones fall behind and end alone.
+  // Here a wavefront is issued before those that are a quarter of their lines further on: FP32
+  // storage at 400 x 100 x 40^2 113 -> 109 us, Shakhov at 130 x 37 x 40^2 34.9 -> 33.4.  FP64, which
+  // waits for its loads more than for issue, is slower with it (190 -> 196 us).  (The FP32 form
+  // then takes 151 registers, three waves per SIMD; held to four it spills and takes 117 us.)
+  constexpr bool kEven = sizeof(S) == 4 || kShak;
   for (int a = a0; a < a1; ++a) {
+    if constexpr (kEven) {
+      const int done = 4 * (a - a0);
+      if (done < a1 - a0)
+        __builtin_amdgcn_s_setprio(3);
+      else if (done < 2 * (a1 - a0))
+        __builtin_amdgcn_s_setprio(2);
+      else if (done < 3 * (a1 - a0))
+        __builtin_amdgcn_s_setprio(1);
+      else
+        __builtin_amdgcn_s_setprio(0);
+    }
     const int k = hu.first + a * hu.step;
     const double u = P.uk[k];
     const double wu = P.wk[k] * (u == 0.0 ? 0.5 : 1.0);
