@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -409,9 +410,9 @@ hipEvent_t pool_get(ugks_handle* h) {
 
 // The distribution between the planes of the current f and the caller's canonical host array,
 // in pieces of one pinned block: whole cells, or where one cell is larger than a block a range of
-// its velocities.  The device transposes a piece into (out of) a block while the host copies the
-// one before it; large arrays are copied by several host threads, each on its own pieces and
-// blocks, since one thread's copy is slower than the host link.
+// its velocities.  The device transposes pieces into (out of) some blocks while the host copies
+// others.  Every launch, event and wait is the calling thread's, whatever stream the handle has: a
+// per-thread stream is another one in every other thread.
 struct StatePieces {
   ugks_handle* h;
   double* host;
@@ -420,103 +421,206 @@ struct StatePieces {
   int nvt;            // values of a cell
   int cells, vels;    // of a piece
   long long count;    // pieces
-};
-// Pieces first, first + stride, ...
-hipError_t move_pieces(const StatePieces& sp, long long first, long long stride) {
-  ugks_handle* h = sp.h;
-  void* blk[2] = {g_pinned.get(), nullptr};
-  if (first + stride < sp.count) blk[1] = g_pinned.get();
-  hipEvent_t ev[2] = {};
-  hipError_t e = blk[0] ? hipSetDevice(h->device) : hipErrorOutOfMemory;
-  const int nb = blk[1] ? 2 : 1;
-  for (int b = 0; b < nb && e == hipSuccess; ++b)
-    e = hipEventCreateWithFlags(&ev[b], hipEventDisableTiming);
-  void* f = h->B.f[h->steps & 1];
-  const int fp32 = h->inst.fp32;
-  const long long per_row = (sp.nvt + sp.vels - 1) / sp.vels;
   struct At {
     long long c0;
     int ncell, v0, nvel;
   };
-  auto at = [&](long long p) {
-    const long long c0 = p / per_row * sp.cells;
-    const int v0 = (int)(p % per_row) * sp.vels;
-    return At{c0, (int)std::min<long long>(sp.cells, sp.nc - c0), v0,
-              std::min(sp.vels, sp.nvt - v0)};
-  };
-  auto host_at = [&](const At& a) { return sp.host + a.c0 * sp.nvt + a.v0; };
-  auto bytes = [&](const At& a) { return (size_t)a.ncell * a.nvel * 8; };  // contiguous
-  auto launch = [&](long long p, int b) {
+  At at(long long p) const {
+    const long long per_row = (nvt + vels - 1) / vels;
+    const long long c0 = p / per_row * cells;
+    const int v0 = (int)(p % per_row) * vels;
+    return {c0, (int)std::min<long long>(cells, nc - c0), v0, std::min(vels, nvt - v0)};
+  }
+  void copy(long long p, void* blk) const {
     const At a = at(p);
-    hipError_t r = launch_state(h->P, f, fp32, sp.out, a.c0, a.ncell, a.v0, a.nvel,
-                                static_cast<double*>(blk[b]), h->stream);
-    return r == hipSuccess ? hipEventRecord(ev[b], h->stream) : r;
+    double* dst = host + a.c0 * nvt + a.v0;
+    const size_t bytes = (size_t)a.ncell * a.nvel * 8;  // contiguous
+    if (out)
+      std::memcpy(dst, blk, bytes);
+    else
+      std::memcpy(blk, dst, bytes);
+  }
+};
+
+// Host copies of pieces, on up to kCopiers threads that do nothing else (one thread's copy is
+// slower than the host link).  Below two threads the caller copies, in hand().
+class Copiers {
+ public:
+  static constexpr int kCopiers = 4, kBlocks = 2 * kCopiers;
+  Copiers(const StatePieces& sp, void* const* blk, int nb, int threads)
+      : sp_(sp), blk_(blk), nb_(nb), want_(threads > 1 ? threads : 0) {}
+  ~Copiers() {
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      stop_ = true;
+    }
+    work_.notify_all();
+    for (int t = 0; t < started_; ++t) th_[t].join();  // after the copies handed over
+  }
+  // Block b holds (is to hold) piece p: its copy may begin.  Each of the first calls starts a
+  // thread; if none will start, the caller copies.
+  void hand(int b, long long p) {
+    if (started_ < want_) {
+      try {
+        th_[started_] = std::thread([this] { run(); });
+        ++started_;
+      } catch (const std::system_error&) {
+        want_ = started_;
+      }
+    }
+    if (started_ == 0) {
+      sp_.copy(p, blk_[b]);
+      done_[b] = true;
+      return;
+    }
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      piece_[b] = p;
+      ready_[b] = true;
+      ++open_;
+    }
+    work_.notify_one();
+  }
+  // A block whose copy has ended, each reported once; -1: none (with wait: none is under way).
+  int take(bool wait) {
+    std::unique_lock<std::mutex> lock(m_);
+    for (;;) {
+      for (int b = 0; b < nb_; ++b)
+        if (done_[b]) {
+          done_[b] = false;
+          return b;
+        }
+      if (!wait || open_ == 0) return -1;
+      ended_.wait(lock);
+    }
+  }
+
+ private:
+  void run() {
+    std::unique_lock<std::mutex> lock(m_);
+    for (;;) {
+      int b = 0;
+      while (b < nb_ && !ready_[b]) ++b;
+      if (b == nb_) {
+        if (stop_) return;
+        work_.wait(lock);
+        continue;
+      }
+      ready_[b] = false;
+      const long long p = piece_[b];
+      lock.unlock();
+      sp_.copy(p, blk_[b]);
+      lock.lock();
+      done_[b] = true;
+      --open_;
+      ended_.notify_one();
+    }
+  }
+
+  const StatePieces& sp_;
+  void* const* blk_;
+  const int nb_;
+  int want_, started_ = 0;
+  std::thread th_[kCopiers];
+  std::mutex m_;
+  std::condition_variable work_, ended_;
+  long long piece_[kBlocks] = {};
+  bool ready_[kBlocks] = {}, done_[kBlocks] = {}, stop_ = false;
+  int open_ = 0;  // copies handed over that have not ended
+};
+
+// Moves the pieces through nb blocks.  A block is with the device from its launch until its event,
+// and with the copiers from hand to take.
+hipError_t move_pieces(const StatePieces& sp, void* const* blk, const hipEvent_t* ev, int nb,
+                       int threads) {
+  ugks_handle* h = sp.h;
+  void* f = h->B.f[h->steps & 1];
+  int idle[Copiers::kBlocks], nidle = nb;
+  for (int b = 0; b < nb; ++b) idle[b] = nb - 1 - b;
+  struct {
+    int b;
+    long long p;
+  } device[Copiers::kBlocks];  // launched, oldest first from `head`
+  long long head = 0, tail = 0;
+  long long held[Copiers::kBlocks] = {};  // piece of each block
+  hipError_t e = hipSuccess;
+  auto launch = [&](int b, long long p) {
+    const StatePieces::At a = sp.at(p);
+    e = launch_state(h->P, f, h->inst.fp32, sp.out, a.c0, a.ncell, a.v0, a.nvel,
+                     static_cast<double*>(blk[b]), h->stream);
+    if (e == hipSuccess) e = hipEventRecord(ev[b], h->stream);
+    device[tail++ % Copiers::kBlocks] = {b, p};
   };
+  auto oldest = [&] {  // the block and piece of the oldest launch, when the device is done with it
+    const auto d = device[head++ % Copiers::kBlocks];
+    e = hipEventSynchronize(ev[d.b]);
+    return d;
+  };
+  Copiers copiers(sp, blk, nb, threads);
+  long long next = 0;
   if (sp.out) {
-    // the next piece is under way while this one is copied
-    if (e == hipSuccess && first < sp.count) e = launch(first, 0);
-    int b = 0;
-    for (long long p = first; p < sp.count && e == hipSuccess; p += stride) {
-      const long long next = p + stride;
-      if (nb == 2 && next < sp.count) e = launch(next, b ^ 1);
-      if (e == hipSuccess) e = hipEventSynchronize(ev[b]);
+    while (e == hipSuccess) {
+      for (int b; (b = copiers.take(false)) >= 0;) idle[nidle++] = b;
+      while (next < sp.count && nidle > 0 && e == hipSuccess) launch(idle[--nidle], next++);
       if (e != hipSuccess) break;
-      const At a = at(p);
-      std::memcpy(host_at(a), blk[b], bytes(a));
-      if (nb == 2)
-        b ^= 1;
-      else if (next < sp.count)
-        e = launch(next, 0);
+      if (head < tail) {
+        const auto d = oldest();
+        if (e == hipSuccess) copiers.hand(d.b, d.p);
+      } else {
+        const int b = copiers.take(true);
+        if (b < 0) break;  // every piece is with the caller
+        idle[nidle++] = b;
+      }
     }
   } else {
-    bool used[2] = {false, false};
-    int b = 0;
-    for (long long p = first; p < sp.count && e == hipSuccess; p += stride) {
-      if (used[b]) e = hipEventSynchronize(ev[b]);
-      if (e != hipSuccess) break;
-      const At a = at(p);
-      std::memcpy(blk[b], host_at(a), bytes(a));
-      e = launch(p, b);
-      used[b] = true;
-      b = nb == 2 ? b ^ 1 : b;
+    long long launched = 0;
+    while (launched < sp.count && e == hipSuccess) {
+      if (next < sp.count && nidle == 0 && head < tail) {
+        idle[nidle++] = oldest().b;
+        if (e != hipSuccess) break;
+      }
+      const bool more = next < sp.count && nidle > 0;
+      if (more) {
+        const int b = idle[--nidle];
+        held[b] = next;
+        copiers.hand(b, next++);
+      }
+      // launch what has been copied; with nothing to hand out, wait for one
+      for (bool wait = !more; e == hipSuccess; wait = false) {
+        const int b = copiers.take(wait);
+        if (b < 0) break;
+        launch(b, held[b]);
+        ++launched;
+      }
     }
   }
   // no block goes back while the device may still use it
-  for (int b = 0; b < nb; ++b)
-    if (ev[b]) {
-      if (e == hipSuccess) e = hipEventSynchronize(ev[b]);
-      (void)hipEventDestroy(ev[b]);
-    }
-  put_block(blk[0], e, h->stream);
-  put_block(blk[1], e, h->stream);
+  while (head < tail && e == hipSuccess) (void)oldest();
   return e;
 }
+
 hipError_t move_state(ugks_handle* h, double* host, bool out) {
   StatePieces sp{h, host, out, (long long)h->P.nx * h->P.ny, h->P.NV * h->P.NC, 0, 0, 0};
   const long long cap = (long long)(kPinnedBytes / 8);
   sp.vels = (int)std::min<long long>(sp.nvt, cap);
   sp.cells = (int)std::max<long long>(1, std::min<long long>(sp.nc, cap / sp.nvt));
   sp.count = (sp.nc + sp.cells - 1) / sp.cells * ((sp.nvt + sp.vels - 1) / sp.vels);
-  // a thread for every four pieces (8 MB), at most four
-  const int nt = (int)std::min<long long>(4, (sp.count + 3) / 4);
-  std::thread th[3];
-  hipError_t e[4] = {};
-  int started = 0;
-  for (; started < nt - 1; ++started) {
-    const int t = started;
-    try {
-      th[t] = std::thread([&sp, &e, t, nt] { e[t + 1] = move_pieces(sp, t + 1, nt); });
-    } catch (const std::system_error&) {
-      break;  // the caller's thread takes the pieces of the threads that did not start
-    }
+  // a copying thread for every four pieces (8 MB), at most four, with two blocks each
+  const int threads = (int)std::min<long long>(Copiers::kCopiers, (sp.count + 3) / 4);
+  const int want = (int)std::min<long long>(sp.count, 2 * threads);
+  void* blk[Copiers::kBlocks] = {};
+  hipEvent_t ev[Copiers::kBlocks] = {};
+  hipError_t e = hipSetDevice(h->device);
+  int nb = 0;
+  for (; nb < want && e == hipSuccess; ++nb) {
+    blk[nb] = g_pinned.get();
+    e = blk[nb] ? hipEventCreateWithFlags(&ev[nb], hipEventDisableTiming) : hipErrorOutOfMemory;
   }
-  e[0] = move_pieces(sp, 0, nt);
-  for (int t = started + 1; t < nt; ++t)
-    if (e[0] == hipSuccess) e[0] = move_pieces(sp, t, nt);
-  for (int t = 0; t < started; ++t) th[t].join();
-  for (int t = 1; t < 4; ++t)
-    if (e[0] == hipSuccess) e[0] = e[t];
-  return e[0];
+  if (e == hipSuccess) e = move_pieces(sp, blk, ev, nb, threads);
+  for (int b = 0; b < nb; ++b)
+    if (ev[b]) (void)hipEventDestroy(ev[b]);
+  for (int b = 0; b < nb; ++b) put_block(blk[b], e, h->stream);
+  return e;
 }
 
 // Enqueue one step of a plan: four launches, each bracketed by timing events when enabled.

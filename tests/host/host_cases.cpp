@@ -1,0 +1,86 @@
+// Cases of the library's host code over the runtime of fake_hip.hpp, one per run (argument 1).
+// Exit status 0 when the case holds.
+#include <cstdio>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "fake_hip.hpp"
+#include "ugks.h"
+
+namespace {
+
+int failures = 0;
+void check(bool ok, const char* what) {
+  if (ok) return;
+  std::fprintf(stderr, "failed: %s\n", what);
+  ++failures;
+}
+
+struct Problem {
+  ugks_mesh mesh{43, 31, 2.0, 1.0};
+  ugks_vgrid vg{64, 61, 5.0, 5.0, 0};  // 41.6 MB of f: 20 pieces
+  ugks_bc bc{UGKS_BC_CHANNEL, 0, 2.0, 1.0, 1.0, 0.0, 0.0};
+  ugks_opts o{};
+  Problem(int nx = 43, int ny = 31, int nu = 64, int nv = 61) {
+    mesh.nx = nx;
+    mesh.ny = ny;
+    vg.nu = nu;
+    vg.nv = nv;
+    o.cfl = 0.8;
+    o.rho0 = o.T0 = 1.0;
+    o.noise = 0.01;
+    o.seed = 1;
+  }
+  size_t cells() const { return (size_t)mesh.nx * mesh.ny; }
+  size_t values() const {
+    return cells() * vg.nu * vg.nv * (vg.internal_dof > 0 ? 2 : 1);
+  }
+  ugks_handle* create(void* stream = nullptr) {
+    o.stream = stream;
+    ugks_handle* h = nullptr;
+    check(ugks_create(&mesh, &vg, 0.1, &bc, &o, &h) == UGKS_OK, ugks_last_error(nullptr));
+    return h;
+  }
+};
+
+bool shifted(const std::vector<double>& a, const std::vector<double>& b, double by) {
+  for (size_t k = 0; k < a.size(); ++k)
+    if (b[k] != a[k] + by) return false;
+  return true;
+}
+
+// Images of many pieces on a stream that every host thread reads as its own: they are taken
+// after the steps enqueued before, and the next step runs on what was set.
+void per_thread_stream() {
+  Problem p;
+  ugks_handle* h = p.create(hipStreamPerThread);
+  std::vector<double> f0(p.values()), f(p.values());
+  check(ugks_get_state(h, f0.data(), nullptr) == UGKS_OK, "get");
+  fake::knobs.step_us = 100000;
+  check(ugks_step(h, 2) == UGKS_OK, "step");
+  check(ugks_get_state(h, f.data(), nullptr) == UGKS_OK, "get after steps");
+  check(shifted(f0, f, 2.0), "the state after both steps");
+  for (double& x : f0) x = 3.0 * x + 1.0;
+  check(ugks_step(h, 1) == UGKS_OK, "step");
+  check(ugks_set_state(h, f0.data(), nullptr) == UGKS_OK, "set under a step");
+  check(ugks_step(h, 1) == UGKS_OK, "step");
+  check(ugks_get_state(h, f.data(), nullptr) == UGKS_OK, "get");
+  check(shifted(f0, f, 1.0), "the state set, one step on");
+  ugks_destroy(h);
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> cases = {
+      {"per_thread_stream", per_thread_stream},
+  };
+  const auto it = cases.find(argc > 1 ? argv[1] : "");
+  if (it == cases.end()) return 2;
+  it->second();
+  std::printf("%s: %s\n", argv[1], failures ? "FAILED" : "ok");
+  std::fflush(stdout);
+  std::_Exit(failures ? 1 : 0);  // the streams' threads never end
+}
