@@ -233,6 +233,24 @@ struct Busy {
   }
 };
 
+// The handle's device is the current one while this lives: kernels are launched and events recorded
+// on a stream of its own device only.  The caller's device is current again afterwards.
+struct OnDevice {
+  int before = -1;  // the caller's device, where it is another one
+  hipError_t e;
+  explicit OnDevice(const ugks_handle* h) {
+    int d = 0;
+    e = hipGetDevice(&d);
+    if (e != hipSuccess || d == h->device) return;
+    e = hipSetDevice(h->device);
+    if (e == hipSuccess) before = d;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+  OnDevice(const OnDevice&) = delete;
+};
+
 // Uniform nodes on [-a, a] with both ends, made exactly mirror-symmetric; trapezoid weights.
 void velocity_nodes(int n, double a, double* x, double* w) {
   const double h = 2.0 * a / (double)(n - 1);
@@ -610,7 +628,7 @@ hipError_t move_state(ugks_handle* h, double* host, bool out) {
   const int want = (int)std::min<long long>(sp.count, 2 * threads);
   void* blk[Copiers::kBlocks] = {};
   hipEvent_t ev[Copiers::kBlocks] = {};
-  hipError_t e = hipSetDevice(h->device);
+  hipError_t e = hipSuccess;
   int nb = 0;
   for (; nb < want && e == hipSuccess; ++nb) {
     blk[nb] = g_pinned.get();
@@ -1093,7 +1111,8 @@ int ugks_moments(ugks_handle* h, double* host_out) {
   int* mark = reinterpret_cast<int*>(blk);
   *mark = 0;
   const double* W = h->B.W[h->steps & 1];
-  hipError_t e = hipSuccess;
+  const OnDevice dev(h);
+  hipError_t e = dev.e;
   for (size_t c0 = 0; c0 < nc && e == hipSuccess; c0 += kCells) {
     const size_t n = std::min(kCells, nc - c0);
     e = launch_moments(W + 4 * c0, (int)n, h->P.lam_c, h->B.flag,
@@ -1172,7 +1191,9 @@ int ugks_get_state(ugks_handle* h, double* f, double* W) {
   if (!b.ok) return fail(h, UGKS_E_BUSY, "handle in use%s");
   if (h->poisoned) return poisoned_fail(h);
   const size_t nc = (size_t)h->P.nx * h->P.ny;
-  hipError_t e = f ? move_state(h, f, true) : hipSuccess;
+  const OnDevice dev(h);
+  hipError_t e = dev.e;
+  if (e == hipSuccess && f) e = move_state(h, f, true);
   if (e == hipSuccess && W)
     e = hipMemcpyAsync(W, h->B.W[h->steps & 1], nc * 4 * 8, hipMemcpyDeviceToHost, h->stream);
   int flag = 0;
@@ -1190,7 +1211,9 @@ int ugks_set_state(ugks_handle* h, const double* f, const double* W) {
   if (!b.ok) return fail(h, UGKS_E_BUSY, "handle in use%s");
   if (h->poisoned) return poisoned_fail(h);
   const size_t nc = (size_t)h->P.nx * h->P.ny;
-  hipError_t e = f ? move_state(h, const_cast<double*>(f), false) : hipSuccess;
+  const OnDevice dev(h);
+  hipError_t e = dev.e;
+  if (e == hipSuccess && f) e = move_state(h, const_cast<double*>(f), false);
   if (e == hipSuccess && W)
     e = hipMemcpyAsync(h->B.W[h->steps & 1], W, nc * 4 * 8, hipMemcpyHostToDevice, h->stream);
   // the adaptive step of the next step follows the new W

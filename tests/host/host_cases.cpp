@@ -71,11 +71,35 @@ void per_thread_stream() {
   ugks_destroy(h);
 }
 
+// A handle of another GPU than the caller's current one, which stays current.
+void other_device() {
+  Problem p;
+  (void)hipSetDevice(1);
+  ugks_handle* h = p.create(fake::make_stream(1));
+  (void)hipSetDevice(0);
+  auto same = [](const char* what) {
+    int d = -1;
+    (void)hipGetDevice(&d);
+    check(d == 0, what);
+  };
+  std::vector<double> f(p.values()), g(p.values()), m(4 * p.cells());
+  check(ugks_moments(h, m.data()) == UGKS_OK, "moments");
+  same("the current device after ugks_moments");
+  check(ugks_get_state(h, f.data(), nullptr) == UGKS_OK, "get");
+  same("the current device after ugks_get_state");
+  for (double& x : f) x += 1.0;
+  check(ugks_set_state(h, f.data(), nullptr) == UGKS_OK, "set");
+  same("the current device after ugks_set_state");
+  check(ugks_get_state(h, g.data(), nullptr) == UGKS_OK && f == g, "the state set");
+  ugks_destroy(h);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
       {"per_thread_stream", per_thread_stream},
+      {"other_device", other_device},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");
   if (it == cases.end()) return 2;

@@ -14,6 +14,7 @@ CLANG = "/opt/rocm/llvm/bin/clang++"
 
 CASES = [
     "per_thread_stream",
+    "other_device",
 ]
 
 
