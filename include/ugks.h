@@ -230,7 +230,8 @@ int ugks_get_time(ugks_handle* h, double* time, double* dt_next);
    of Eq. (4).  f: nx*ny*NF doubles, W: 4*nx*ny doubles, canonical layout, caller-owned host
    memory; either may be NULL.  get waits for the stream; set replaces the current state
    (in FP32-store mode f is rounded to FP32).  Errors: UGKS_E_INVAL (NULL handle),
-   UGKS_E_BUSY, UGKS_E_DEVICE (a copy failed), UGKS_E_STATE (get: an invalid state was
+   UGKS_E_BUSY, UGKS_E_DEVICE (a copy failed; if set had replaced part of f by then, the handle is
+   marked failed as after a launch failure in ugks_step), UGKS_E_STATE (get: an invalid state was
    flagged; the buffers are still written). */
 int ugks_get_state(ugks_handle* h, double* f, double* W);
 int ugks_set_state(ugks_handle* h, const double* f, const double* W);

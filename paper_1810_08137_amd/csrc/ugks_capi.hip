@@ -67,8 +67,9 @@ struct ugks_handle {
   double tau_ref = 0.0;
   std::string err;
   std::atomic<int> busy{0};
-  // a launch failed part-way through a step: the device state is unknown (which f/W buffer
-  // is current cannot be trusted), so every later call except destroy returns UGKS_E_DEVICE
+  // a launch failed part-way through a step (which f/W buffer is current cannot be trusted), or
+  // ugks_set_state failed with part of f replaced: the device state is unknown, so every later
+  // call except destroy returns UGKS_E_DEVICE
   bool poisoned = false;
   // kernel timing
   bool timing = false;
@@ -218,7 +219,8 @@ int hip_fail(ugks_handle* h, hipError_t e, const char* what) {
 
 int poisoned_fail(ugks_handle* h) {
   return fail(h, UGKS_E_DEVICE,
-              "a kernel launch failed part-way through a step; the state is unknown%s");
+              "a kernel launch failed part-way through a step, or setting the state did; "
+              "the state is unknown%s");
 }
 
 struct Busy {
@@ -550,7 +552,7 @@ class Copiers {
 // Moves the pieces through nb blocks.  A block is with the device from its launch until its event,
 // and with the copiers from hand to take.
 hipError_t move_pieces(const StatePieces& sp, void* const* blk, const hipEvent_t* ev, int nb,
-                       int threads) {
+                       int threads, long long* launched) {
   ugks_handle* h = sp.h;
   void* f = h->B.f[h->steps & 1];
   int idle[Copiers::kBlocks], nidle = nb;
@@ -566,7 +568,9 @@ hipError_t move_pieces(const StatePieces& sp, void* const* blk, const hipEvent_t
     const StatePieces::At a = sp.at(p);
     e = launch_state(h->P, f, h->inst.fp32, sp.out, a.c0, a.ncell, a.v0, a.nvel,
                      static_cast<double*>(blk[b]), h->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[b], h->stream);
+    if (e != hipSuccess) return;
+    ++*launched;
+    e = hipEventRecord(ev[b], h->stream);
     device[tail++ % Copiers::kBlocks] = {b, p};
   };
   auto oldest = [&] {  // the block and piece of the oldest launch, when the device is done with it
@@ -591,8 +595,7 @@ hipError_t move_pieces(const StatePieces& sp, void* const* blk, const hipEvent_t
       }
     }
   } else {
-    long long launched = 0;
-    while (launched < sp.count && e == hipSuccess) {
+    while (*launched < sp.count && e == hipSuccess) {
       if (next < sp.count && nidle == 0 && head < tail) {
         idle[nidle++] = oldest().b;
         if (e != hipSuccess) break;
@@ -608,7 +611,6 @@ hipError_t move_pieces(const StatePieces& sp, void* const* blk, const hipEvent_t
         const int b = copiers.take(wait);
         if (b < 0) break;
         launch(b, held[b]);
-        ++launched;
       }
     }
   }
@@ -617,7 +619,8 @@ hipError_t move_pieces(const StatePieces& sp, void* const* blk, const hipEvent_t
   return e;
 }
 
-hipError_t move_state(ugks_handle* h, double* host, bool out) {
+// *launched: the pieces that the device was given.
+hipError_t move_state(ugks_handle* h, double* host, bool out, long long* launched) {
   StatePieces sp{h, host, out, (long long)h->P.nx * h->P.ny, h->P.NV * h->P.NC, 0, 0, 0};
   const long long cap = (long long)(kPinnedBytes / 8);
   sp.vels = (int)std::min<long long>(sp.nvt, cap);
@@ -628,15 +631,21 @@ hipError_t move_state(ugks_handle* h, double* host, bool out) {
   const int want = (int)std::min<long long>(sp.count, 2 * threads);
   void* blk[Copiers::kBlocks] = {};
   hipEvent_t ev[Copiers::kBlocks] = {};
-  hipError_t e = hipSuccess;
+  // all blocks and events are at hand before the first launch; fewer than wanted serve as well
   int nb = 0;
-  for (; nb < want && e == hipSuccess; ++nb) {
+  for (; nb < want; ++nb) {
     blk[nb] = g_pinned.get();
-    e = blk[nb] ? hipEventCreateWithFlags(&ev[nb], hipEventDisableTiming) : hipErrorOutOfMemory;
+    if (!blk[nb]) break;
+    if (hipEventCreateWithFlags(&ev[nb], hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      g_pinned.put(blk[nb]);
+      break;
+    }
   }
-  if (e == hipSuccess) e = move_pieces(sp, blk, ev, nb, threads);
-  for (int b = 0; b < nb; ++b)
-    if (ev[b]) (void)hipEventDestroy(ev[b]);
+  *launched = 0;
+  const hipError_t e =
+      nb > 0 ? move_pieces(sp, blk, ev, nb, threads, launched) : hipErrorOutOfMemory;
+  for (int b = 0; b < nb; ++b) (void)hipEventDestroy(ev[b]);
   for (int b = 0; b < nb; ++b) put_block(blk[b], e, h->stream);
   return e;
 }
@@ -1193,7 +1202,8 @@ int ugks_get_state(ugks_handle* h, double* f, double* W) {
   const size_t nc = (size_t)h->P.nx * h->P.ny;
   const OnDevice dev(h);
   hipError_t e = dev.e;
-  if (e == hipSuccess && f) e = move_state(h, f, true);
+  long long pieces = 0;
+  if (e == hipSuccess && f) e = move_state(h, f, true, &pieces);
   if (e == hipSuccess && W)
     e = hipMemcpyAsync(W, h->B.W[h->steps & 1], nc * 4 * 8, hipMemcpyDeviceToHost, h->stream);
   int flag = 0;
@@ -1213,7 +1223,8 @@ int ugks_set_state(ugks_handle* h, const double* f, const double* W) {
   const size_t nc = (size_t)h->P.nx * h->P.ny;
   const OnDevice dev(h);
   hipError_t e = dev.e;
-  if (e == hipSuccess && f) e = move_state(h, const_cast<double*>(f), false);
+  long long pieces = 0;  // of f that may have been replaced
+  if (e == hipSuccess && f) e = move_state(h, const_cast<double*>(f), false, &pieces);
   if (e == hipSuccess && W)
     e = hipMemcpyAsync(h->B.W[h->steps & 1], W, nc * 4 * 8, hipMemcpyHostToDevice, h->stream);
   // the adaptive step of the next step follows the new W
@@ -1228,7 +1239,10 @@ int ugks_set_state(ugks_handle* h, const double* f, const double* W) {
     e = launch_ghost_fill(pv, h->pt, h->inst.fp32, h->stream);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "writing the state");
+  if (e != hipSuccess) {
+    h->poisoned = h->poisoned || pieces > 0;
+    return hip_fail(h, e, "writing the state");
+  }
   return UGKS_OK;
 }
 

@@ -318,6 +318,7 @@ hipError_t hipHostFree(void* p) {
     pinned().erase(it);
   }
   --fake::counts.pinned_live;
+  ++fake::knobs.pinned_left;
   std::free(p);
   return hipSuccess;
 }
@@ -370,6 +371,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
 hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
 hipError_t hipEventDestroy(hipEvent_t e) {
   delete reinterpret_cast<Event*>(e);
+  ++fake::knobs.events_left;
   return hipSuccess;
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t st) {

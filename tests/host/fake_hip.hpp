@@ -15,8 +15,8 @@ namespace fake {
 struct Knobs {
   std::atomic<int> step_us{0};           // time an update takes
   std::atomic<int> image_us{0};          // time the copy of one image piece takes
-  std::atomic<int> pinned_left{1 << 30};  // pinned allocations that still succeed
-  std::atomic<int> events_left{1 << 30};  // events that can still be created
+  std::atomic<int> pinned_left{1 << 30};  // pinned allocations that can be live besides those now
+  std::atomic<int> events_left{1 << 30};  // events, likewise
   std::atomic<int> images_left{1 << 30};  // launches of the image kernel that still succeed
 };
 extern Knobs knobs;

@@ -94,12 +94,48 @@ void other_device() {
   ugks_destroy(h);
 }
 
+// Setting a state is whole or an error.  Too little pinned memory or too few events for every
+// block: fewer serve.  A launch that fails: nothing was written before the first, and after it the
+// handle is marked failed, as after a step that failed part-way.
+void set_is_whole() {
+  Problem p;
+  std::vector<double> f0(p.values()), f(p.values()), g(p.values()), m(4 * p.cells());
+  const int plenty = 1 << 30;
+  ugks_handle* h = p.create();
+  check(ugks_get_state(h, f0.data(), nullptr) == UGKS_OK, "get");
+  for (int n = 1; n <= 5; n += 2) {
+    for (double& x : f0) x += 1.0;
+    ugks_destroy(h);  // the pool's blocks go with the last handle
+    h = p.create();
+    (n == 3 ? fake::knobs.events_left : fake::knobs.pinned_left) = n;
+    check(ugks_set_state(h, f0.data(), nullptr) == UGKS_OK, "set with few blocks");
+    check(ugks_get_state(h, g.data(), nullptr) == UGKS_OK && f0 == g, "the state set");
+    fake::knobs.pinned_left = plenty;
+    fake::knobs.events_left = plenty;
+  }
+  for (size_t k = 0; k < f.size(); ++k) f[k] = f0[k] + 5.0;
+  fake::knobs.images_left = 0;
+  check(ugks_set_state(h, f.data(), nullptr) == UGKS_E_DEVICE, "set without a launch");
+  fake::knobs.images_left = 5;
+  check(ugks_get_state(h, g.data(), nullptr) == UGKS_E_DEVICE, "get that fails part-way");
+  fake::knobs.images_left = plenty;
+  check(ugks_get_state(h, g.data(), nullptr) == UGKS_OK && f0 == g, "the state before");
+  fake::knobs.images_left = 5;
+  check(ugks_set_state(h, f.data(), nullptr) == UGKS_E_DEVICE, "set that fails part-way");
+  fake::knobs.images_left = plenty;
+  check(ugks_step(h, 1) == UGKS_E_DEVICE, "step after a state set in part");
+  check(ugks_moments(h, m.data()) == UGKS_E_DEVICE, "moments after a state set in part");
+  ugks_destroy(h);
+  check(fake::counts.misuse == 0, "no block given back early");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
       {"per_thread_stream", per_thread_stream},
       {"other_device", other_device},
+      {"set_is_whole", set_is_whole},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");
   if (it == cases.end()) return 2;

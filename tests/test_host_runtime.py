@@ -15,6 +15,7 @@ CLANG = "/opt/rocm/llvm/bin/clang++"
 CASES = [
     "per_thread_stream",
     "other_device",
+    "set_is_whole",
 ]
 
 
