@@ -619,7 +619,44 @@ hipError_t move_pieces(const StatePieces& sp, void* const* blk, const hipEvent_t
   return e;
 }
 
-// *launched: the pieces that the device was given.
+// The same without pinned memory: plane by plane through pageable memory, transposed by the host.
+hipError_t move_planes(const StatePieces& sp, long long* launched) {
+  ugks_handle* h = sp.h;
+  const size_t ss = h->ssize, row = (size_t)h->P.nx * ss, pitch = (size_t)h->P.Lx * ss;
+  std::unique_ptr<char[]> raw(new (std::nothrow) char[(size_t)sp.nc * ss]);
+  if (!raw) return hipErrorOutOfMemory;
+  double* d = reinterpret_cast<double*>(raw.get());
+  float* s = reinterpret_cast<float*>(raw.get());
+  const bool fp32 = h->prec == UGKS_FP32_STORE;
+  hipError_t e = hipSuccess;
+  for (int v = 0; v < sp.nvt && e == hipSuccess; ++v) {
+    char* cells = static_cast<char*>(h->B.f[h->steps & 1]) +
+                  ((size_t)v * h->P.PS + (size_t)kHalo * h->P.Lx + kHalo) * ss;
+    double* x = sp.host + v;
+    if (sp.out) {
+      e = hipMemcpy2DAsync(raw.get(), row, cells, pitch, row, (size_t)h->P.ny,
+                           hipMemcpyDeviceToHost, h->stream);
+      if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+      if (e != hipSuccess) break;
+      for (long long c = 0; c < sp.nc; ++c) x[c * sp.nvt] = fp32 ? (double)s[c] : d[c];
+    } else {
+      for (long long c = 0; c < sp.nc; ++c) {
+        if (fp32)
+          s[c] = (float)x[c * sp.nvt];
+        else
+          d[c] = x[c * sp.nvt];
+      }
+      e = hipMemcpy2DAsync(cells, pitch, raw.get(), row, row, (size_t)h->P.ny,
+                           hipMemcpyHostToDevice, h->stream);
+      if (e != hipSuccess) break;
+      ++*launched;
+      e = hipStreamSynchronize(h->stream);
+    }
+  }
+  return e;
+}
+
+// *launched: the pieces (planes) that the device was given.
 hipError_t move_state(ugks_handle* h, double* host, bool out, long long* launched) {
   StatePieces sp{h, host, out, (long long)h->P.nx * h->P.ny, h->P.NV * h->P.NC, 0, 0, 0};
   const long long cap = (long long)(kPinnedBytes / 8);
@@ -644,9 +681,49 @@ hipError_t move_state(ugks_handle* h, double* host, bool out, long long* launche
   }
   *launched = 0;
   const hipError_t e =
-      nb > 0 ? move_pieces(sp, blk, ev, nb, threads, launched) : hipErrorOutOfMemory;
+      nb > 0 ? move_pieces(sp, blk, ev, nb, threads, launched) : move_planes(sp, launched);
   for (int b = 0; b < nb; ++b) (void)hipEventDestroy(ev[b]);
   for (int b = 0; b < nb; ++b) put_block(blk[b], e, h->stream);
+  return e;
+}
+
+// (rho, U, V, T) of all cells into the caller's buffer, through a pinned block whose first 64 bytes
+// hold the mark of an invalid state; without one W is copied as it is and the host forms them.
+hipError_t read_moments(ugks_handle* h, size_t nc, double* out, bool& bad) {
+  constexpr size_t kHead = 64, kCells = (kPinnedBytes - kHead) / 32;
+  const double* W = h->B.W[h->steps & 1];
+  hipError_t e = hipSuccess;
+  if (char* blk = static_cast<char*>(g_pinned.get())) {
+    int* mark = reinterpret_cast<int*>(blk);
+    *mark = 0;
+    for (size_t c0 = 0; c0 < nc && e == hipSuccess; c0 += kCells) {
+      const size_t n = std::min(kCells, nc - c0);
+      e = launch_moments(W + 4 * c0, (int)n, h->P.lam_c, h->B.flag,
+                         reinterpret_cast<double*>(blk + kHead), mark, h->stream);
+      const hipError_t es = hipStreamSynchronize(h->stream);
+      if (e == hipSuccess) e = es;
+      if (e == hipSuccess) std::memcpy(out + 4 * c0, blk + kHead, n * 32);
+    }
+    bad = *mark != 0;
+    put_block(blk, e, h->stream);
+    return e;
+  }
+  int flag = 0;
+  e = hipMemcpyAsync(out, W, nc * 32, hipMemcpyDeviceToHost, h->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(&flag, h->B.flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  if (e != hipSuccess) return e;
+  bad = flag != 0;
+  for (size_t c = 0; c < nc; ++c, out += 4) {
+    const double rho = out[0], U = out[1] / rho, V = out[2] / rho;
+    const double T = (out[3] - 0.5 * rho * (U * U + V * V)) / (h->P.lam_c * rho);
+    out[1] = U;
+    out[2] = V;
+    out[3] = T;
+    if (!(rho > 0) || !(T > 0) || !std::isfinite(U) || !std::isfinite(V) || !std::isfinite(T))
+      bad = true;
+  }
   return e;
 }
 
@@ -1113,25 +1190,9 @@ int ugks_moments(ugks_handle* h, double* host_out) {
   if (!b.ok) return fail(h, UGKS_E_BUSY, "handle in use%s");
   if (h->poisoned) return poisoned_fail(h);
   const size_t nc = (size_t)h->P.nx * h->P.ny;
-  // through a pinned block: its first 64 bytes hold the mark of an invalid state
-  constexpr size_t kHead = 64, kCells = (kPinnedBytes - kHead) / 32;
-  char* blk = static_cast<char*>(g_pinned.get());
-  if (!blk) return hip_fail(h, hipErrorOutOfMemory, "pinned memory for the moments");
-  int* mark = reinterpret_cast<int*>(blk);
-  *mark = 0;
-  const double* W = h->B.W[h->steps & 1];
   const OnDevice dev(h);
-  hipError_t e = dev.e;
-  for (size_t c0 = 0; c0 < nc && e == hipSuccess; c0 += kCells) {
-    const size_t n = std::min(kCells, nc - c0);
-    e = launch_moments(W + 4 * c0, (int)n, h->P.lam_c, h->B.flag,
-                       reinterpret_cast<double*>(blk + kHead), mark, h->stream);
-    const hipError_t es = hipStreamSynchronize(h->stream);
-    if (e == hipSuccess) e = es;
-    if (e == hipSuccess) std::memcpy(host_out + 4 * c0, blk + kHead, n * 32);
-  }
-  const bool bad = *mark != 0;
-  put_block(blk, e, h->stream);
+  bool bad = false;
+  const hipError_t e = dev.e == hipSuccess ? read_moments(h, nc, host_out, bad) : dev.e;
   if (e != hipSuccess) return hip_fail(h, e, "reading the moments");
   if (bad) return fail(h, UGKS_E_STATE, "invalid state (NaN, rho <= 0 or T <= 0)%s");
   return UGKS_OK;

@@ -129,6 +129,39 @@ void set_is_whole() {
   check(fake::counts.misuse == 0, "no block given back early");
 }
 
+// No pinned memory at all: everything that needs none of its own still works.
+void no_pinned_memory() {
+  fake::knobs.pinned_left = 0;
+  for (int form = 0; form < 3; ++form) {
+    Problem p(43, 31, 24, 25);
+    p.o.precision = form == 1 ? UGKS_FP32_STORE : UGKS_FP64;
+    p.vg.internal_dof = form == 2 ? 1 : 0;
+    p.bc.kind = form == 2 ? UGKS_BC_PERIODIC : UGKS_BC_CHANNEL;
+    ugks_handle* h = p.create();
+    std::vector<double> f0(p.values()), f(p.values()), W(4 * p.cells()), m(4 * p.cells());
+    check(ugks_get_state(h, f0.data(), nullptr) == UGKS_OK, "get");
+    for (size_t k = 0; k < f0.size(); ++k) f0[k] = (double)(k % 4099) + 0.5;
+    check(ugks_set_state(h, f0.data(), nullptr) == UGKS_OK, "set");
+    check(ugks_step(h, 1) == UGKS_OK, "step");
+    check(ugks_get_state(h, f.data(), W.data()) == UGKS_OK, "get");
+    check(shifted(f0, f, 1.0), "the state set, one step on");
+    check(ugks_moments(h, m.data()) == UGKS_OK, "moments");
+    const double lam_c = 0.25 * (2 + p.vg.internal_dof);
+    bool same = true;
+    for (size_t c = 0; c < p.cells(); ++c) {
+      const double* w = &W[4 * c];
+      const double U = w[1] / w[0], V = w[2] / w[0];
+      const double T = (w[3] - 0.5 * w[0] * (U * U + V * V)) / (lam_c * w[0]);
+      same = same && m[4 * c] == w[0] && m[4 * c + 1] == U && m[4 * c + 2] == V && m[4 * c + 3] == T;
+    }
+    check(same, "the moments of W");
+    W[4 * p.cells() - 1] = -1.0;
+    check(ugks_set_state(h, nullptr, W.data()) == UGKS_OK, "set W");
+    check(ugks_moments(h, m.data()) == UGKS_E_STATE && m[0] == W[0], "moments of an invalid state");
+    ugks_destroy(h);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -136,6 +169,7 @@ int main(int argc, char** argv) {
       {"per_thread_stream", per_thread_stream},
       {"other_device", other_device},
       {"set_is_whole", set_is_whole},
+      {"no_pinned_memory", no_pinned_memory},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");
   if (it == cases.end()) return 2;

@@ -16,6 +16,7 @@ CASES = [
     "per_thread_stream",
     "other_device",
     "set_is_whole",
+    "no_pinned_memory",
 ]
 
 
