@@ -179,20 +179,31 @@ PinnedPool g_pinned;
 
 // Hands a block back after work on `stream` that ended with e.  Where that was an error the device
 // may still use the block: it waits again, also where a capture on some other stream refuses
-// ordinary waits (work put into a capture on this one does not run), and a block that cannot be
-// waited for is not handed back.
+// ordinary waits, and a block that cannot be waited for is not handed back.
 void put_block(void* blk, hipError_t e, hipStream_t stream) {
   if (blk && e != hipSuccess) {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    const bool done = (hipStreamIsCapturing(stream, &status) == hipSuccess &&
-                       status != hipStreamCaptureStatusNone) ||
-                      hipStreamSynchronize(stream) == hipSuccess;
+    const bool done = hipStreamSynchronize(stream) == hipSuccess;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (!done) return;
+    if (!done) {
+      (void)hipGetLastError();  // not for the next launch to report
+      return;
+    }
   }
   g_pinned.put(blk);
+}
+
+// Calls that wait for their stream ask this first: a stream that is being captured refuses the
+// wait, but what was enqueued before it would stay in the capture, and run on the caller's memory or
+// on a pinned block whenever the graph is launched.
+hipError_t can_wait(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return hipSuccess;  // the calls that follow give the error
+  }
+  return status == hipStreamCaptureStatusNone ? hipSuccess : hipErrorStreamCaptureUnsupported;
 }
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -239,13 +250,15 @@ struct Busy {
 // on a stream of its own device only.  The caller's device is current again afterwards.
 struct OnDevice {
   int before = -1;  // the caller's device, where it is another one
-  hipError_t e;
+  hipError_t e;     // of that, or of can_wait
   explicit OnDevice(const ugks_handle* h) {
     int d = 0;
     e = hipGetDevice(&d);
-    if (e != hipSuccess || d == h->device) return;
-    e = hipSetDevice(h->device);
-    if (e == hipSuccess) before = d;
+    if (e == hipSuccess && d != h->device) {
+      e = hipSetDevice(h->device);
+      if (e == hipSuccess) before = d;
+    }
+    if (e == hipSuccess) e = can_wait(h->stream);
   }
   ~OnDevice() {
     if (before >= 0) (void)hipSetDevice(before);
@@ -1090,10 +1103,12 @@ int ugks_create(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, const
   // through a pinned block, as far as it holds them: the runtime stages copies from pageable memory
   // one by one (a solver of 130 x 37 cells is created in 193 us so, in 240 from pageable memory)
   int rc = UGKS_OK;
+  e = can_wait(h->stream);
+  if (e != hipSuccess) rc = hip_fail(nullptr, e, "waiting for the initial state");
   g_pinned.add_user();
-  char* blk = static_cast<char*>(g_pinned.get());
+  char* blk = rc == UGKS_OK ? static_cast<char*>(g_pinned.get()) : nullptr;
   size_t used = 0;
-  for (int c = 0; c < nt; ++c) {
+  for (int c = 0; c < nt && rc == UGKS_OK; ++c) {
     Copy cp = copies[c];
     if (blk && used + cp.n <= kPinnedBytes) {
       cp.src = std::memcpy(blk + used, cp.src, cp.n);
@@ -1245,7 +1260,9 @@ int ugks_get_time(ugks_handle* h, double* time, double* dt_next) {
   if (!b.ok) return fail(h, UGKS_E_BUSY, "handle in use%s");
   if (h->poisoned) return poisoned_fail(h);
   unsigned long long rt[3];
-  hipError_t e = hipMemcpyAsync(rt, h->B.rmax, sizeof rt, hipMemcpyDeviceToHost, h->stream);
+  hipError_t e = can_wait(h->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(rt, h->B.rmax, sizeof rt, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "reading the time");
   std::memcpy(time, &rt[2], sizeof(double));
@@ -1317,8 +1334,9 @@ int ugks_get_face_flux(ugks_handle* h, double* Fx, double* Fy) {
                 "the last step ran with ugks_step_static, whose face records are not kept%s");
   const size_t nfx = (size_t)h->P.ny * (h->P.nx + 1), nfy = (size_t)(h->P.ny + 1) * h->P.nx;
   std::vector<double> rx(Fx ? nfx * kRec : 0), ry(Fy ? nfy * kRec : 0);
-  hipError_t e = hipSuccess;
-  if (Fx) e = hipMemcpyAsync(rx.data(), h->B.recx, rx.size() * 8, hipMemcpyDeviceToHost, h->stream);
+  hipError_t e = can_wait(h->stream);
+  if (e == hipSuccess && Fx)
+    e = hipMemcpyAsync(rx.data(), h->B.recx, rx.size() * 8, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess && Fy)
     e = hipMemcpyAsync(ry.data(), h->B.recy, ry.size() * 8, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);

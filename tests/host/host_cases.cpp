@@ -162,6 +162,38 @@ void no_pinned_memory() {
   }
 }
 
+// Calls that wait for their stream are refused while it is captured, and leave nothing in the
+// capture that would read or write their memory when the graph is launched.
+void under_capture() {
+  Problem p;
+  hipStream_t stream = fake::make_stream(0);
+  ugks_handle* h = p.create(stream);
+  std::vector<double> f0(p.values()), f(p.values()), W(4 * p.cells()), m(4 * p.cells());
+  check(ugks_get_state(h, f0.data(), W.data()) == UGKS_OK, "get");
+  auto refused = [&](const char* what, auto call) {
+    fake::begin_capture(stream);
+    const int rc = call();
+    check(fake::end_capture(stream) == 0, what);
+    check(rc == UGKS_E_DEVICE, what);
+  };
+  refused("moments", [&] { return ugks_moments(h, m.data()); });
+  refused("get f", [&] { return ugks_get_state(h, f.data(), nullptr); });
+  refused("get W", [&] { return ugks_get_state(h, nullptr, W.data()); });
+  refused("set f", [&] { return ugks_set_state(h, f0.data(), nullptr); });
+  refused("set W", [&] { return ugks_set_state(h, nullptr, W.data()); });
+  refused("time", [&] { return ugks_get_time(h, &m[0], &m[1]); });
+  refused("face flux", [&] { return ugks_get_face_flux(h, f.data(), nullptr); });
+  refused("create", [&] {
+    ugks_handle* other = nullptr;
+    p.o.stream = stream;
+    return ugks_create(&p.mesh, &p.vg, 0.1, &p.bc, &p.o, &other);
+  });
+  check(ugks_step(h, 1) == UGKS_OK && ugks_get_state(h, f.data(), nullptr) == UGKS_OK, "step");
+  check(shifted(f0, f, 1.0), "the state after the step");
+  ugks_destroy(h);
+  check(fake::counts.misuse == 0, "no block given back early");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -170,6 +202,7 @@ int main(int argc, char** argv) {
       {"other_device", other_device},
       {"set_is_whole", set_is_whole},
       {"no_pinned_memory", no_pinned_memory},
+      {"under_capture", under_capture},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");
   if (it == cases.end()) return 2;

@@ -17,6 +17,7 @@ CASES = [
     "other_device",
     "set_is_whole",
     "no_pinned_memory",
+    "under_capture",
 ]
 
 
