@@ -14,7 +14,6 @@
 #include <memory>
 #include <mutex>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -497,7 +496,7 @@ class Copiers {
       try {
         th_[started_] = std::thread([this] { run(); });
         ++started_;
-      } catch (const std::system_error&) {
+      } catch (...) {  // no thread, or no memory for one
         want_ = started_;
       }
     }

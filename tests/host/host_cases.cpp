@@ -1,8 +1,13 @@
 // Cases of the library's host code over the runtime of fake_hip.hpp, one per run (argument 1).
 // Exit status 0 when the case holds.
+#include <dlfcn.h>
+
+#include <atomic>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -194,7 +199,38 @@ void under_capture() {
   check(fake::counts.misuse == 0, "no block given back early");
 }
 
+// Host memory runs out while the copying threads start: the images are moved all the same.
+std::atomic<int> allocations_left{1 << 30};  // of the library that still succeed
+void threads_that_do_not_start() {
+  Problem p;
+  ugks_handle* h = p.create();
+  std::vector<double> f0(p.values()), f(p.values());
+  check(ugks_get_state(h, f0.data(), nullptr) == UGKS_OK, "get");
+  for (int n = 0; n < 4; ++n) {
+    for (double& x : f0) x += 1.0;
+    allocations_left = n;
+    check(ugks_set_state(h, f0.data(), nullptr) == UGKS_OK, "set");
+    allocations_left = n;
+    check(ugks_get_state(h, f.data(), nullptr) == UGKS_OK, "get");
+    allocations_left = 1 << 30;
+    check(f0 == f, "the state set");
+  }
+  ugks_destroy(h);
+}
+
 }  // namespace
+
+void* operator new(size_t n) {
+  Dl_info at;
+  if (allocations_left < (1 << 20) && dladdr(__builtin_return_address(0), &at) &&
+      std::strstr(at.dli_fname, "libugks") && allocations_left.fetch_sub(1) <= 0)
+    throw std::bad_alloc();
+  void* p = std::malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
@@ -203,6 +239,7 @@ int main(int argc, char** argv) {
       {"set_is_whole", set_is_whole},
       {"no_pinned_memory", no_pinned_memory},
       {"under_capture", under_capture},
+      {"threads_that_do_not_start", threads_that_do_not_start},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");
   if (it == cases.end()) return 2;
