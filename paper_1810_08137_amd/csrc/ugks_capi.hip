@@ -123,10 +123,12 @@ void* scratch_address(int device, std::string& why) {
   return g_scratch_ptr[device];
 }
 
-// Pinned host blocks through which the state goes between the planes and the caller's buffers,
-// kept while a handle or a batch lives (allocating one costs more than a small copy), at most
-// kPinnedKept of them.  A block belongs to one call from get to put, so calls on any threads
-// and streams share the pool.
+// Pinned host blocks through which the state goes between the planes and the caller's buffers, at
+// most kPinnedKept of them kept while a handle or a batch lives.  The last handle gives back all but
+// one: allocating and freeing a block takes 50 us, and a process with one solver at a time (40 x 10
+// cells: created, its moments read, closed) took 173 us for each when none stayed, 118 with one
+// kept.  A block belongs to one call from get to put, so calls on any threads and streams share the
+// pool.
 constexpr size_t kPinnedBytes = (size_t)2 << 20;
 constexpr int kPinnedKept = 8;
 class PinnedPool {
@@ -147,7 +149,7 @@ class PinnedPool {
     if (!p) return;
     {
       std::lock_guard<std::mutex> lock(m_);
-      if (users_ > 0 && nfree_ < kPinnedKept) {
+      if (nfree_ < (users_ > 0 ? kPinnedKept : 1)) {
         free_[nfree_++] = p;
         return;
       }
@@ -164,7 +166,7 @@ class PinnedPool {
     {
       std::lock_guard<std::mutex> lock(m_);
       if (--users_ > 0) return;
-      while (nfree_ > 0) drop[n++] = free_[--nfree_];
+      while (nfree_ > 1) drop[n++] = free_[--nfree_];
     }
     while (n > 0) (void)hipHostFree(drop[--n]);
   }
@@ -1099,25 +1101,12 @@ int ugks_create(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, const
   copies[nt++] = {B.rmax, rmax_tsum, sizeof rmax_tsum};
   copies[nt++] = {h->plan_dev, plan_host.data(), plan_host.size()};
   if (h->static_ok) copies[nt++] = {h->plan_static, plan_static_host.data(), plan_static_host.size()};
-  // through a pinned block, as far as it holds them: the runtime stages copies from pageable memory
-  // one by one (a solver of 130 x 37 cells is created in 193 us so, in 240 from pageable memory)
   int rc = UGKS_OK;
   e = can_wait(h->stream);
   if (e != hipSuccess) rc = hip_fail(nullptr, e, "waiting for the initial state");
-  g_pinned.add_user();
-  char* blk = rc == UGKS_OK ? static_cast<char*>(g_pinned.get()) : nullptr;
-  size_t used = 0;
   for (int c = 0; c < nt && rc == UGKS_OK; ++c) {
-    Copy cp = copies[c];
-    if (blk && used + cp.n <= kPinnedBytes) {
-      cp.src = std::memcpy(blk + used, cp.src, cp.n);
-      used = round_up(used + cp.n, 64);
-    }
-    e = hipMemcpyAsync(cp.dst, cp.src, cp.n, hipMemcpyHostToDevice, h->stream);
-    if (e != hipSuccess) {
-      rc = hip_fail(nullptr, e, "hipMemcpyAsync of the tables");
-      break;
-    }
+    e = hipMemcpyAsync(copies[c].dst, copies[c].src, copies[c].n, hipMemcpyHostToDevice, h->stream);
+    if (e != hipSuccess) rc = hip_fail(nullptr, e, "hipMemcpyAsync of the tables");
   }
   if (rc == UGKS_OK) {
     e = hipMemsetAsync(B.flag, 0, sizeof(int), h->stream);
@@ -1141,13 +1130,12 @@ int ugks_create(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, const
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) rc = hip_fail(nullptr, e, "initial state");
   }
-  put_block(blk, rc == UGKS_OK ? hipSuccess : e, h->stream);
   if (rc != UGKS_OK) {
-    g_pinned.drop_user();
     if (h->owns_ws) (void)hipFree(h->ws);
     delete h;
     return rc;
   }
+  g_pinned.add_user();
   *out = h;
   return UGKS_OK;
 }

@@ -199,6 +199,24 @@ void under_capture() {
   check(fake::counts.misuse == 0, "no block given back early");
 }
 
+// One solver at a time: the pool keeps a block from one to the next, and no more than that once a
+// solver that needed many is closed.
+void one_solver_at_a_time() {
+  Problem small(40, 10, 24, 24), large;
+  std::vector<double> m(4 * small.cells()), f(large.values());
+  for (int n = 0; n < 3; ++n) {
+    ugks_handle* h = small.create();
+    check(ugks_moments(h, m.data()) == UGKS_OK, "moments");
+    ugks_destroy(h);
+    check(fake::counts.pinned_allocs == 1, "one allocation serves every solver");
+  }
+  ugks_handle* h = large.create();
+  check(ugks_get_state(h, f.data(), nullptr) == UGKS_OK, "get");
+  check(fake::counts.pinned_live > 1 && fake::counts.pinned_live <= 8, "blocks of a live solver");
+  ugks_destroy(h);
+  check(fake::counts.pinned_live == 1, "blocks kept without a solver");
+}
+
 // Host memory runs out while the copying threads start: the images are moved all the same.
 std::atomic<int> allocations_left{1 << 30};  // of the library that still succeed
 void threads_that_do_not_start() {
@@ -239,6 +257,7 @@ int main(int argc, char** argv) {
       {"set_is_whole", set_is_whole},
       {"no_pinned_memory", no_pinned_memory},
       {"under_capture", under_capture},
+      {"one_solver_at_a_time", one_solver_at_a_time},
       {"threads_that_do_not_start", threads_that_do_not_start},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");

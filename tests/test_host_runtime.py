@@ -18,6 +18,7 @@ CASES = [
     "set_is_whole",
     "no_pinned_memory",
     "under_capture",
+    "one_solver_at_a_time",
     "threads_that_do_not_start",
 ]
 
