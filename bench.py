@@ -26,11 +26,11 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "8f4732c106abcbc87a269a831a337bb491fa02957559a090989e63ca755a9f4a",
-    "fp64": 1.339e9,
-    "fp32_store": 0.6997e9,
+    "source_sha256": "f96029b6e4502e8f65bafc36014eed522cfc61ee4a2093f9d9af5484eab890d4",
+    "fp64": 1.3429e9,
+    "fp32_store": 0.6999e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
-    "valu_fp64": 1.0107e8,
+    "valu_fp64": 1.0104e8,
 }
 # VALU issue ceiling: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles at
 # 2.4 GHz (FP64 FMA runs at this full rate on MI355X: 78.6 TFLOP/s)

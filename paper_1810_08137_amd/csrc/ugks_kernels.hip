@@ -315,15 +315,15 @@ __device__ __forceinline__ int plane_col(const KParams& P, int i) {
   return P.bc == UGKS_BC_PERIODIC ? wrap(i, P.nx) : (i < P.nx + 1 ? i : P.nx + 1);
 }
 
-// Workgroups are handed to the 8 XCDs round-robin; renumber the n of one instance, whose blocks
-// start at a multiple of 8, so that each XCD works through one contiguous range of them (its own
-// L2 then serves the rows its neighbours also read) and all XCDs work on every instance.  -1: one
-// of the blocks that fill the instance up to a multiple of 8.
+// Workgroups are handed to the 8 XCDs round-robin; renumber the n of one instance so that each XCD
+// works through one contiguous range of them (its own L2 then serves the rows its neighbours also
+// read) and all XCDs work on every instance.  Which XCD its first block falls on does not matter:
+// blocks 8 apart share one.  (With every instance filled up to a multiple of 8 blocks, a step of 256
+// solves of 4..8 x 3..6 cells at 8^2 took 149 us, without 107; of 16 of 60..135 x 20..35 at 24..32 x
+// 24 404 and 367.)
 constexpr int kXcd = 8;
-__host__ __device__ __forceinline__ int xcd_round(int n) { return (n + kXcd - 1) / kXcd * kXcd; }
 __device__ __forceinline__ int xcd_block(int local, int n) {
   const int q = n / kXcd, r = n % kXcd, x = local % kXcd, i = local / kXcd;
-  if (i >= q + (x < r ? 1 : 0)) return -1;
   return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
@@ -542,7 +542,6 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, c
   const int G = I->gsplit;
   const int ntx = (P.nx + kTileS - 1) / kTileS;
   const int b = xcd_block(blockIdx.x - first_block(off, ii), ntx * P.ny * G * P.NC);
-  if (b < 0) return;
   int t, gg, j;
   cell_block(b, P.ny, ntx, t, gg, j);
   const bool hpart = gg >= G;  // planes of H
@@ -2067,7 +2066,6 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
   const int ntx = (P.nx + kTileU - 1) / kTileU;
   const int b = xcd_block(blockIdx.x - first_block(off, ii),
                           ntx * ((P.ny + 1) / 2) * G * Gv * P.NC);
-  if (b < 0) return;
   int t, gg, pb;
   cell_block(b, (P.ny + 1) / 2, ntx, t, gg, pb);
   const int jb = min(2 * pb, P.ny - 2);       // rows jb, jb + 1
@@ -2697,9 +2695,8 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
     off[4][q] = t.red;
     off[5][q] = 0;
     t.shak = t.shak || P.shak;
-    t.sums += xcd_round(((P.nx + kTileS - 1) / kTileS) * P.ny * G);
-    t.upd += xcd_round(((P.nx + kTileU - 1) / kTileU) * ((P.ny + 1) / 2) * img[q].usplit *
-                       P.vsplit * P.NC);
+    t.sums += ((P.nx + kTileS - 1) / kTileS) * P.ny * G;
+    t.upd += ((P.nx + kTileU - 1) / kTileU) * ((P.ny + 1) / 2) * img[q].usplit * P.vsplit * P.NC;
     if (G > 1)
       t.red += (nfx + t.red_faces - 1) / t.red_faces + (nfy + t.red_faces - 1) / t.red_faces +
                (P.shak ? ((kSlotsShakhov - kSlotCell) * (int)P.ncs + kWave * t.red_waves - 1) /

@@ -220,12 +220,29 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared,
   return hipSuccess;
 }
 
-hipError_t hipLaunchKernel(const void* func, dim3, dim3, void** args, size_t, hipStream_t stream) {
+hipError_t hipLaunchKernel(const void* func, dim3 grid, dim3, void** args, size_t,
+                           hipStream_t stream) {
   Stream& s = at(stream);
   if (s.device != t_device) return ret(hipErrorInvalidHandle);
   const std::string& name = kernels()[func];
   auto is = [&](const char* part) { return name.find(part) != std::string::npos; };
   const bool f32 = is("If");
+  if (is("sums_kernel") || is("update_kernel")) {
+    // a workgroup for each segment of 62 (update: 60) cells of a row (of two) and each chunk
+    const bool sums = is("sums_kernel");
+    const Inst* in = arg<const Inst*>(args, 0);
+    const int n = arg<int>(args, 2);
+    s.put([=] {
+      long long work = 0;
+      for (int q = 0; q < n; ++q) {
+        const KParams& P = in[q].P;
+        const int tile = sums ? 62 : 60, rows = sums ? P.ny : (P.ny + 1) / 2;
+        work += (long long)((P.nx + tile - 1) / tile) * rows * P.NC *
+                (sums ? in[q].gsplit : in[q].usplit * P.vsplit);
+      }
+      fake::counts.idle_workgroups += (int)(grid.x - work);
+    });
+  }
   if (is("init_kernel")) {
     const PlanView pv = arg<PlanView>(args, 0);
     s.put([=] { f32 ? init<float>(pv.inst[0]) : init<double>(pv.inst[0]); });

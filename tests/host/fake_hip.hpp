@@ -23,6 +23,7 @@ extern Knobs knobs;
 
 struct Counts {
   std::atomic<int> pinned_allocs{0}, pinned_live{0};
+  std::atomic<int> idle_workgroups{0};  // of the moment and update kernels' grids
   std::atomic<int> misuse{0};  // pinned memory freed or given out while queued work used it
 };
 extern Counts counts;

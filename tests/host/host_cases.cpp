@@ -217,6 +217,23 @@ void one_solver_at_a_time() {
   check(fake::counts.pinned_live == 1, "blocks kept without a solver");
 }
 
+// Every workgroup of a batch's launches has work, however small its members are.
+void batch_workgroups() {
+  std::vector<ugks_handle*> hs;
+  std::vector<Problem> ps;
+  for (int k = 0; k < 9; ++k) ps.emplace_back(3 + 20 * k, 1 + k % 5, 8 + k, 8);
+  for (Problem& p : ps) hs.push_back(p.create());
+  ugks_batch* b = nullptr;
+  check(ugks_batch_create(nullptr, 9, &b) == UGKS_OK, "batch");
+  check(ugks_step_batch(b, hs.data(), 9, 2) == UGKS_OK, "batch step");
+  for (ugks_handle* h : hs) check(ugks_step(h, 1) == UGKS_OK, "step alone");
+  std::vector<double> m(4 * ps[0].cells());
+  check(ugks_moments(hs[0], m.data()) == UGKS_OK, "moments");
+  check(fake::counts.idle_workgroups == 0, "no workgroup without work");
+  for (ugks_handle* h : hs) ugks_destroy(h);
+  ugks_batch_destroy(b);
+}
+
 // Host memory runs out while the copying threads start: the images are moved all the same.
 std::atomic<int> allocations_left{1 << 30};  // of the library that still succeed
 void threads_that_do_not_start() {
@@ -258,6 +275,7 @@ int main(int argc, char** argv) {
       {"no_pinned_memory", no_pinned_memory},
       {"under_capture", under_capture},
       {"one_solver_at_a_time", one_solver_at_a_time},
+      {"batch_workgroups", batch_workgroups},
       {"threads_that_do_not_start", threads_that_do_not_start},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");

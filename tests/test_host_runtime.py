@@ -19,6 +19,7 @@ CASES = [
     "no_pinned_memory",
     "under_capture",
     "one_solver_at_a_time",
+    "batch_workgroups",
     "threads_that_do_not_start",
 ]
 
