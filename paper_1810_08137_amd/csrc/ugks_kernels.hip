@@ -579,10 +579,12 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, c
   chunk_range(hu.count, g, G, a0, a1);
   // The wavefronts of a SIMD are issued oldest first, so the later ones fall behind and end alone.
   // Here a wavefront is issued before those that are a quarter of their lines further on: FP32
-  // storage at 400 x 100 x 40^2 113 -> 109 us, Shakhov at 130 x 37 x 40^2 34.9 -> 33.4.  FP64, which
-  // waits for its loads more than for issue, is slower with it (190 -> 196 us).  (The FP32 form
-  // then takes 151 registers, three waves per SIMD; held to four it spills and takes 117 us.)
-  constexpr bool kEven = sizeof(S) == 4 || kShak;
+  // storage at 400 x 100 x 40^2 113 -> 109 us, FP64 Shakhov at 130 x 37 x 40^2 34.9 -> 33.4.  FP64
+  // BGK, which waits for its loads more than for issue, is slower with it (190 -> 196 us).  It costs
+  // registers: the FP32 BGK form then takes 151, three waves per SIMD instead of four, and held to
+  // four it spills and takes 117 us; the FP32 Shakhov form would take 171 instead of 165, two waves
+  // instead of three (400 x 100 x 40^2 115 -> 154 us), so it goes without.
+  constexpr bool kEven = (sizeof(S) == 4) != kShak;
   for (int a = a0; a < a1; ++a) {
     if constexpr (kEven) {
       const int done = 4 * (a - a0);
