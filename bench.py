@@ -26,9 +26,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "dbc40656d47d5e2de10d7663ab244a69af4a410a7b5029b06940a3ab49a606f7",
-    "fp64": 1.3411e9,
-    "fp32_store": 0.6995e9,
+    "source_sha256": "6482c71608d5e6066d103838e6ecb47278ca4a97792bd703e2026ee8f0a66af5",
+    "fp64": 1.3362e9,
+    "fp32_store": 0.7e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
     "valu_fp64": 1.0104e8,
 }

@@ -1560,8 +1560,10 @@ struct PairStage {
   // and at every u node, so formed once per workgroup and not by every wavefront
   T qx[kPair][kWave + 1];
   T qy[kPair + 1][kWave];
-  T qg[kPair][2][kWave];
 };
+// Those of each cell's g^n (0) and g^{n+1} (1), the last of the stage.
+template <typename T>
+using CellFactors = T[2][kWave];
 
 // A Gaussian factor exp(-lam (x - c)^2) along the uniform nodes x0, x0 + h, x0 + 2h, ...:
 // e is its value at the current node and r the ratio to the next one; successive ratios
@@ -1571,6 +1573,13 @@ template <typename T>
 __device__ __forceinline__ void gauss_next(T& e, T& r, T qm1) {
   e *= r;
   r = fma(r, qm1, r);
+}
+
+// The second factor, exp(-2 lam h^2) - 1, in the arithmetic type.
+template <typename T>
+__device__ __forceinline__ T second_factor(double hstep, double lam) {
+  const T h = T(hstep);
+  return expm1_of(T(-2) * h * h * T(lam));
 }
 
 // Cubic of the folded equilibrium polynomial P(un, ut) of a record (interface scalars) in
@@ -1699,8 +1708,9 @@ __device__ __forceinline__ void y_face(const PairStage<T>& st, int fr, int lane,
 // FP32 storage 4% slower, its registers then spill); the Shakhov variant has no registers to
 // spare beyond 1.  The ring only works because nothing else in the loop is a vector load: the
 // next v node is a scalar load (UGKS_CONST), so waiting for it never waits for f loads.
-template <typename S, int SU, bool kShak, bool kNode, int kAhead = kShak ? 1 : 2>
+template <typename S, int SU, bool kShak, bool kNode, bool kOwnQ, int kAhead = kShak ? 1 : 2>
 __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<S>& st,
+                                              const CellFactors<S>* qg,
                                               const S (*sk)[4][kWave], int lane, int sv,
                                               int jb, bool store0, int g, int G, int gv, int Gv,
                                               bool writes, bool ghost_lane, bool late,
@@ -1738,8 +1748,14 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
   const int hf = sv > 0 ? 0 : 1;
   const T qx0 = st.qx[r0][xo], qx1 = st.qx[r1][xo];
   const T qyi = st.qy[fin_r][lane], qym = st.qy[fmid_r][lane], qyo = st.qy[fout_r][lane];
-  const T qn0 = st.qg[r0][0][lane], q10 = st.qg[r0][1][lane];
-  const T qn1 = st.qg[r1][0][lane], q11 = st.qg[r1][1][lane];
+  auto cell_factor = [&](int r, int n) {
+    if constexpr (kOwnQ)
+      return second_factor<T>(P.dv, st.cell[r][n == 0 ? C_LAMN : C_LAM1][lane]);
+    else
+      return qg[r][n][lane];
+  };
+  const T qn0 = cell_factor(r0, 0), q10 = cell_factor(r0, 1);
+  const T qn1 = cell_factor(r1, 0), q11 = cell_factor(r1, 1);
   const T two_idx = T(2.0 * P.inv_dx), two_idy = T(2.0 * P.inv_dy);
   // this workgroup's v nodes of the half: chunk gv of Gv, vh nodes from node vf
   int vc0, vc1;
@@ -1990,7 +2006,7 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
 // checkpoint steps on exactly as a running solver does.
 template <typename S, int SU>
 __device__ __forceinline__ void ghost_fill_quadrant(const KParams& P, const PairStage<S>& st,
-                                                    int lane, int sv, int jb, bool store0,
+                                                    const CellFactors<S>* qg, int lane, int sv, int jb, bool store0,
                                                     int g, int G, int gv, int Gv, bool ghost_w,
                                                     UGKS_GLOBAL S* f, int i) {
   typedef S T;
@@ -2005,8 +2021,8 @@ __device__ __forceinline__ void ghost_fill_quadrant(const KParams& P, const Pair
   const unsigned w0 = st0 ? oC : kDropOffset, w1 = st1 ? oD : kDropOffset;
   const Half hu = axis_half(P.K, SU, false), hv = axis_half(P.M, sv, false);
   const int hf = sv > 0 ? 0 : 1;
-  const T qn0 = st.qg[r0][0][lane], q10 = st.qg[r0][1][lane];
-  const T qn1 = st.qg[r1][0][lane], q11 = st.qg[r1][1][lane];
+  const T qn0 = qg[r0][0][lane], q10 = qg[r0][1][lane];
+  const T qn1 = qg[r1][0][lane], q11 = qg[r1][1][lane];
   const long long pstep = (long long)hv.step * P.PS;
   int a0, a1;
   chunk_range(hu.count, g, G, a0, a1);
@@ -2056,6 +2072,13 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
   // Shakhov: (1 - Pr)(lambda^2/rho) q of each lane's cell at t^n and t^{n+1}, per row
   __shared__ T sk_raw[kShak ? kPair * 4 * kWave : 1];
   T(*sk)[4][kWave] = reinterpret_cast<T(*)[4][kWave]>(sk_raw);
+  // The FP64 Shakhov form of four wavefronts forms the cells' second factors in every wavefront
+  // instead: with them in LDS a CU holds one of its workgroups and not two (update of 100 x 60 cells
+  // at 11 x 24, 300 workgroups: 48.2 us with them there, 36.5 without; of 40 x 10 at 24^2, 120
+  // workgroups: 15.8 and 16.9).
+  constexpr bool kOwnQ = sizeof(S) == 8 && kShak && kCh == 1;
+  __shared__ T qg_raw[kOwnQ ? 1 : kPair * 2 * kWave];
+  CellFactors<T>* qg = reinterpret_cast<CellFactors<T>*>(qg_raw);
   const int lane = threadIdx.x & (kWave - 1);
   // wavefront w: quadrant q, and c, which of the workgroup's kCh velocity chunks
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2246,11 +2269,6 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
     r[col] = T(exp(-lam * hs * (2.0 * d + hs)));
     lost = lost || (x > 700.0 && (h == 0 ? c > v0 : c < v0));
   };
-  // exp(-2 lam h^2) - 1, in the arithmetic type
-  auto second_factor = [&](double lam) {
-    const T h = T(hstep);
-    return expm1_of(T(-2) * h * h * T(lam));
-  };
   // Gauss starts of g^n of the cells of row jb + r from their primitive state p
   auto start_gn = [&](const Prim& p, int r) {
 #pragma unroll
@@ -2357,8 +2375,10 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
     const double cell[C_COUNT] = {pn.lam, pn.U, pn.V, p1.lam, p1.U, p1.V, An, A1, Af, AdF};
 #pragma unroll
     for (int n = 0; n < C_COUNT; ++n) st.cell[r][n][lane] = T(cell[n]);
-    st.qg[r][0][lane] = second_factor(pn.lam);
-    st.qg[r][1][lane] = second_factor(p1.lam);
+    if constexpr (!kOwnQ) {
+      qg[r][0][lane] = second_factor<T>(hstep, pn.lam);
+      qg[r][1][lane] = second_factor<T>(hstep, p1.lam);
+    }
     // Gauss starts of this cell in both halves of v
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -2384,7 +2404,7 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
         T* e = u < kPair ? st.xs[h][u][0] : st.ys[h][u - kPair][0];
         T* r = u < kPair ? st.xs[h][u][1] : st.ys[h][u - kPair][1];
         start(flam[n], fvel[n], h, e, r, lane);
-        if (h == 0) (u < kPair ? st.qx[u] : st.qy[u - kPair])[lane] = second_factor(flam[n]);
+        if (h == 0) (u < kPair ? st.qx[u] : st.qy[u - kPair])[lane] = second_factor<T>(hstep, flam[n]);
       }
     }
   }
@@ -2395,29 +2415,30 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
   const int sv = quad_sv(q);
   if constexpr (kFill) {
     if (quad_su(q) > 0)
-      ghost_fill_quadrant<S, 1>(P, st, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
+      ghost_fill_quadrant<S, 1>(P, st, qg, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
                                 ghost_w, fout, i);
     else
-      ghost_fill_quadrant<S, -1>(P, st, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
+      ghost_fill_quadrant<S, -1>(P, st, qg, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
                                  ghost_w, fout, i);
     return;
   }
   if (quad_su(q) > 0)
-    pair_quadrant<S, 1, kShak, kNode>(P, st, sk, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
-                               valid || ghost_w, ghost_lane, kCh == 2 && c == 1, fin, fout,
-                               i);
+    pair_quadrant<S, 1, kShak, kNode, kOwnQ>(P, st, qg, sk, lane, sv, jb, store0, kCh * g + c,
+                                             kCh * G, gv, Gv, valid || ghost_w, ghost_lane,
+                                             kCh == 2 && c == 1, fin, fout, i);
   else
-    pair_quadrant<S, -1, kShak, kNode>(P, st, sk, lane, sv, jb, store0, kCh * g + c, kCh * G, gv, Gv,
-                                valid || ghost_w, ghost_lane, kCh == 2 && c == 1, fin, fout,
-                                i);
+    pair_quadrant<S, -1, kShak, kNode, kOwnQ>(P, st, qg, sk, lane, sv, jb, store0, kCh * g + c,
+                                              kCh * G, gv, Gv, valid || ghost_w, ghost_lane,
+                                              kCh == 2 && c == 1, fin, fout, i);
 }
 
 // Velocity chunks per update workgroup, kCh (its wavefronts: four quadrants times kCh), which
 // share one stage, and the update waves per SIMD.  FP64: the registers of two rows allow two
-// waves per SIMD; with two chunks, one workgroup of eight waves per CU (its stage takes 73 KB),
-// and sharing the stage halves its cost per velocity node; one chunk serves meshes too small
-// to give every CU a workgroup of two.  FP32 storage: four waves per SIMD, four workgroups of
-// four waves per CU (37 KB each); the Shakhov form two waves per SIMD.
+// waves per SIMD; with two chunks, one workgroup of eight waves per CU, and sharing the stage
+// halves its cost per velocity node; one chunk, two workgroups of four waves per CU (79.7 KB
+// each, 81.8 Shakhov), serves meshes too small to give every CU a workgroup of two.  FP32 storage:
+// four waves per SIMD, four workgroups of four waves per CU (39.9 KB each); the Shakhov form two
+// waves per SIMD.
 template <typename S, bool kShak>
 constexpr int kUpdateWaves = sizeof(S) == 8 || kShak ? 2 : 4;
 

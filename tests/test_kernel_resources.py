@@ -75,3 +75,21 @@ def _waves(vgprs):
 ])
 def test_moment_kernel_wavefronts(kernels, kernel, waves):
     assert _waves(kernels[kernel][0]) >= waves, kernels[kernel]
+
+
+@pytest.mark.parametrize("kernel,workgroups", [
+    ("update_kernel<double, 1>", 2),
+    ("update_kernel_nodes<double, 1>", 2),
+    ("update_kernel_shakhov<double, 1>", 2),
+    ("update_kernel<double, 2>", 1),
+    ("update_kernel_nodes<double, 2>", 1),
+    ("update_kernel_shakhov<double, 2>", 1),
+    ("update_kernel<float, 1>", 4),
+    ("update_kernel_nodes<float, 1>", 4),
+    ("update_kernel_shakhov<float, 1>", 2),
+])
+def test_update_kernel_workgroups(kernels, kernel, workgroups):
+    """By registers and by LDS: the plan's workgroups that run at once on a CU."""
+    vgprs, lds, threads = kernels[kernel]
+    assert _waves(vgprs) * 4 * 64 // threads >= workgroups, (vgprs, threads)
+    assert LDS // lds >= workgroups, lds
