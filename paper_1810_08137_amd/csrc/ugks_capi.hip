@@ -293,7 +293,6 @@ struct Shape {
   int Lx, Ly;
   size_t PS;  // values per velocity plane
   size_t nc;
-  size_t ncs;  // cells of the moment sums: those of the mesh and the two ghost columns
 };
 
 bool shape_ok(const ugks_mesh* mesh, const ugks_vgrid* vg, Shape& s, std::string& why) {
@@ -341,7 +340,6 @@ bool shape_ok(const ugks_mesh* mesh, const ugks_vgrid* vg, Shape& s, std::string
   s.Ly = s.ny + 2 * kHalo;
   s.PS = round_up((size_t)s.Lx * (size_t)s.Ly, (size_t)kWave);
   s.nc = (size_t)s.nx * s.ny;
-  s.ncs = s.nc + 2 * (size_t)s.ny;
   return true;
 }
 
@@ -378,7 +376,7 @@ Layout layout_of(const Shape& s, int prec, int chunks, bool shak) {
       s.nc * 4 * 8,                             // W0
       s.nc * 4 * 8,                             // W1
       2 * (size_t)s.ny * 4 * 8,                 // Wg
-      (size_t)s.NC * chunks * s.ncs * (shak ? kSlotsShakhov : kSlots) * 8,  // hs: partial sums
+      (size_t)s.NC * chunks * hs_part(s.nc, (size_t)s.ny, shak) * 8,  // hs: partial sums
       (size_t)s.NC * s.ny * (s.nx + 1) * kRec * 8,  // recx
       (size_t)s.NC * (s.ny + 1) * s.nx * kRec * 8,  // recy
       (size_t)(s.K + 6 * s.M) * 8,              // wk, wm, vmom
@@ -835,8 +833,8 @@ void fill_constants(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, c
   P.q_c = 0.5 * (double)(2 + s.dof);
   P.a4_c = 4.0 / (double)(2 + s.dof);
   P.shak = shak ? 1 : 0;
-  P.nslot = shak ? kSlotsShakhov : kSlots;
-  P.ncs = (long long)s.ncs;
+  P.nc = (long long)s.nc;
+  P.part = (long long)hs_part(s.nc, (size_t)s.ny, shak);
   P.pr_c = shak ? 1.0 - opts->prandtl : 0.0;
   P.Lx = s.Lx;
   P.Ly = s.Ly;

@@ -72,8 +72,8 @@ struct KParams {
   double q_c;       // (2 + dof)/2: the energy row of the micro-slope solve, q2 = |U|^2 + q_c/lambda
   double a4_c;      // 4/(2 + dof): its energy coefficient, a4 = a4_c lambda^2/rho (...)
   int shak;         // Shakhov collision model (else BGK)
-  int nslot;        // per-cell sums per velocity chunk: kSlots, or kSlotsShakhov
-  long long ncs;    // cells of one such sum: those of the mesh and the two ghost columns
+  long long nc;     // cells, nx ny
+  long long part;   // values of one chunk's moment sums (hs_part)
   double pr_c;      // 1 - Prandtl number (Shakhov)
   int Lx, Ly;       // padded row length and row count of a plane
   int bc, collisionless, inlet_fixed_u;
@@ -106,14 +106,21 @@ struct KParams {
   UGKS_GLOBAL double* tsum;              // simulated time: the sum of the steps taken
 };
 
+// One chunk's moment sums: sum after sum (kSlots of them, kSlotsShakhov with the Shakhov model), each
+// of all cells; sum q of face side s is number 16 s + q.  The sums towards x faces (and their heat
+// sums) have ny values more, of a channel's ghost cell in each row: the inlet's in those towards +x,
+// the outlet's in those towards -x.
+inline size_t hs_part(size_t nc, size_t ny, bool shak) {
+  return shak ? kSlotsShakhov * nc + 34 * ny : kSlots * nc + 32 * ny;
+}
+
 // Device buffers carved out of one workspace.
 struct Buffers {
   void* f[2];       // [NC NV][PS] storage type
   double* W[2];     // [nx*ny][4], ping-pong with f
   double* Wg;       // [2][ny][4]
-  double* hs;       // [NC gmax][nslot][ncs]: partial g of sum q of face side s of cell c at
-                    // ((g nslot) + 16 s + q) ncs + c; chunks of H after those of G.  The inlet
-                    // ghost of row j is cell nx ny + j, the outlet ghost nx ny + ny + j
+  double* hs;       // [NC gmax][hs_part]: moment sums of the velocity chunks, those of H after
+                    // those of G
   double* recx;     // [NC][32][ny (nx+1)]: records of G, then of H, field-major
   double* recy;     // [NC][32][(ny+1) nx]
   double* wk;       // [K], followed by wm [M], then vmom [M][5]

@@ -315,6 +315,19 @@ __device__ __forceinline__ int plane_col(const KParams& P, int i) {
   return P.bc == UGKS_BC_PERIODIC ? wrap(i, P.nx) : (i < P.nx + 1 ? i : P.nx + 1);
 }
 
+// Place of the first value of sum q (16: the Shakhov model's heat sum) of face side s, which is one of
+// an x (y) face, and of the raw moment r of the Shakhov model's cells, in a chunk's moment sums
+// (hs_part).
+template <bool kX>
+__device__ __forceinline__ long long sum_at(const KParams& P, int s, int q) {
+  const long long first = q < 16 ? 16 * s + q : s;
+  const long long at = kX ? first * (P.nc + P.ny) : first * P.nc + (q < 16 ? 32LL : 2LL) * P.ny;
+  return q < 16 ? at : at + kSlotHeat * P.nc + 32LL * P.ny;
+}
+__device__ __forceinline__ long long cell_sum_at(const KParams& P, int r) {
+  return (kSlotCell + r) * P.nc + 34LL * P.ny;
+}
+
 // Workgroups are handed to the 8 XCDs round-robin; renumber the n of one instance so that each XCD
 // works through one contiguous range of them (its own L2 then serves the rows its neighbours also
 // read) and all XCDs work on every instance.  Which XCD its first block falls on does not matter:
@@ -548,7 +561,7 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, c
   const int g = hpart ? gg - G : gg;
   const UGKS_GLOBAL S* f = static_cast<const UGKS_GLOBAL S*>(I->f[(I->cur + step) & 1]) +
                            (hpart ? (long long)P.NV * P.PS : 0ll);
-  UGKS_GLOBAL double* hs = I->hs + (size_t)gg * P.nslot * (size_t)P.ncs;
+  UGKS_GLOBAL double* hs = I->hs + gg * P.part;
   const int i = t * kTileS - 1 + lane;
   const bool valid = lane >= 1 && lane <= kTileS && i < P.nx;
   // channel ghost columns (i = -1, nx): their sums towards the domain are the ghost sums of
@@ -804,16 +817,13 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, c
     }
   }
   __syncthreads();
-  const size_t nc = (size_t)P.ncs;
   // the inlet ghost's sums towards +x (waves 0 and 3), the outlet ghost's towards -x (waves
   // 1 and 2)
   if (ghost_wave && ghost && q == (i < 0 ? 0 : 2)) {
     const int ox = q == 0 ? 3 : 2, fx = q == 0 ? S_XP : S_XM;
-    const size_t cell = (size_t)P.nx * P.ny + (size_t)(i < 0 ? 0 : P.ny) + j;
+    const size_t cell = (size_t)P.nc + j;
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      hs[(size_t)(16 * fx + r) * nc + cell] = ax[r] + red[ox][r][lane];
-    if constexpr (kShak) hs[(size_t)(kSlotHeat + fx) * nc + cell] = ax[16] + red[ox][16][lane];
+    for (int r = 0; r < kR; ++r) hs[sum_at<true>(P, fx, r) + cell] = ax[r] + red[ox][r][lane];
   }
   if (valid && (q == 0 || q == 2)) {
     const size_t cell = (size_t)j * P.nx + i;
@@ -823,16 +833,16 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, c
     for (int r = 0; r < 16; ++r) {
       const double sx = (ax[r] + red[ox][r][lane]) * (r >= 4 && r < 8 ? two_idy : 1.0);
       const double sy = (ay[r] + red[oy][r][lane]) * (r >= 4 && r < 8 ? two_idx : 1.0);
-      hs[(size_t)(16 * fx + r) * nc + cell] = sx;
-      hs[(size_t)(16 * fy + r) * nc + cell] = sy;
+      hs[sum_at<true>(P, fx, r) + cell] = sx;
+      hs[sum_at<false>(P, fy, r) + cell] = sy;
     }
     if constexpr (kShak) {
-      hs[(size_t)(kSlotHeat + fx) * nc + cell] = ax[16] + red[ox][16][lane];
-      hs[(size_t)(kSlotHeat + fy) * nc + cell] = ay[16] + red[oy][16][lane];
+      hs[sum_at<true>(P, fx, 16) + cell] = ax[16] + red[ox][16][lane];
+      hs[sum_at<false>(P, fy, 16) + cell] = ay[16] + red[oy][16][lane];
       if (q == 0) {
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-          hs[(size_t)(kSlotCell + r) * nc + cell] =
+          hs[cell_sum_at(P, r) + cell] =
               ((cm[r] + cellred[0][r][lane]) + cellred[1][r][lane]) + cellred[2][r][lane];
       }
     }
@@ -1058,20 +1068,15 @@ __device__ __forceinline__ Face<x> face_at(const KParams& P, long e) {
   f.gl = x && chan && f.i == 0;
   f.gr = x && chan && f.i == P.nx;
   f.wall = !x && chan && (f.j == 0 || f.j == P.ny);
-  const unsigned ghost = (unsigned)P.nx * P.ny + f.j;
+  const unsigned ghost = (unsigned)P.nc + f.j;
   if (x) {
     f.cl = f.gl ? ghost : (unsigned)(f.j * P.nx + wrap(f.i - 1, P.nx));
-    f.cr = f.gr ? ghost + P.ny : (unsigned)(f.j * P.nx + wrap(f.i, P.nx));
+    f.cr = f.gr ? ghost : (unsigned)(f.j * P.nx + wrap(f.i, P.nx));
   } else {
     f.cl = (unsigned)(wrap(f.j - 1, P.ny) * P.nx + f.i);
     f.cr = (unsigned)(wrap(f.j, P.ny) * P.nx + f.i);
   }
   return f;
-}
-
-// Slot of sum q towards face side s (16: the Shakhov model's heat sum) of a part of the sums.
-__device__ __forceinline__ long long slot_of(int s, int q) {
-  return q < 16 ? 16 * s + q : kSlotHeat + s;
 }
 
 // W of the cells (or ghosts) below and above a face, in its local frame.
@@ -1196,16 +1201,16 @@ __device__ __forceinline__ void face_direct(const Inst* __restrict__ I, const KP
   if (e >= (long)f.nf) return;
   // a wall takes the sums of its cell alone, which lies above the bottom and below the top
   const bool nol = f.wall && f.j == 0, nor = f.wall && f.j != 0;
-  auto sum_at = [&](int side, int q, unsigned c) {
-    return ldb((const UGKS_GLOBAL double*)I->hs + slot_of(side, q) * P.ncs, c * 8u);
+  auto sum = [&](int side, int q, unsigned c) {
+    return ldb((const UGKS_GLOBAL double*)I->hs + sum_at<kX>(P, side, q), c * 8u);
   };
   double S[16], T3 = 0.0, wl[4], wr[4];
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
-    const double a = sum_at(kX ? S_XP : S_YP, q, f.cl), c = sum_at(kX ? S_XM : S_YM, q, f.cr);
+    const double a = sum(kX ? S_XP : S_YP, q, f.cl), c = sum(kX ? S_XM : S_YM, q, f.cr);
     S[q] = nol ? c : (nor ? a : a + c);
   }
-  if (P.shak) T3 = sum_at(kX ? S_XP : S_YP, 16, f.cl) + sum_at(kX ? S_XM : S_YM, 16, f.cr);
+  if (P.shak) T3 = sum(kX ? S_XP : S_YP, 16, f.cl) + sum(kX ? S_XM : S_YM, 16, f.cr);
   face_sides(I, P, parity, f, wl, wr);
   face_record(I, P, step_dt(P, parity), f, S, T3, wl, wr);
 }
@@ -1401,7 +1406,6 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
   // above it; 32, 33: their heat sums), up to kParts parts at a time (past the last part it is
   // read again and not added).  With kF = 64 a wavefront's sum is uniform and its slot goes into
   // the base; else the slot is a lane's, in the 32-bit offset (the plan sees to the size).
-  const long long part = (long long)P.nslot * P.ncs;
   auto add = [&](int u0, auto count_c, auto parts_c) {
     constexpr int kN = decltype(count_c)::value, kParts = decltype(parts_c)::value;
     const UGKS_GLOBAL double* base[kN];
@@ -1411,11 +1415,11 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
     for (int it = 0; it < kN; ++it) {
       const int u = u0 + it * kStep;
       const bool above = u < 32 ? u >= 16 : u == 33;
-      const long long slot = slot_of(above ? (kX ? S_XM : S_YM) : (kX ? S_XP : S_YP),
-                                     u < 32 ? u & 15 : 16);
+      const long long first = sum_at<kX>(P, above ? (kX ? S_XM : S_YM) : (kX ? S_XP : S_YP),
+                                         u < 32 ? u & 15 : 16);
       const unsigned c = above ? f.cr : f.cl;
-      base[it] = I->hs + (kSub == 1 ? slot * P.ncs : 0);
-      off[it] = ((kSub == 1 ? 0u : (unsigned)(slot * P.ncs)) + c) * 8u;
+      base[it] = I->hs + (kSub == 1 ? first : 0);
+      off[it] = ((kSub == 1 ? 0u : (unsigned)first) + c) * 8u;
       a[it] = 0.0;
     }
     long long at = 0;
@@ -1425,7 +1429,7 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
       for (int k = 0; k < kParts; ++k) {
 #pragma unroll
         for (int it = 0; it < kN; ++it) v[it][k] = ldb(base[it] + at, off[it]);
-        at += g0 + k + 1 < n ? part : 0;
+        at += g0 + k + 1 < n ? P.part : 0;
       }
 #pragma unroll
       for (int k = 0; k < kParts; ++k) {
@@ -1506,15 +1510,14 @@ __attribute__((amdgpu_waves_per_eu(2))) void faces_kernel_chunks(const Inst* ins
     return;
   }
   const int n = I->gsplit * P.NC;
-  const size_t nc = (size_t)P.ncs;
-  const size_t e = (size_t)(local - bx - by) * (kWave * kNW) + threadIdx.x;
-  if (e >= (size_t)(kSlotsShakhov - kSlotCell) * nc) return;
-  UGKS_GLOBAL double* at = I->hs + (size_t)kSlotCell * nc + e;
+  const long long e = (long long)(local - bx - by) * (kWave * kNW) + threadIdx.x;
+  if (e >= (kSlotsShakhov - kSlotCell) * P.nc) return;
+  UGKS_GLOBAL double* at = I->hs + cell_sum_at(P, 0) + e;
   double x = at[0];
   for (int g0 = 1; g0 < n; g0 += 8) {
     double v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = g0 + k < n ? at[(size_t)(g0 + k) * P.nslot * nc] : 0.0;
+    for (int k = 0; k < 8; ++k) v[k] = g0 + k < n ? at[(g0 + k) * P.part] : 0.0;
 #pragma unroll
     for (int k = 0; k < 8; ++k)
       if (g0 + k < n) x += v[k];
@@ -2357,8 +2360,8 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
     }
     if constexpr (kShak) {
       // heat flux of f^n about U^n from the cell's raw moments (moment kernel, chunk 0)
-      const size_t nc = (size_t)P.ncs;
-      const UGKS_GLOBAL double* cm = I->hs + (size_t)kSlotCell * nc + cc;
+      const size_t nc = (size_t)P.nc;
+      const UGKS_GLOBAL double* cm = I->hs + cell_sum_at(P, 0) + cc;
       double m[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) m[k] = valid ? cm[(size_t)k * nc] : 0.0;
@@ -2722,7 +2725,7 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
     t.upd += ((P.nx + kTileU - 1) / kTileU) * ((P.ny + 1) / 2) * img[q].usplit * P.vsplit * P.NC;
     if (G > 1)
       t.red += (nfx + t.red_faces - 1) / t.red_faces + (nfy + t.red_faces - 1) / t.red_faces +
-               (P.shak ? ((kSlotsShakhov - kSlotCell) * (int)P.ncs + kWave * t.red_waves - 1) /
+               (P.shak ? ((kSlotsShakhov - kSlotCell) * (int)P.nc + kWave * t.red_waves - 1) /
                              (kWave * t.red_waves)
                        : 0);
     else

@@ -234,6 +234,15 @@ void batch_workgroups() {
   ugks_batch_destroy(b);
 }
 
+// The transient buffers of 4 x 10000 cells, 46.6 MB with 17 sums for each ghost cell, fit the static
+// scratch.
+void static_scratch() {
+  Problem p(4, 10000, 2, 2);
+  ugks_handle* h = p.create();
+  check(ugks_step_static(h, 1) == UGKS_OK, ugks_last_error(h));
+  ugks_destroy(h);
+}
+
 // Host memory runs out while the copying threads start: the images are moved all the same.
 std::atomic<int> allocations_left{1 << 30};  // of the library that still succeed
 void threads_that_do_not_start() {
@@ -276,6 +285,7 @@ int main(int argc, char** argv) {
       {"under_capture", under_capture},
       {"one_solver_at_a_time", one_solver_at_a_time},
       {"batch_workgroups", batch_workgroups},
+      {"static_scratch", static_scratch},
       {"threads_that_do_not_start", threads_that_do_not_start},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");

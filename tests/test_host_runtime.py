@@ -20,6 +20,7 @@ CASES = [
     "under_capture",
     "one_solver_at_a_time",
     "batch_workgroups",
+    "static_scratch",
     "threads_that_do_not_start",
 ]
 
