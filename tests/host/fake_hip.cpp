@@ -118,6 +118,11 @@ std::map<const void*, std::string>& kernels() {
   return *k;
 }
 
+std::set<std::string>& names() {
+  static auto* n = new std::set<std::string>;
+  return *n;
+}
+
 void pause_us(int us) {
   if (us > 0) std::this_thread::sleep_for(std::chrono::microseconds(us));
 }
@@ -185,6 +190,10 @@ void moments(const double* W, int n, double lam_c, const int* flag, double* out,
 
 namespace fake {
 hipStream_t make_stream(int device) { return reinterpret_cast<hipStream_t>(new Stream(device)); }
+std::set<std::string> launched() {
+  std::lock_guard<std::mutex> lock(g_m);
+  return names();
+}
 void begin_capture(hipStream_t s) { at(s).capturing = true; }
 int end_capture(hipStream_t s) {
   Stream& st = at(s);
@@ -227,6 +236,10 @@ hipError_t hipLaunchKernel(const void* func, dim3 grid, dim3, void** args, size_
   const std::string& name = kernels()[func];
   auto is = [&](const char* part) { return name.find(part) != std::string::npos; };
   const bool f32 = is("If");
+  {
+    std::lock_guard<std::mutex> lock(g_m);
+    names().insert(name);
+  }
   if (is("sums_kernel") || is("update_kernel")) {
     // a workgroup for each segment of 62 (update: 60) cells of a row (of two) and each chunk
     const bool sums = is("sums_kernel");

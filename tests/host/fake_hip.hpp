@@ -9,6 +9,8 @@
 
 #include <atomic>
 #include <cstddef>
+#include <set>
+#include <string>
 
 namespace fake {
 
@@ -29,6 +31,8 @@ struct Counts {
 extern Counts counts;
 
 hipStream_t make_stream(int device);
+// The (mangled) names of the kernels launched so far.
+std::set<std::string> launched();
 void begin_capture(hipStream_t s);
 // Ends the capture; the number of operations the stream was given since.
 int end_capture(hipStream_t s);

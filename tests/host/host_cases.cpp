@@ -9,6 +9,7 @@
 #include <map>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "fake_hip.hpp"
@@ -243,6 +244,49 @@ void static_scratch() {
   ugks_destroy(h);
 }
 
+// Host threads with a solver and a stream each go through the shared pool: every image and every set
+// of moments is the caller's own.
+void threads_share_the_pool() {
+  fake::knobs.image_us = 200;
+  std::atomic<int> wrong{0};
+  auto work = [&wrong](int t) {
+    for (int round = 0; round < 3; ++round) {
+      Problem p = t % 2 ? Problem(43, 31, 40, 41) : Problem(40, 10, 24, 24);
+      ugks_handle* h = p.create(fake::make_stream(0));
+      std::vector<double> f(p.values()), g(p.values()), W(4 * p.cells()), m(4 * p.cells());
+      for (size_t k = 0; k < f.size(); ++k) f[k] = 1e6 * (t + 1) + (double)(k % 100003);
+      for (int n = 0; n < 3; ++n) {
+        if (ugks_set_state(h, f.data(), nullptr) != UGKS_OK || ugks_step(h, 1) != UGKS_OK ||
+            ugks_moments(h, m.data()) != UGKS_OK ||
+            ugks_get_state(h, g.data(), W.data()) != UGKS_OK || !shifted(f, g, 1.0))
+          ++wrong;
+        for (size_t c = 0; c < p.cells(); ++c)
+          if (m[4 * c] != W[4 * c]) ++wrong;
+      }
+      ugks_destroy(h);
+    }
+  };
+  std::vector<std::thread> th;
+  for (int t = 0; t < 4; ++t) th.emplace_back(work, t);
+  for (auto& t : th) t.join();
+  check(wrong == 0, "images and moments of several threads");
+  check(fake::counts.misuse == 0, "no block given back early");
+  check(fake::counts.pinned_live <= 1, "blocks kept without a solver");
+}
+
+// Prints the kernels of one step: nx ny nu nv fp32 dof prandtl bc.
+void kernels(char** argv) {
+  Problem p(std::atoi(argv[0]), std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]));
+  p.o.precision = std::atoi(argv[4]) ? UGKS_FP32_STORE : UGKS_FP64;
+  p.vg.internal_dof = std::atoi(argv[5]);
+  p.o.prandtl = std::atof(argv[6]);
+  p.bc.kind = std::atoi(argv[7]);
+  ugks_handle* h = p.create();
+  check(ugks_step(h, 1) == UGKS_OK, "step");
+  for (const std::string& name : fake::launched()) std::printf("%s\n", name.c_str());
+  ugks_destroy(h);
+}
+
 // Host memory runs out while the copying threads start: the images are moved all the same.
 std::atomic<int> allocations_left{1 << 30};  // of the library that still succeed
 void threads_that_do_not_start() {
@@ -286,11 +330,16 @@ int main(int argc, char** argv) {
       {"one_solver_at_a_time", one_solver_at_a_time},
       {"batch_workgroups", batch_workgroups},
       {"static_scratch", static_scratch},
+      {"threads_share_the_pool", threads_share_the_pool},
       {"threads_that_do_not_start", threads_that_do_not_start},
   };
   const auto it = cases.find(argc > 1 ? argv[1] : "");
-  if (it == cases.end()) return 2;
-  it->second();
+  if (it != cases.end())
+    it->second();
+  else if (argc == 10 && std::strcmp(argv[1], "kernels") == 0)
+    kernels(argv + 2);
+  else
+    return 2;
   std::printf("%s: %s\n", argv[1], failures ? "FAILED" : "ok");
   std::fflush(stdout);
   std::_Exit(failures ? 1 : 0);  // the streams' threads never end

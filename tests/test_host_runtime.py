@@ -7,6 +7,9 @@ import subprocess
 import pytest
 
 from paper_1810_08137_amd import ugks
+from tests import test_gpu_face_chunks as FACES
+from tests import test_gpu_update_nodes as NODES
+from tests import test_gpu_update_nodes_more as MORE
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests", "host")
@@ -21,6 +24,7 @@ CASES = [
     "one_solver_at_a_time",
     "batch_workgroups",
     "static_scratch",
+    "threads_share_the_pool",
     "threads_that_do_not_start",
 ]
 
@@ -45,3 +49,30 @@ def program(tmp_path_factory):
 def test_host_code(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def _kernels(program, nx, ny, nu, nv, precision="fp64", dof=0, prandtl=1.0, bc=1):
+    """Names of the kernels that one step of such a solver launches."""
+    r = subprocess.run([program, "kernels"] + [str(x) for x in (
+        nx, ny, nu, nv, int(precision == "fp32_store"), dof, prandtl, bc)],
+        capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+# of tests/test_gpu_update_nodes.py: its second form (four nodes in a line: nothing to split) and its
+# fifth take whole lines
+@pytest.mark.parametrize("form,by_node", list(zip(
+    NODES.FORMS + MORE.FORMS, [True, False, True, True, False, True] + [True] * len(MORE.FORMS))),
+    ids=str)
+def test_which_solvers_split_their_update_chunks_by_node(program, form, by_node):
+    assert ("update_kernel_nodes" in _kernels(program, **form)) == by_node
+
+
+@pytest.mark.parametrize("form", FACES.FORMS, ids=str)
+@pytest.mark.parametrize("mesh,faces,waves", list(zip(
+    FACES.MESHES, [16, 16, 32, 64, 32, 64, 64], [8, 8, 8, 8, 8, 4, 8])), ids=str)
+def test_which_interface_kernel_a_mesh_takes(program, mesh, faces, waves, form):
+    names = _kernels(program, *mesh, 16, 18, **form)
+    assert f"faces_kernel_chunksILi{faces}ELi{waves}E" in names
+    assert names.count("faces_kernel") == 1
