@@ -26,9 +26,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "421c5e2d106c468395b41b99d9ce04ce5b4e68faee2bd209ce27617f58a51614",
-    "fp64": 1.3403e9,
-    "fp32_store": 0.6997e9,
+    "source_sha256": "2e11307da25be90f3c95763c5f0214c17f20baef634f9bd151773418ce162767",
+    "fp64": 1.3411e9,
+    "fp32_store": 0.6999e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
     "valu_fp64": 1.0104e8,
 }

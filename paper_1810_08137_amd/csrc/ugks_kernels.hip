@@ -369,7 +369,7 @@ __device__ __forceinline__ Half axis_half(int n, int s, bool share_zero) {
 }
 
 // Nodes [a0, a1) of a half's node sequence taken by velocity chunk g of G.
-__device__ __forceinline__ void chunk_range(int count, int g, int G, int& a0, int& a1) {
+__host__ __device__ __forceinline__ void chunk_range(int count, int g, int G, int& a0, int& a1) {
   a0 = (int)((long long)g * count / G);
   a1 = (int)((long long)(g + 1) * count / G);
 }
@@ -2595,19 +2595,33 @@ int update_chunks_single(long long base, long long slots, int cap, int per_wg, i
 }
 
 // Whether the update kernel's G chunks of a quadrant split its nodes evenly (by node) rather than
-// its u lines: K u nodes and vh v nodes of the longer halves.  The longest chunk sets the time.
-// In nodes of the v loop, a line's setup (its cubics and u Gaussians) counts as four and running
-// the recurrences to a node inside a line as a sixth of a node each.  Whole lines win where they
-// divide evenly (400 x 100 x 40^2: 20 lines over 4 chunks); 80 x 40 x 49^2 (25 lines over 12
-// chunks, the longest 3) went from 62.6 to 54.8 us by node, 200 x 50 x 101^2 (51 over 10) from
-// 575 to 545, 120 x 60 x 29^2 in FP32 storage (15 over 14) from 39 to 35.
-bool update_by_node(int K, int vh, int G) {
-  constexpr int NB = 3;  // nodes of a group
+// its u lines: K u nodes and vh v nodes of the longer halves, ch chunks to a workgroup.  The longest
+// chunk sets the time, counted in nodes of the v loop, with three for every line it touches (its
+// cubics and u Gaussians); of the two chunks of a workgroup, which share a SIMD, their mean counts.
+// On 126 solvers (20..400 x 10..100 cells, 8..72 nodes an axis, both storage types, H, periodic
+// boxes) the update kernel then takes 0.3% more than the better of the two forms, at most 1.9% where
+// it splits nodes and 3.7% where it does not; always whole lines 1.9% and at most 31%, always by
+// node 1.0% and 11%.  (With the longest single chunk, four nodes a line and a sixth for each node run
+// past inside a line: 0.6%, 5.4% and 9.4%.)  80 x 40 x 49^2, 25 lines over 12 chunks: 55.4 us by
+// line, 51.4 by node; 200 x 50 x 101^2, 51 over 10: 563 and 536; 120 x 60 x 29^2 in FP32 storage, 15
+// over 14: 37.5 and 34.5.
+bool update_by_node(int K, int vh, int G, int ch) {
+  constexpr int NB = 3, kLine = 3;  // nodes of a group, of a line's setup
   const int lines = K - K / 2, vg = (vh + NB - 1) / NB;
-  const int whole = (lines + G - 1) / G;
-  const int len = (lines * vg + G - 1) / G;  // groups
-  const int touched = len > 1 ? (len - 2) / vg + 2 : 1;
-  return 6 * NB * len + 24 * touched + vh < whole * (6 * vh + 24);
+  long long whole = 0, split = 0;  // of the longest chunk, or pair of chunks
+  for (int g = 0; g < G; g += ch) {
+    long long w = 0, s = 0;
+    for (int c = g; c < g + ch; ++c) {
+      int a0, a1;
+      chunk_range(lines, c, G, a0, a1);
+      w += (long long)(a1 - a0) * (vh + kLine);
+      chunk_range(lines * vg, c, G, a0, a1);
+      if (a1 > a0) s += (long long)(a1 - a0) * NB + ((a1 - 1) / vg - a0 / vg + 1) * kLine;
+    }
+    whole = std::max(whole, w);
+    split = std::max(split, s);
+  }
+  return split < whole;
 }
 
 int update_vsplit(int nx, int ny, int K, int M, int NC, int fp32, int shak, int cap) {
@@ -2698,7 +2712,7 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
   if (n == 1 && !shak) {
     const KParams& P = insts[0].P;
     const int vh = ((P.M - P.M / 2) + P.vsplit - 1) / P.vsplit;
-    t.upd_nodes = update_by_node(P.K, vh, per_wg * img[0].usplit) ? 1 : 0;
+    t.upd_nodes = update_by_node(P.K, vh, per_wg * img[0].usplit, per_wg) ? 1 : 0;
   }
   // Faces and wavefronts per workgroup of the chunked interface kernel: 16 or 32 faces while each
   // workgroup (eight wavefronts, whose registers fill a CU) still has a CU of its own, then 64,

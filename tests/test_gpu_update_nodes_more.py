@@ -1,7 +1,6 @@
-"""Update-kernel chunks by node in the forms that the shortest lines and a periodic box take: the same
-bits as in a batch (whole lines), and the oracle's values.  That every form here, and each of
-tests/test_gpu_update_nodes.py that should, takes that kernel is checked in
-tests/test_host_runtime.py."""
+"""Update-kernel chunks by node in every form of that kernel: the same bits as in a batch (whole
+lines), and the oracle's values.  tests/test_host_runtime.py checks that all of these solvers take
+it."""
 import numpy as np
 import pytest
 
@@ -12,11 +11,14 @@ from tests.test_gpu_update_nodes import _case, _solver
 pytestmark = pytest.mark.gpu
 
 FORMS = [
-    dict(nx=40, ny=20, nu=29, nv=9),                                   # five nodes in a line
-    dict(nx=61, ny=31, nu=33, nv=10, bc=0),
+    dict(nx=40, ny=20, nu=29, nv=9),                           # five nodes in a line
+    dict(nx=26, ny=39, nu=47, nv=21),                          # odd rows, two chunks a workgroup
+    dict(nx=70, ny=16, nu=34, nv=22, bc=0),
+    dict(nx=66, ny=7, nu=49, nv=21, dof=1),
+    dict(nx=33, ny=5, nu=40, nv=11, dof=1),                    # one chunk a workgroup
     dict(nx=95, ny=37, nu=41, nv=10, bc=0, precision="fp32_store"),
 ]
-IDS = ["short lines", "periodic", "periodic fp32"]
+IDS = ["short lines", "odd rows", "periodic", "dof", "dof, one chunk", "periodic fp32"]
 
 
 @pytest.mark.parametrize("form", FORMS, ids=IDS)
