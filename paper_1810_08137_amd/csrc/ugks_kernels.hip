@@ -640,8 +640,8 @@ __global__ __launch_bounds__(kWave* kQuads) void sums_kernel(const Inst* inst, c
         n2 = wp[wstep + 2];
         n3 = wp[wstep + 3];
         n4 = wp[wstep + 4];
-      } else {  // FP32 storage: read at the node (holding the next node's weights would cost
-                // this kernel its fourth wave per SIMD)
+      } else {  // FP32 storage: read at the node (with the next node's held, 600 x 300 x 24^2 took
+                // 195 us instead of 191, 120 x 60 x 29^2 20.5 instead of 20.0)
         w0 = wp[0];
         w1 = wp[1];
         w2 = wp[2];
@@ -2009,9 +2009,9 @@ __device__ __forceinline__ void pair_quadrant(const KParams& P, const PairStage<
 // checkpoint steps on exactly as a running solver does.
 template <typename S, int SU>
 __device__ __forceinline__ void ghost_fill_quadrant(const KParams& P, const PairStage<S>& st,
-                                                    const CellFactors<S>* qg, int lane, int sv, int jb, bool store0,
-                                                    int g, int G, int gv, int Gv, bool ghost_w,
-                                                    UGKS_GLOBAL S* f, int i) {
+                                                    const CellFactors<S>* qg, int lane, int sv,
+                                                    int jb, bool store0, int g, int G, int gv,
+                                                    int Gv, bool ghost_w, UGKS_GLOBAL S* f, int i) {
   typedef S T;
   const int r0 = sv > 0 ? 0 : 1, r1 = 1 - r0;
   const int j0 = jb + r0;
@@ -2407,7 +2407,8 @@ __device__ __forceinline__ void update_body(const Inst* inst, const int* off, in
         T* e = u < kPair ? st.xs[h][u][0] : st.ys[h][u - kPair][0];
         T* r = u < kPair ? st.xs[h][u][1] : st.ys[h][u - kPair][1];
         start(flam[n], fvel[n], h, e, r, lane);
-        if (h == 0) (u < kPair ? st.qx[u] : st.qy[u - kPair])[lane] = second_factor<T>(hstep, flam[n]);
+        if (h == 0)
+          (u < kPair ? st.qx[u] : st.qy[u - kPair])[lane] = second_factor<T>(hstep, flam[n]);
       }
     }
   }
@@ -2453,8 +2454,9 @@ void update_kernel(const Inst* inst, const int* off, int ninst, int step) {
 }
 
 // The chunks of this form split a quadrant's nodes instead of its u lines (update_by_node).  A
-// kernel of its own: the few registers it takes more would spill in the FP32-storage form
-// (400 x 100 x 40^2, which takes whole lines: 181 us without, 188 us with it).
+// kernel of its own: it takes a few registers more, and in FP32 storage spills two of them (12 bytes
+// of scratch a lane), which would cost the solvers that take whole lines (400 x 100 x 40^2: 181 us
+// without, 188 us with it).
 template <typename S, int kCh>
 __global__ __launch_bounds__(kWave* kQuads* kCh)
 __attribute__((amdgpu_waves_per_eu(kUpdateWaves<S, false>)))
@@ -2484,8 +2486,9 @@ void ghost_fill_kernel(const Inst* inst, const int* off, int ninst, int step) {
 // a row, the host image (pinned memory, accessed over the host link) in 64 velocities of a
 // cell, 512 contiguous bytes each way.  Bound by the host link and the host's copy to or from the
 // caller's buffer: reading and setting the state of 80 x 40 cells at 29^2 (21.5 MB) takes 1.6 ms
-// with a step on either side, 13.8 ms when the host did the transpose.  The piece: cells [c0, c0 + ncell) by velocities [v0, v0 + nvel) of the NC NV
-// values of a cell, at img[(c - c0) nvel + v - v0].
+// with a step on either side, 13.8 ms when the host did the transpose.  The piece: cells
+// [c0, c0 + ncell) by velocities [v0, v0 + nvel) of the NC NV values of a cell, at
+// img[(c - c0) nvel + v - v0].
 constexpr int kTile = 64;
 template <typename S, bool kOut>
 __global__ __launch_bounds__(256) void state_kernel(UGKS_GLOBAL S* f, KParams P, long long c0,
