@@ -124,11 +124,10 @@ void* scratch_address(int device, std::string& why) {
 }
 
 // Pinned host blocks through which the state goes between the planes and the caller's buffers, at
-// most kPinnedKept of them kept while a handle or a batch lives.  The last handle gives back all but
-// one: allocating and freeing a block takes 50 us, and a process with one solver at a time (40 x 10
-// cells: created, its moments read, closed) took 173 us for each when none stayed, 118 with one
-// kept.  A block belongs to one call from get to put, so calls on any threads and streams share the
-// pool.
+// most kPinnedKept of them kept while a handle or a batch lives.  The last handle gives back all
+// but one: allocating and freeing a block takes 50 us, which a process with one solver at a time
+// would pay for each.  A block belongs to one call from get to put, so calls on any threads and
+// streams share the pool.
 constexpr size_t kPinnedBytes = (size_t)2 << 20;
 constexpr int kPinnedKept = 8;
 class PinnedPool {
@@ -1090,26 +1089,50 @@ int ugks_create(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, const
     }
   }
 
+  // The tables, the flag (clear) and the plans lie next to each other in the workspace and go up in
+  // one copy, W of the initial state in another, both through a pinned block as far as it holds them
+  // (a solver of 40 x 10 cells is created in 64 us, of 120 x 60 in 173; with ten copies of their own
+  // from pageable memory 106 and 187, where other programs use the GPU 290, with ten through a block
+  // 103 and 199).
   Copy copies[10];
   int nt = table_copies(B, T, s, copies);
   copies[nt++] = {B.xi_in, xi.data(), xi.size() * 8};
-  copies[nt++] = {B.W[0], W0.data(), W0.size() * 8};
   // rmax[0] of the initial state (adaptive step), rmax[1] and the simulated time zero
   const unsigned long long rmax_tsum[3] = {rate_bits(P, W0.data(), s.nc), 0ull, 0ull};
   copies[nt++] = {B.rmax, rmax_tsum, sizeof rmax_tsum};
   copies[nt++] = {h->plan_dev, plan_host.data(), plan_host.size()};
-  if (h->static_ok) copies[nt++] = {h->plan_static, plan_static_host.data(), plan_static_host.size()};
+  if (h->static_ok)
+    copies[nt++] = {h->plan_static, plan_static_host.data(), plan_static_host.size()};
+  char* const tables_dev = reinterpret_cast<char*>(B.wk);
+  const size_t tables_n = L.total - L.off[8], W0_n = W0.size() * 8;
+  std::unique_ptr<char[]> pageable;
+  char* blk = nullptr;
   int rc = UGKS_OK;
   e = can_wait(h->stream);
-  if (e != hipSuccess) rc = hip_fail(nullptr, e, "waiting for the initial state");
-  for (int c = 0; c < nt && rc == UGKS_OK; ++c) {
-    e = hipMemcpyAsync(copies[c].dst, copies[c].src, copies[c].n, hipMemcpyHostToDevice, h->stream);
-    if (e != hipSuccess) rc = hip_fail(nullptr, e, "hipMemcpyAsync of the tables");
-  }
-  if (rc == UGKS_OK) {
-    e = hipMemsetAsync(B.flag, 0, sizeof(int), h->stream);
-
-    if (e != hipSuccess) rc = hip_fail(nullptr, e, "hipMemsetAsync of the state flag");
+  if (e != hipSuccess) {
+    rc = hip_fail(nullptr, e, "waiting for the initial state");
+  } else {
+    blk = static_cast<char*>(g_pinned.get());
+    char* img = blk;
+    if (!blk || tables_n > kPinnedBytes) {
+      pageable.reset(new (std::nothrow) char[tables_n]);
+      img = pageable.get();
+    }
+    if (!img) {
+      rc = fail(nullptr, UGKS_E_NOMEM, "host allocation failed%s");
+    } else {
+      std::memset(img, 0, tables_n);
+      for (int c = 0; c < nt; ++c)
+        std::memcpy(img + (static_cast<char*>(copies[c].dst) - tables_dev), copies[c].src,
+                    copies[c].n);
+      const size_t at = img == blk ? round_up(tables_n, 64) : 0;
+      const void* W0_src = W0.data();
+      if (blk && at + W0_n <= kPinnedBytes) W0_src = std::memcpy(blk + at, W0.data(), W0_n);
+      e = hipMemcpyAsync(tables_dev, img, tables_n, hipMemcpyHostToDevice, h->stream);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(B.W[0], W0_src, W0_n, hipMemcpyHostToDevice, h->stream);
+      if (e != hipSuccess) rc = hip_fail(nullptr, e, "hipMemcpyAsync of the tables");
+    }
   }
   if (rc == UGKS_OK) {
     // the halo rows and columns start at zero; in a channel only the ghost columns are
@@ -1128,6 +1151,7 @@ int ugks_create(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, const
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) rc = hip_fail(nullptr, e, "initial state");
   }
+  put_block(blk, e, h->stream);
   if (rc != UGKS_OK) {
     if (h->owns_ws) (void)hipFree(h->ws);
     delete h;
