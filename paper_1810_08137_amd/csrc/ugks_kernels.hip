@@ -328,9 +328,9 @@ __device__ __forceinline__ long long cell_sum_at(const KParams& P, int r) {
   return (kSlotCell + r) * P.nc + 34LL * P.ny;
 }
 
-// Workgroups are handed to the 8 XCDs round-robin; renumber the n of one instance so that each XCD
+// Workgroups are handed to the 8 938Ds round-robin; renumber the n of one instance so that each 938D
 // works through one contiguous range of them (its own L2 then serves the rows its neighbours also
-// read) and all XCDs work on every instance.  Which XCD its first block falls on does not matter:
+// read) and all 938Ds work on every instance.  Which 938D its first block falls on does not matter:
 // blocks 8 apart share one.  (With every instance filled up to a multiple of 8 blocks, a step of 256
 // solves of 4..8 x 3..6 cells at 8^2 took 149 us, without 107; of 16 of 60..135 x 20..35 at 24..32 x
 // 24 404 and 367.)
@@ -375,9 +375,9 @@ __host__ __device__ __forceinline__ void chunk_range(int count, int g, int G, in
 }
 
 // Workgroup L of a cell kernel: row segment t (fastest), row j, velocity chunk g.  The
-// workgroups an XCD runs at once then cover whole rows of a band of neighbouring rows, so the
+// workgroups an 938D runs at once then cover whole rows of a band of neighbouring rows, so the
 // cache lines a segment shares with the next one, and the rows j +- 1, j +- 2 it reads, come
-// from that XCD's L2.
+// from that 938D's L2.
 __device__ __forceinline__ void cell_block(int L, int ny, int ntx, int& t, int& g, int& j) {
   t = L % ntx;
   const int r = L / ntx;
@@ -2598,28 +2598,30 @@ int update_chunks_single(long long base, long long slots, int cap, int per_wg, i
 }
 
 // Whether the update kernel's G chunks of a quadrant split its nodes evenly (by node) rather than
-// its u lines: K u nodes and vh v nodes of the longer halves, ch chunks to a workgroup.  The longest
-// chunk sets the time, counted in nodes of the v loop, with three for every line it touches (its
-// cubics and u Gaussians); of the two chunks of a workgroup, which share a SIMD, their mean counts.
-// On 126 solvers (20..400 x 10..100 cells, 8..72 nodes an axis, both storage types, H, periodic
-// boxes) the update kernel then takes 0.3% more than the better of the two forms, at most 1.9% where
-// it splits nodes and 3.7% where it does not; always whole lines 1.9% and at most 31%, always by
-// node 1.0% and 11%.  (With the longest single chunk, four nodes a line and a sixth for each node run
-// past inside a line: 0.6%, 5.4% and 9.4%.)  80 x 40 x 49^2, 25 lines over 12 chunks: 55.4 us by
-// line, 51.4 by node; 200 x 50 x 101^2, 51 over 10: 563 and 536; 120 x 60 x 29^2 in FP32 storage, 15
-// over 14: 37.5 and 34.5.
-bool update_by_node(int K, int vh, int G, int ch) {
-  constexpr int NB = 3, kLine = 3;  // nodes of a group, of a line's setup
+// its u lines: K u nodes and vh v nodes of the longer halves, the latter one of Gv chunks, ch chunks
+// to a workgroup.  The longest chunk sets the time, counted in nodes of the v loop, with four for
+// every line it touches (its cubics and u Gaussians); of the two chunks of a workgroup, which share
+// a SIMD, their mean counts, except where v is in chunks as well: these are short and wait for
+// latency more than for one another.  On 129 solvers (20..400 x 10..100 cells, 8..101 nodes an axis,
+// both storage types, H, periodic boxes) a step then takes 0.14% more than with the better of the two
+// forms, at most 1.8%; always whole lines 1.1% and at most 17%, always by node 0.7% and 5%.  (With
+// single chunks everywhere, and a sixth of a node for each node run past inside a line: 0.33% and
+// 4.8%.)  Steps by line and by node: 80 x 40 x 49^2, 25 lines over 12 chunks, 92.3 and 88.1 us;
+// 200 x 50 x 101^2, 51 over 10, 938 and 911; 120 x 60 x 29^2 in FP32 storage, 15 over 14, 64.0 and 61.3.
+bool update_by_node(int K, int vh, int Gv, int G, int ch) {
+  constexpr int NB = 3, kLine = 4;  // nodes of a group, of a line's setup
   const int lines = K - K / 2, vg = (vh + NB - 1) / NB;
-  long long whole = 0, split = 0;  // of the longest chunk, or pair of chunks
-  for (int g = 0; g < G; g += ch) {
-    long long w = 0, s = 0;
-    for (int c = g; c < g + ch; ++c) {
+  const int together = Gv > 1 ? 1 : ch;
+  auto nodes = [&](int group) { return group / vg * vh + std::min(group % vg * NB, vh); };
+  int whole = 0, split = 0;  // of the longest chunk, or chunks together
+  for (int g = 0; g < G; g += together) {
+    int w = 0, s = 0;
+    for (int c = g; c < g + together; ++c) {
       int a0, a1;
       chunk_range(lines, c, G, a0, a1);
-      w += (long long)(a1 - a0) * (vh + kLine);
+      w += (a1 - a0) * (vh + kLine);
       chunk_range(lines * vg, c, G, a0, a1);
-      if (a1 > a0) s += (long long)(a1 - a0) * NB + ((a1 - 1) / vg - a0 / vg + 1) * kLine;
+      if (a1 > a0) s += nodes(a1) - nodes(a0) + ((a1 - 1) / vg - a0 / vg + 1) * kLine;
     }
     whole = std::max(whole, w);
     split = std::max(split, s);
@@ -2653,8 +2655,8 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
   const size_t off_bytes = (((size_t)(n + 1) * sizeof(int) + 255) / 256) * 256;
   // The instances with the longest workgroups first (their nodes per quadrant), so that a launch
   // ends on short ones.  Twelve FP32-storage solves of the serving shapes (190M updates a step):
-  // 1174 us in the callers' order with one XCD range over all instances, 1022 with the range per
-  // instance (some XCDs had only long workgroups), 949 with this order as well.  More and smaller
+  // 1174 us in the callers' order with one 938D range over all instances, 1022 with the range per
+  // instance (some 938Ds had only long workgroups), 949 with this order as well.  More and smaller
   // chunks for the longer instances gained nothing further.
   Inst* img = reinterpret_cast<Inst*>(h);
   {
@@ -2715,7 +2717,7 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
   if (n == 1 && !shak) {
     const KParams& P = insts[0].P;
     const int vh = ((P.M - P.M / 2) + P.vsplit - 1) / P.vsplit;
-    t.upd_nodes = update_by_node(P.K, vh, per_wg * img[0].usplit, per_wg) ? 1 : 0;
+    t.upd_nodes = update_by_node(P.K, vh, P.vsplit, per_wg * img[0].usplit, per_wg) ? 1 : 0;
   }
   // Faces and wavefronts per workgroup of the chunked interface kernel: 16 or 32 faces while each
   // workgroup (eight wavefronts, whose registers fill a CU) still has a CU of its own, then 64,
