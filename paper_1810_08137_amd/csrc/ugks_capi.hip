@@ -832,7 +832,7 @@ void fill_constants(const ugks_mesh* mesh, const ugks_vgrid* vgrid, double kn, c
   P.q_c = 0.5 * (double)(2 + s.dof);
   P.a4_c = 4.0 / (double)(2 + s.dof);
   P.shak = shak ? 1 : 0;
-  P.nc = (long long)s.nc;
+  P.nc = (int)s.nc;
   P.part = (long long)hs_part(s.nc, (size_t)s.ny, shak);
   P.pr_c = shak ? 1.0 - opts->prandtl : 0.0;
   P.Lx = s.Lx;

@@ -72,7 +72,7 @@ struct KParams {
   double q_c;       // (2 + dof)/2: the energy row of the micro-slope solve, q2 = |U|^2 + q_c/lambda
   double a4_c;      // 4/(2 + dof): its energy coefficient, a4 = a4_c lambda^2/rho (...)
   int shak;         // Shakhov collision model (else BGK)
-  long long nc;     // cells, nx ny
+  int nc;           // cells, nx ny
   long long part;   // values of one chunk's moment sums (hs_part)
   double pr_c;      // 1 - Prandtl number (Shakhov)
   int Lx, Ly;       // padded row length and row count of a plane

@@ -320,12 +320,13 @@ __device__ __forceinline__ int plane_col(const KParams& P, int i) {
 // (hs_part).
 template <bool kX>
 __device__ __forceinline__ long long sum_at(const KParams& P, int s, int q) {
-  const long long first = q < 16 ? 16 * s + q : s;
-  const long long at = kX ? first * (P.nc + P.ny) : first * P.nc + (q < 16 ? 32LL : 2LL) * P.ny;
-  return q < 16 ? at : at + kSlotHeat * P.nc + 32LL * P.ny;
+  const int first = q < 16 ? 16 * s + q : s;
+  const long long at = kX ? (long long)first * (P.nc + P.ny)
+                          : (long long)first * P.nc + (q < 16 ? 32LL : 2LL) * P.ny;
+  return q < 16 ? at : at + (long long)kSlotHeat * P.nc + 32LL * P.ny;
 }
 __device__ __forceinline__ long long cell_sum_at(const KParams& P, int r) {
-  return (kSlotCell + r) * P.nc + 34LL * P.ny;
+  return (long long)(kSlotCell + r) * P.nc + 34LL * P.ny;
 }
 
 // Workgroups are handed to the 8 938Ds round-robin; renumber the n of one instance so that each 938D
@@ -1511,7 +1512,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void faces_kernel_chunks(const Inst* ins
   }
   const int n = I->gsplit * P.NC;
   const long long e = (long long)(local - bx - by) * (kWave * kNW) + threadIdx.x;
-  if (e >= (kSlotsShakhov - kSlotCell) * P.nc) return;
+  if (e >= (long long)(kSlotsShakhov - kSlotCell) * P.nc) return;
   UGKS_GLOBAL double* at = I->hs + cell_sum_at(P, 0) + e;
   double x = at[0];
   for (int g0 = 1; g0 < n; g0 += 8) {
