@@ -26,9 +26,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "ccf17ba9bc14dc2fc6dfbb49909a0d17037e1865c7c79e46825472458c8b8174",
-    "fp64": 1.3418e9,
-    "fp32_store": 0.6998e9,
+    "source_sha256": "773ce25a43c24b3174fe474ecd83b3d38112a5fadb377f41af90cb1342b4bd7f",
+    "fp64": 1.3377e9,
+    "fp32_store": 0.6991e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
     "valu_fp64": 1.0104e8,
 }

@@ -2601,23 +2601,28 @@ int update_chunks_single(long long base, long long slots, int cap, int per_wg, i
 // Whether the update kernel's G chunks of a quadrant split its nodes evenly (by node) rather than
 // its u lines: K u nodes and vh v nodes of the longer halves, the latter one of Gv chunks, ch chunks
 // to a workgroup.  The longest chunk sets the time, counted in nodes of the v loop, with four for
-// every line it touches (its cubics and u Gaussians); of the two chunks of a workgroup, which share
+// every line it touches (its cubics and u Gaussians).  Of the two chunks of a workgroup, which share
 // a SIMD, their mean counts, except where v is in chunks as well: these are short and wait for
-// latency more than for one another.  On 129 solvers (20..400 x 10..100 cells, 8..101 nodes an axis,
-// both storage types, H, periodic boxes) a step then takes 0.14% more than with the better of the two
-// forms, at most 1.8%; always whole lines 1.1% and at most 17%, always by node 0.7% and 5%.  (With
-// single chunks everywhere, and a sixth of a node for each node run past inside a line: 0.33% and
-// 4.8%.)  Steps by line and by node: 80 x 40 x 49^2, 25 lines over 12 chunks, 92.3 and 88.1 us;
-// 200 x 50 x 101^2, 51 over 10, 938 and 911; 120 x 60 x 29^2 in FP32 storage, 15 over 14, 64.0 and 61.3.
+// latency more than for one another, so the longest bound of a single one counts, a sixth of a node
+// for each run past inside a line included.  On 129 solvers (20..400 x 10..100 cells, 8..101 nodes
+// an axis, both storage types, H, periodic boxes) a step then takes 0.12% more than with the better
+// of the two forms, at most 1.8%; always whole lines 1.1% and at most 17%, always by node 0.7% and
+// 5%, with the bound of single chunks everywhere 0.33% and 4.8%.
+// Steps by line and by node: 80 x 40 x 49^2, 25 lines over 12 chunks, 92.3 and 88.1 us; 200 x 50 x
+// 101^2, 51 over 10, 938 and 911; 120 x 60 x 29^2 in FP32 storage, 15 over 14, 64.0 and 61.3.
 bool update_by_node(int K, int vh, int Gv, int G, int ch) {
   constexpr int NB = 3, kLine = 4;  // nodes of a group, of a line's setup
   const int lines = K - K / 2, vg = (vh + NB - 1) / NB;
-  const int together = Gv > 1 ? 1 : ch;
+  if (Gv > 1) {
+    const int len = (lines * vg + G - 1) / G;  // groups
+    const int touched = len > 1 ? (len - 2) / vg + 2 : 1;
+    return 6 * (NB * len + kLine * touched) + vh < 6 * ((lines + G - 1) / G) * (vh + kLine);
+  }
   auto nodes = [&](int group) { return group / vg * vh + std::min(group % vg * NB, vh); };
-  int whole = 0, split = 0;  // of the longest chunk, or chunks together
-  for (int g = 0; g < G; g += together) {
+  int whole = 0, split = 0;  // of the longest workgroup
+  for (int g = 0; g < G; g += ch) {
     int w = 0, s = 0;
-    for (int c = g; c < g + together; ++c) {
+    for (int c = g; c < g + ch; ++c) {
       int a0, a1;
       chunk_range(lines, c, G, a0, a1);
       w += (a1 - a0) * (vh + kLine);

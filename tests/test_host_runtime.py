@@ -76,6 +76,7 @@ MEASURED = [
     (dict(nx=94, ny=44, nu=71, nv=8, dof=1), False),                       # 88.3, 85.5
     (dict(nx=155, ny=80, nu=61, nv=11, precision="fp32_store"), False),    # 83.4, 80.1
     (dict(nx=57, ny=20, nu=51, nv=28, precision="fp32_store"), False),     # 45.5, 43.2
+    (dict(nx=70, ny=26, nu=11, nv=48, bc=0), False),                       # 46.1, 44.9
 ]
 
 
