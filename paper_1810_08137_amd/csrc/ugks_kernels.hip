@@ -1403,11 +1403,14 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
   const Face<kX> f = face_at<kX>(P, mine ? first + fl : nf - 1);
   double wl[4], wr[4];
   if (w < 2) face_sides(I, P, parity, f, wl, wr);
-  // Sums u0 + it kStep (u < 16: sum u of the cell below the face, else sum u - 16 of the cell
-  // above it; 32, 33: their heat sums), up to kParts parts at a time (past the last part it is
-  // read again and not added).  With kF = 64 a wavefront's sum is uniform and its slot goes into
-  // the base; else the slot is a lane's, in the 32-bit offset (the plan sees to the size).
-  auto add = [&](int u0, auto count_c, auto parts_c) {
+  // Sums u0 + it kStep from `first` on (u < half: sum u of the cell below the face, else sum u - half
+  // of the cell above it; those of one face family follow one another, stride values apart) into the
+  // rows of `out`, up to kParts parts at a time (past the last part it is read again and not added).
+  // With kF = 64 a wavefront's sum is uniform and its place goes into the base; else it is a lane's,
+  // in the 32-bit offset (the plan sees to the size).
+  const long long stride = kX ? P.nc + P.ny : P.nc;
+  auto add = [&](const UGKS_GLOBAL double* first, int half, double (*out)[kF], int u0,
+                 auto count_c, auto parts_c) {
     constexpr int kN = decltype(count_c)::value, kParts = decltype(parts_c)::value;
     const UGKS_GLOBAL double* base[kN];
     unsigned off[kN];
@@ -1415,12 +1418,9 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
 #pragma unroll
     for (int it = 0; it < kN; ++it) {
       const int u = u0 + it * kStep;
-      const bool above = u < 32 ? u >= 16 : u == 33;
-      const long long first = sum_at<kX>(P, above ? (kX ? S_XM : S_YM) : (kX ? S_XP : S_YP),
-                                         u < 32 ? u & 15 : 16);
-      const unsigned c = above ? f.cr : f.cl;
-      base[it] = I->hs + (kSub == 1 ? first : 0);
-      off[it] = ((kSub == 1 ? 0u : (unsigned)first) + c) * 8u;
+      const unsigned c = u >= half ? f.cr : f.cl;
+      base[it] = first + (kSub == 1 ? u * stride : 0);
+      off[it] = ((kSub == 1 ? 0u : (unsigned)(u * stride)) + c) * 8u;
       a[it] = 0.0;
     }
     long long at = 0;
@@ -1439,24 +1439,26 @@ __device__ __forceinline__ void faces_of_chunks(const Inst* __restrict__ I, cons
       }
     }
 #pragma unroll
-    for (int it = 0; it < kN; ++it) red[u0 + it * kStep][fl] = a[it];
+    for (int it = 0; it < kN; ++it) out[u0 + it * kStep][fl] = a[it];
   };
   using It = std::integral_constant<int, kIt>;
   const int u0 = w * kSub + sub;
+  const UGKS_GLOBAL double* sums = I->hs + sum_at<kX>(P, kX ? S_XP : S_YP, 0);
   if (n <= 2)
-    add(u0, It(), std::integral_constant<int, 2>());
+    add(sums, 16, red, u0, It(), std::integral_constant<int, 2>());
   else if (n <= 4)
-    add(u0, It(), std::integral_constant<int, 4>());
+    add(sums, 16, red, u0, It(), std::integral_constant<int, 4>());
   else if (n <= 6 || kIt == 8)
-    add(u0, It(), std::integral_constant<int, 6>());
+    add(sums, 16, red, u0, It(), std::integral_constant<int, 6>());
   else if (n <= 9)
-    add(u0, It(), std::integral_constant<int, 9>());
+    add(sums, 16, red, u0, It(), std::integral_constant<int, 9>());
   else if (n <= 12)
-    add(u0, It(), std::integral_constant<int, 12>());
+    add(sums, 16, red, u0, It(), std::integral_constant<int, 12>());
   else
-    add(u0, It(), std::integral_constant<int, 16>());
-  if (P.shak && w >= kNW - 2 && sub == 0)
-    add(32 + w - (kNW - 2), std::integral_constant<int, 1>(), std::integral_constant<int, 8>());
+    add(sums, 16, red, u0, It(), std::integral_constant<int, 16>());
+  if (P.shak && w >= kNW - 2 && sub == 0)  // the heat sums, in rows 32 and 33
+    add(I->hs + sum_at<kX>(P, kX ? S_XP : S_YP, 16), 1, red + 32, w - (kNW - 2),
+        std::integral_constant<int, 1>(), std::integral_constant<int, 8>());
   __syncthreads();
   const double dt = step_dt(P, parity);
   if (!P.collisionless) {
