@@ -27,8 +27,11 @@
  *     freedom, nc = 2 (c = 0: G, c = 1: H);
  *     W[(j*nx + i)*4 + q] with W = (rho, rho U, rho V, rho E).
  *   - Work is enqueued on the stream given in ugks_opts (hipStream_t; NULL = the default
- *     stream).  Only ugks_moments, ugks_get_state, ugks_set_state, ugks_get_face_flux,
- *     ugks_get_kernel_timing and ugks_destroy synchronise with it.
+ *     stream; the per-thread stream is that of the calling thread).  Only ugks_create,
+ *     ugks_moments, ugks_get_time, ugks_get_state, ugks_set_state, ugks_get_face_flux,
+ *     ugks_set_kernel_timing, ugks_get_kernel_timing and ugks_destroy synchronise with it.  While
+ *     the stream is being captured, those that return values or set them give UGKS_E_DEVICE and
+ *     enqueue nothing.
  *   - A handle may be used by one host thread at a time.
  */
 #ifndef UGKS_H
