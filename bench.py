@@ -26,9 +26,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector
 # known size.  Valid only for the kernel source whose SHA-256 is recorded; null otherwise.
 KERNEL_SOURCE = os.path.join(HERE, "paper_1810_08137_amd", "csrc", "ugks_kernels.hip")
 MEASURED_TRAFFIC = {
-    "source_sha256": "9b254c6e6196d4738fac1fdec0503ddcb20e2221020a6672284e420a2a5f7252",
-    "fp64": 1.3415e9,
-    "fp32_store": 0.7e9,
+    "source_sha256": "70d31534132b3048ef9cf4851df80c9b912b39474df3321ed7aa2383278d1da3",
+    "fp64": 1.342e9,
+    "fp32_store": 0.699e9,
     # SQ_INSTS_VALU per launch of the update kernel (wave instructions), same source
     "valu_fp64": 1.0104e8,
 }

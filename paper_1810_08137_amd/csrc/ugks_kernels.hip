@@ -329,12 +329,12 @@ __device__ __forceinline__ long long cell_sum_at(const KParams& P, int r) {
   return (long long)(kSlotCell + r) * P.nc + 34LL * P.ny;
 }
 
-// Workgroups are handed to the 8 938Ds round-robin; renumber the n of one instance so that each 938D
+// Workgroups are handed to the 8 XCDs round-robin; renumber the n of one instance so that each XCD
 // works through one contiguous range of them (its own L2 then serves the rows its neighbours also
-// read) and all 938Ds work on every instance.  Which 938D its first block falls on does not matter:
+// read) and all XCDs work on every instance.  Which XCD its first block falls on does not matter:
 // blocks 8 apart share one.  (With every instance filled up to a multiple of 8 blocks, a step of 256
-// solves of 4..8 x 3..6 cells at 8^2 took 149 us, without 107; of 16 of 60..135 x 20..35 at 24..32 x
-// 24 404 and 367.)
+// solves of 4..8 x 3..6 cells at 8^2 took 149 us, without 107; of 16 periodic ones of 60..135 x
+// 20..35 cells at 24..32 x 24 404 and 367.)
 constexpr int kXcd = 8;
 __device__ __forceinline__ int xcd_block(int local, int n) {
   const int q = n / kXcd, r = n % kXcd, x = local % kXcd, i = local / kXcd;
@@ -376,9 +376,9 @@ __host__ __device__ __forceinline__ void chunk_range(int count, int g, int G, in
 }
 
 // Workgroup L of a cell kernel: row segment t (fastest), row j, velocity chunk g.  The
-// workgroups an 938D runs at once then cover whole rows of a band of neighbouring rows, so the
+// workgroups an XCD runs at once then cover whole rows of a band of neighbouring rows, so the
 // cache lines a segment shares with the next one, and the rows j +- 1, j +- 2 it reads, come
-// from that 938D's L2.
+// from that XCD's L2.
 __device__ __forceinline__ void cell_block(int L, int ny, int ntx, int& t, int& g, int& j) {
   t = L % ntx;
   const int r = L / ntx;
@@ -2605,7 +2605,7 @@ int update_chunks_single(long long base, long long slots, int cap, int per_wg, i
 // to a workgroup.  The longest chunk sets the time, counted in nodes of the v loop, with four for
 // every line it touches (its cubics and u Gaussians).  Of the two chunks of a workgroup, which share
 // a SIMD, their mean counts, except where v is in chunks as well: these are short and wait for
-// latency more than for one another, so the longest bound of a single one counts, a sixth of a node
+// latency more than for one another, so a bound of the longest single one counts, a sixth of a node
 // for each run past inside a line included.  On 129 solvers (20..400 x 10..100 cells, 8..101 nodes
 // an axis, both storage types, H, periodic boxes) a step then takes 0.12% more than with the better
 // of the two forms, at most 1.8%; always whole lines 1.1% and at most 17%, always by node 0.7% and
@@ -2663,8 +2663,8 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
   const size_t off_bytes = (((size_t)(n + 1) * sizeof(int) + 255) / 256) * 256;
   // The instances with the longest workgroups first (their nodes per quadrant), so that a launch
   // ends on short ones.  Twelve FP32-storage solves of the serving shapes (190M updates a step):
-  // 1174 us in the callers' order with one 938D range over all instances, 1022 with the range per
-  // instance (some 938Ds had only long workgroups), 949 with this order as well.  More and smaller
+  // 1174 us in the callers' order with one XCD range over all instances, 1022 with the range per
+  // instance (some XCDs had only long workgroups), 949 with this order as well.  More and smaller
   // chunks for the longer instances gained nothing further.
   Inst* img = reinterpret_cast<Inst*>(h);
   {
@@ -2752,7 +2752,7 @@ PlanTotals build_plan(const Inst* insts, int n, void* buf, const void* dev, Plan
     t.upd += ((P.nx + kTileU - 1) / kTileU) * ((P.ny + 1) / 2) * img[q].usplit * P.vsplit * P.NC;
     if (G > 1)
       t.red += (nfx + t.red_faces - 1) / t.red_faces + (nfy + t.red_faces - 1) / t.red_faces +
-               (P.shak ? ((kSlotsShakhov - kSlotCell) * (int)P.nc + kWave * t.red_waves - 1) /
+               (P.shak ? ((kSlotsShakhov - kSlotCell) * P.nc + kWave * t.red_waves - 1) /
                              (kWave * t.red_waves)
                        : 0);
     else
