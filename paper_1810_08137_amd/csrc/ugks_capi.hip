@@ -473,14 +473,13 @@ struct StatePieces {
   }
 };
 
-// Host copies of pieces by the caller, where it would wait, and up to kCopiers - 1 threads that do
-// nothing else (one thread's copy is slower than the host link).  A checkpoint of 80 x 40 cells at
-// 29^2, a step in between, takes 1625 us; with the caller waiting and a thread more 1658.
+// Host copies of pieces, on up to kCopiers threads that do nothing else (one thread's copy is
+// slower than the host link).  Below two threads the caller copies, in hand().
 class Copiers {
  public:
   static constexpr int kCopiers = 4, kBlocks = 2 * kCopiers;
   Copiers(const StatePieces& sp, void* const* blk, int nb, int threads)
-      : sp_(sp), blk_(blk), nb_(nb), want_(threads - 1) {}
+      : sp_(sp), blk_(blk), nb_(nb), want_(threads > 1 ? threads : 0) {}
   ~Copiers() {
     {
       std::lock_guard<std::mutex> lock(m_);
@@ -490,7 +489,7 @@ class Copiers {
     for (int t = 0; t < started_; ++t) th_[t].join();  // after the copies handed over
   }
   // Block b holds (is to hold) piece p: its copy may begin.  Each of the first calls starts a
-  // thread; without any the caller copies at once.
+  // thread; if none will start, the caller copies.
   void hand(int b, long long p) {
     if (started_ < want_) {
       try {
@@ -513,8 +512,7 @@ class Copiers {
     }
     work_.notify_one();
   }
-  // A block whose copy has ended, each reported once; -1: none (with wait: none is under way).  A
-  // caller that would wait makes the next copy itself.
+  // A block whose copy has ended, each reported once; -1: none (with wait: none is under way).
   int take(bool wait) {
     std::unique_lock<std::mutex> lock(m_);
     for (;;) {
@@ -524,34 +522,29 @@ class Copiers {
           return b;
         }
       if (!wait || open_ == 0) return -1;
-      if (!copy_next(lock)) ended_.wait(lock);
+      ended_.wait(lock);
     }
   }
 
  private:
-  // Copies the first block that is ready, if any, without the lock.
-  bool copy_next(std::unique_lock<std::mutex>& lock) {
-    int b = 0;
-    while (b < nb_ && !ready_[b]) ++b;
-    if (b == nb_) return false;
-    ready_[b] = false;
-    const long long p = piece_[b];
-    lock.unlock();
-    sp_.copy(p, blk_[b]);
-    lock.lock();
-    done_[b] = true;
-    --open_;
-    return true;
-  }
   void run() {
     std::unique_lock<std::mutex> lock(m_);
     for (;;) {
-      if (copy_next(lock))
-        ended_.notify_one();
-      else if (stop_)
-        return;
-      else
+      int b = 0;
+      while (b < nb_ && !ready_[b]) ++b;
+      if (b == nb_) {
+        if (stop_) return;
         work_.wait(lock);
+        continue;
+      }
+      ready_[b] = false;
+      const long long p = piece_[b];
+      lock.unlock();
+      sp_.copy(p, blk_[b]);
+      lock.lock();
+      done_[b] = true;
+      --open_;
+      ended_.notify_one();
     }
   }
 
@@ -559,7 +552,7 @@ class Copiers {
   void* const* blk_;
   const int nb_;
   int want_, started_ = 0;
-  std::thread th_[kCopiers - 1];
+  std::thread th_[kCopiers];
   std::mutex m_;
   std::condition_variable work_, ended_;
   long long piece_[kBlocks] = {};
@@ -681,8 +674,7 @@ hipError_t move_state(ugks_handle* h, double* host, bool out, long long* launche
   sp.vels = (int)std::min<long long>(sp.nvt, cap);
   sp.cells = (int)std::max<long long>(1, std::min<long long>(sp.nc, cap / sp.nvt));
   sp.count = (sp.nc + sp.cells - 1) / sp.cells * ((sp.nvt + sp.vels - 1) / sp.vels);
-  // a copying thread for every four pieces (8 MB), the caller the first, at most four, with two blocks
-  // each
+  // a copying thread for every four pieces (8 MB), at most four, with two blocks each
   const int threads = (int)std::min<long long>(Copiers::kCopiers, (sp.count + 3) / 4);
   const int want = (int)std::min<long long>(sp.count, 2 * threads);
   void* blk[Copiers::kBlocks] = {};
